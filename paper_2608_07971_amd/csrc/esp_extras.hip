@@ -306,18 +306,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_nearest(KArgs a, NearestArgs 
 // Outer ESP-IAC rounds (Sec. 3.4, Alg. 1; thresholds of Eq. 11)
 // ---------------------------------------------------------------------------
 
-// One wavefront per cluster, after the round's tatonnement and re-selection:
+// One workgroup per cluster, after the round's tatonnement and re-selection:
 //  BinPack  jobs in index order; job j at its chosen configuration needs
 //           g = d[r_gpus] GPUs (a whole number in 1..8, else not placeable)
 //           and d[r_mem] / g memory and d[r_sm] / g compute on each; it takes
 //           the g lowest-index GPUs with room for one share (all or
-//           nothing).  Jobs are gathered 64 at a time (one per lane) and
-//           placed in order; each lane tests 4 consecutive GPUs, so one step
-//           covers 256, only in blocks whose summary (largest residuals,
-//           fewest jobs) admits the share, and ballots rank the fitting
-//           GPUs.  A job needing at least as much as a share that already
-//           failed in this round is skipped without a scan.  Residuals live
-//           in LDS, updated in job order (binary64, the oracle's operations).
+//           nothing; binary64 residuals, the oracle's operations).
 //  IAC      every pair of jobs sharing a GPU: S_x|y = 1 + a_x b_y against
 //           tau_x = tau_base_x + min(beta (U / U_target - 1), beta_max),
 //           U = busy GPUs / G; a pair violates when either slowdown exceeds
@@ -327,6 +321,28 @@ __global__ __launch_bounds__(kBlockThreads) void k_nearest(KArgs a, NearestArgs 
 //           fp32(penalty + kappa * excess), in the packed penalty column
 //           (its sign bit, the switching-cost mark, is kept).
 // A cluster without violations is frozen: later rounds' kernels skip it.
+//
+// First fit is one serial chain over the jobs, so its latency per job bounds
+// the kernel.  Wavefront 0 does nothing else: it holds every GPU's residuals
+// in registers (lane l, slot i: GPU 64 i + l), so testing a group of 4 slots
+// (256 GPUs) is 8 compares whose results are the wave-wide masks, and a share
+// is placed by the lanes that hold its GPUs, with no LDS round trip (the
+// occupants are written to LDS, read only after the packing).  The other
+// wavefronts gather the jobs ahead of it, kPackChunk batches of 64 at a time
+// into one of two LDS buffers, leaving out the jobs that cannot be placed.
+// The chain is bound by the issue of a lone wavefront (about 90 instructions
+// and 560 cycles per placed share, no memory access in it).  Measured per
+// round against one wavefront that gathered and placed with the residuals in
+// LDS: 4,096 jobs on 512 GPUs (1,035 jobs tried) 870 -> 268 us, 32 clusters of
+// 4,096 jobs on 576..768 GPUs 1,256 -> 396 us.
+//
+// Shortcuts, all exact because residuals only shrink while jobs are placed:
+//  - a job that needs at least as much (GPU count, memory and compute per
+//    GPU) as one that found no room is not tried (up to 64 such needs, none
+//    at or above another, one per lane of wavefront 0; the gathering
+//    wavefronts test against the list of the chunk before);
+//  - a group of 256 GPUs that had no GPU at all for a need is not visited
+//    for needs at or above it (two such needs per group, lane b: group b).
 // Wave-uniform copies of lane t's value (t uniform).
 __device__ __forceinline__ int lane_i(int v, int t) { return __builtin_amdgcn_readlane(v, t); }
 __device__ __forceinline__ double lane_d(double v, int t) {
@@ -336,263 +352,363 @@ __device__ __forceinline__ double lane_d(double v, int t) {
     return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
 }
 
-// Maximum of x and minimum of c over the 64 lanes (all active): DPP inside
-// each 16-lane row, then the four row results.
-__device__ __forceinline__ void wave_max2_min(double &x, double &y, int &c) {
-    x = fmax(x, dpp_d<kDppXor1>(x));
-    y = fmax(y, dpp_d<kDppXor1>(y));
-    c = min(c, dpp_i<kDppXor1>(c));
-    x = fmax(x, dpp_d<kDppXor2>(x));
-    y = fmax(y, dpp_d<kDppXor2>(y));
-    c = min(c, dpp_i<kDppXor2>(c));
-    x = fmax(x, dpp_d<kDppHalfMirror>(x));
-    y = fmax(y, dpp_d<kDppHalfMirror>(y));
-    c = min(c, dpp_i<kDppHalfMirror>(c));
-    x = fmax(x, dpp_d<kDppMirror>(x));
-    y = fmax(y, dpp_d<kDppMirror>(y));
-    c = min(c, dpp_i<kDppMirror>(c));
-    x = fmax(fmax(lane_d(x, 0), lane_d(x, 16)), fmax(lane_d(x, 32), lane_d(x, 48)));
-    y = fmax(fmax(lane_d(y, 0), lane_d(y, 16)), fmax(lane_d(y, 32), lane_d(y, 48)));
-    c = min(min(lane_i(c, 0), lane_i(c, 16)), min(lane_i(c, 32), lane_i(c, 48)));
-}
+constexpr int kPackWaves = 8;                            // wavefront 0 places, the others gather
+constexpr int kPackThreads = kPackWaves * kWaveSize;
+constexpr int kPackPer = 2;                              // batches per gathering wavefront and chunk
+constexpr int kPackChunk = (kPackWaves - 1) * kPackPer;  // batches of 64 jobs per chunk
+constexpr int kGroupSlots = 4;                           // slots per group: 256 GPUs
+constexpr int kGroups = kMaxGpus / (kGroupSlots * kWaveSize);
+static_assert((kMaxPerGpu & (kMaxPerGpu - 1)) == 0, "a GPU's entries of s_occ are found by masking");
+static_assert(kGroups <= 32, "two needs per group in the lanes of a wavefront");
 
-template <int R>
-__global__ __launch_bounds__(kWaveSize) void k_pack_iac(KArgs a, IacArgs m) {
-    constexpr int kPerLane = 4;                          // GPUs per lane in one scan step
-    constexpr int kStep = kWaveSize * kPerLane;          // GPUs per scan step
-    constexpr int kBlocks = kMaxGpus / kStep;
-    __shared__ double s_mem[kMaxGpus];
-    __shared__ double s_sm[kMaxGpus];
-    __shared__ int s_cnt[kMaxGpus];
-    __shared__ int s_occ[kMaxGpus][kMaxPerGpu];
-    __shared__ int s_sel[kMaxShards];
-    static_assert(kBlocks <= kWaveSize, "one lane per block summary");
+// GPUs of a group with room for a share: per slot, the lanes whose GPU has it.
+struct Room {
+    uint64_t mk[kGroupSlots];
+    __device__ __forceinline__ uint64_t any() const { return mk[0] | mk[1] | mk[2] | mk[3]; }
+    __device__ __forceinline__ int count() const {
+        return __popcll(mk[0]) + __popcll(mk[1]) + __popcll(mk[2]) + __popcll(mk[3]);
+    }
+    // The GPU of lowest index alone, the lowest lane's first slot (all: any(), not 0).
+    __device__ __forceinline__ Room first(uint64_t all) const {
+        const uint64_t r0 = all & (0 - all), r1 = r0 & ~mk[0], r2 = r1 & ~mk[1];
+        return {{r0 & mk[0], r1 & mk[1], r2 & mk[2], r2 & ~mk[2]}};
+    }
+};
+
+// One group of GPUs in the registers of a wavefront: GPU 4 l + i of the group
+// in lane l, slot i.
+struct GroupRoom {
+    double mem[kGroupSlots], sm[kGroupSlots];            // residuals; memory -inf: takes no more jobs
+    int at[kGroupSlots];                                 // the next free entry of s_occ
+
+    // GPUs with room (all compares first: their latencies overlap).
+    __device__ __forceinline__ Room room(double nm, double ns) const {
+        Room r;
+        uint64_t ok[kGroupSlots];
+#pragma unroll
+        for (int i = 0; i < kGroupSlots; ++i) r.mk[i] = __ballot(mem[i] >= nm);
+#pragma unroll
+        for (int i = 0; i < kGroupSlots; ++i) ok[i] = __ballot(sm[i] >= ns);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kGroupSlots; ++i) r.mk[i] &= ok[i];
+        return r;
+    }
+    // Take one share (nm, ns) from the one GPU in `t`; returns its entry of
+    // s_occ (in that GPU's lane).  One assembly block of predicated
+    // operations: written as branches, the compiler kept two copies of every
+    // residual and moved them at each job.  EXEC is saved and restored.
+    __device__ __forceinline__ int take(const Room &t, double nm, double ns) {
+        int w;
+        uint64_t ex;
+        asm volatile("s_mov_b64 %[ex], exec\n\t"
+                     "s_mov_b64 exec, %[e0]\n\t"
+                     "v_mov_b32 %[w], %[a0]\n\t"
+                     "v_add_f64 %[m0], %[m0], -%[nm]\n\t"
+                     "v_add_f64 %[s0], %[s0], -%[ns]\n\t"
+                     "v_add_u32 %[a0], 1, %[a0]\n\t"
+                     "s_mov_b64 exec, %[e1]\n\t"
+                     "v_mov_b32 %[w], %[a1]\n\t"
+                     "v_add_f64 %[m1], %[m1], -%[nm]\n\t"
+                     "v_add_f64 %[s1], %[s1], -%[ns]\n\t"
+                     "v_add_u32 %[a1], 1, %[a1]\n\t"
+                     "s_mov_b64 exec, %[e2]\n\t"
+                     "v_mov_b32 %[w], %[a2]\n\t"
+                     "v_add_f64 %[m2], %[m2], -%[nm]\n\t"
+                     "v_add_f64 %[s2], %[s2], -%[ns]\n\t"
+                     "v_add_u32 %[a2], 1, %[a2]\n\t"
+                     "s_mov_b64 exec, %[e3]\n\t"
+                     "v_mov_b32 %[w], %[a3]\n\t"
+                     "v_add_f64 %[m3], %[m3], -%[nm]\n\t"
+                     "v_add_f64 %[s3], %[s3], -%[ns]\n\t"
+                     "v_add_u32 %[a3], 1, %[a3]\n\t"
+                     "s_mov_b64 exec, %[ex]"
+                     : [m0] "+v"(mem[0]), [m1] "+v"(mem[1]), [m2] "+v"(mem[2]), [m3] "+v"(mem[3]), [s0] "+v"(sm[0]),
+                       [s1] "+v"(sm[1]), [s2] "+v"(sm[2]), [s3] "+v"(sm[3]), [a0] "+v"(at[0]), [a1] "+v"(at[1]),
+                       [a2] "+v"(at[2]), [a3] "+v"(at[3]), [w] "=&v"(w), [ex] "=&s"(ex)
+                     : [e0] "s"(t.mk[0]), [e1] "s"(t.mk[1]), [e2] "s"(t.mk[2]), [e3] "s"(t.mk[3]), [nm] "s"(nm),
+                       [ns] "s"(ns));
+        return w;
+    }
+    // The GPU in `t` is full: its memory no longer admits anything.
+    __device__ __forceinline__ void close(const Room &t) {
+#pragma unroll
+        for (int i = 0; i < kGroupSlots; ++i)
+            mem[i] = __builtin_amdgcn_inverse_ballot_w64(t.mk[i]) ? -__builtin_inf() : mem[i];
+    }
+};
+
+// Jobs of one batch that may still be placed, in job order.
+struct PackBatch {
+    double mem[kWaveSize], sm[kWaveSize];                // per share
+    int gj[kWaveSize];                                   // job - 64 * batch, shares in the low 4 bits
+};
+
+// Needs that found no room (entry 0 .. n - 1; g above any job's when unused).
+struct PackFails {
+    double mem[kWaveSize], sm[kWaveSize];
+    int g[kWaveSize];
+    int n;
+};
+
+__global__ __launch_bounds__(kPackThreads) void k_pack_iac(KArgs a, IacArgs m) {
+    __shared__ int s_occ[kMaxGpus * kMaxPerGpu];         // jobs of each GPU in placement order, -1 free
+    __shared__ double s_mem[kMaxGpus], s_sm[kMaxGpus];   // the groups that are not in registers
+    __shared__ int s_at[kMaxGpus];
+    __shared__ PackBatch s_batch[2][kPackChunk];
+    __shared__ int s_n[2][kPackChunk];
+    __shared__ PackFails s_fail[2];
+    __shared__ int s_used, s_viol;
     const int cl = blockIdx.x;
-    const int lane = threadIdx.x;
     if (a.flags[cl] & kFlagFrozen) return;
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
     const int G = m.gpus[cl];
-    const int nblk = (G + kStep - 1) / kStep;
     const int N = a.N;
     float *col = const_cast<float *>(a.table) + cl * a.cluster_stride;
     const int32_t *ch = m.choice + static_cast<size_t>(cl) * N;
-    // GPUs beyond G get no room at all (count kMaxPerGpu), so they never fit
-    for (int h = lane; h < nblk * kStep; h += kWaveSize) {
-        s_mem[h] = m.gpu_memory;
+    for (int i = tid; i < G * kMaxPerGpu; i += kPackThreads) s_occ[i] = -1;
+    for (int h = tid; h < (G + kGroupSlots * kWaveSize - 1) / (kGroupSlots * kWaveSize) * (kGroupSlots * kWaveSize); h += kPackThreads) {
+        s_mem[h] = h < G ? m.gpu_memory : -__builtin_inf();   // GPUs beyond G get no room at all
         s_sm[h] = m.gpu_compute;
-        s_cnt[h] = h < G ? 0 : kMaxPerGpu;
-#pragma unroll
-        for (int i = 0; i < kMaxPerGpu; ++i) s_occ[h][i] = -1;
+        s_at[h] = h * kMaxPerGpu;
     }
-    // Lane c < nblk keeps block c's summary in registers: largest residual
-    // memory and compute over its GPUs that can still take a job, fewest
-    // jobs, or bounds on them (upper, upper, lower).  A block failing any of
-    // the three cannot hold the share, so skipping it is exact.
-    double sum_m = m.gpu_memory, sum_s = m.gpu_compute;
-    int sum_c = lane < nblk ? 0 : kMaxPerGpu;
-    // Lane l remembers a share that found no room in this round (GPU count,
-    // memory and compute per GPU; the lanes are filled in turn).  Residuals
-    // only shrink and counts only grow while jobs are placed, so a job that
-    // needs at least as much in all three as a remembered failure cannot be
-    // placed either: it is skipped without a scan.
-    int fail_g = 0x7fffffff;
-    double fail_m = __builtin_inf(), fail_s = __builtin_inf();
-    int n_fail = 0;
-    wave_sync();
-    const uint64_t below = (1ull << lane) - 1ull;
-    // Jobs 64 at a time: each lane gathers one job's share (GPU count,
-    // memory and compute per GPU), then the wavefront places them in order.
-    // The gathers run one batch ahead: while a batch is placed (LDS and
-    // registers only), the next batch's table values and the choices and
-    // family slots of the batch after it are in flight.  Indices past N are
-    // clamped (loaded, then ignored), so every load stays in bounds.
-    auto job_entry = [&](int j0, int &k, size_t &base) {
-        const int jl = min(j0 + lane, N - 1);
-        k = ch[jl];
-        base = a.K > 0 ? static_cast<size_t>(jl) * a.K : static_cast<size_t>(a.jobs[jl].slot);
-    };
-    auto share_of = [&](int k, size_t base, float &gv, float &mv, float &sv) {
-        const size_t e = base + static_cast<size_t>(k > 0 ? k : 0);
-        gv = col[(m.r_gpus + 1) * a.col_len + e];
-        mv = col[(m.r_mem + 1) * a.col_len + e];
-        sv = col[(m.r_sm + 1) * a.col_len + e];
-    };
-    int k_cur, k_next;
-    size_t b_cur, b_next;
-    float gv_cur, mv_cur, sv_cur;
-    job_entry(0, k_cur, b_cur);
-    share_of(k_cur, b_cur, gv_cur, mv_cur, sv_cur);
-    job_entry(kWaveSize, k_next, b_next);
-    for (int j0 = 0; j0 < N; j0 += kWaveSize) {
-        float gv_n, mv_n, sv_n;
-        share_of(k_next, b_next, gv_n, mv_n, sv_n);
-        int k_after;
-        size_t b_after;
-        job_entry(j0 + 2 * kWaveSize, k_after, b_after);
-        int g_l = 0;
-        double nm_l = 0.0, ns_l = 0.0;
-        const double gv = static_cast<double>(gv_cur);
-        if ((j0 + lane < N) & (k_cur >= 0) & (gv >= 1.0) & (gv <= static_cast<double>(kMaxShards)) &
-            (gv == floor(gv))) {
-            g_l = static_cast<int>(gv);
-            nm_l = static_cast<double>(mv_cur) / gv;
-            ns_l = static_cast<double>(sv_cur) / gv;
+    if (tid < 2) s_fail[tid].n = 0;
+    if (tid == 0) s_used = s_viol = 0;
+    const int batches = (N + kWaveSize - 1) / kWaveSize;
+    const int chunks = (batches + kPackChunk - 1) / kPackChunk;
+
+    // Gathering wavefronts: batch (wave - 1) + 7 u of chunk c, into buffer c & 1.
+    // Indices past N are clamped (loaded, then ignored), so the loads of all
+    // batches are issued together and stay in bounds.
+    auto gather = [&](int c) {
+        int k[kPackPer], size[kPackPer];
+        size_t base[kPackPer];
+        float gv[kPackPer], mv[kPackPer], sv[kPackPer];
+#pragma unroll
+        for (int u = 0; u < kPackPer; ++u) {
+            const int b = c * kPackChunk + (wave - 1) + u * (kPackWaves - 1);
+            const int jl = static_cast<int>(min(static_cast<int64_t>(b) * kWaveSize + lane, static_cast<int64_t>(N - 1)));
+            k[u] = ch[jl];
+            if (a.K > 0) {
+                base[u] = static_cast<size_t>(jl) * a.K;
+                size[u] = a.K;
+            } else {
+                const JobSlot js = a.jobs[jl];
+                base[u] = js.slot;
+                size[u] = static_cast<int>(js.size);
+            }
         }
-        k_cur = k_next;
-        gv_cur = gv_n;
-        mv_cur = mv_n;
-        sv_cur = sv_n;
-        k_next = k_after;
-        b_next = b_after;
-        const int cnt = min(kWaveSize, N - j0);
-        // jobs of the batch already ruled out by the failures remembered so
-        // far (each lane tests its own job against every remembered one)
-        bool ruled_out = g_l == 0;
-        for (int f = 0; f < min(n_fail, kWaveSize); ++f) {
-            const int fg = lane_i(fail_g, f);
-            const double fm = lane_d(fail_m, f), fs = lane_d(fail_s, f);
-            ruled_out = ruled_out | ((g_l >= fg) & (nm_l >= fm) & (ns_l >= fs));
+#pragma unroll
+        for (int u = 0; u < kPackPer; ++u) {
+            const size_t e = base[u] + static_cast<size_t>(((k[u] >= 0) & (k[u] < size[u])) ? k[u] : 0);
+            gv[u] = col[(m.r_gpus + 1) * a.col_len + e];
+            mv[u] = col[(m.r_mem + 1) * a.col_len + e];
+            sv[u] = col[(m.r_sm + 1) * a.col_len + e];
         }
-        const uint64_t skip = __ballot(ruled_out);
-        for (int t = 0; t < cnt; ++t) {
-            if ((skip >> t) & 1ull) continue;             // not placeable, or needs more than a failure
-            const int g = lane_i(g_l, t);
-            const double nm = lane_d(nm_l, t);
-            const double ns = lane_d(ns_l, t);
-            // failures remembered within this batch
-            if (__ballot((g >= fail_g) & (nm >= fail_m) & (ns >= fail_s)) != 0ull) continue;
-            uint64_t cand = __ballot((sum_c < kMaxPerGpu) & (sum_m >= nm) & (sum_s >= ns));
-            int found = 0, visited = 0;
-            // the last visited block's GPUs of this lane, and which of them fit
-            int c = 0, h0 = 0, before = 0;
-            bool fit[kPerLane];
-            int cv[kPerLane];
-            double mv[kPerLane], sv[kPerLane];
-            while ((cand != 0ull) & (found < g)) {
-                c = __builtin_ctzll(cand);
-                cand &= cand - 1ull;
-                ++visited;
-                // lane l tests GPUs c*256 + 4l .. 4l+3 (ascending with the lane)
-                h0 = c * kStep + lane * kPerLane;
-                int total = 0;
-                before = 0;
+        const PackFails &fl = s_fail[c & 1];
+        const int nf = fl.n;
 #pragma unroll
-                for (int i = 0; i < kPerLane; ++i) {
-                    cv[i] = s_cnt[h0 + i];
-                    mv[i] = s_mem[h0 + i];
-                    sv[i] = s_sm[h0 + i];
+        for (int u = 0; u < kPackPer; ++u) {
+            const int q = (wave - 1) + u * (kPackWaves - 1);
+            const int64_t j = (static_cast<int64_t>(c) * kPackChunk + q) * kWaveSize + lane;
+            const double g = static_cast<double>(gv[u]);
+            const double nm = static_cast<double>(mv[u]) / g;
+            const double ns = static_cast<double>(sv[u]) / g;
+            bool ok = (j < N) & (k[u] >= 0) & (k[u] < size[u]) & (g >= 1.0) &
+                      (g <= static_cast<double>(kMaxShards)) & (g == floor(g));
+            const int gi = ok ? static_cast<int>(g) : 0;
+            for (int f = 0; f < nf; ++f) ok = ok & !((gi >= fl.g[f]) & (nm >= fl.mem[f]) & (ns >= fl.sm[f]));
+            const uint64_t keep = __ballot(ok);
+            PackBatch &o = s_batch[c & 1][q];
+            if (ok) {
+                const int at = __popcll(keep & ((1ull << lane) - 1ull));
+                o.mem[at] = nm;
+                o.sm[at] = ns;
+                o.gj[at] = (lane << 4) | gi;
+            }
+            if (lane == 0) s_n[c & 1][q] = __popcll(keep);
+        }
+    };
+
+    if (wave > 0) {
+        __syncthreads();                                   // the empty failure lists are there
+        gather(0);
+        __syncthreads();
+        for (int c = 0; c < chunks; ++c) {
+            if (c + 1 < chunks) gather(c + 1);
+            __syncthreads();
+        }
+    } else {
+        GroupRoom gr;                                      // the GPUs of group `cur`
+        int cur = 0;
+        auto load = [&]() {
+#pragma unroll
+            for (int i = 0; i < kGroupSlots; ++i) {
+                const int h = (cur * kWaveSize + lane) * kGroupSlots + i;
+                gr.mem[i] = s_mem[h];
+                gr.sm[i] = s_sm[h];
+                gr.at[i] = s_at[h];
+            }
+            // arrived before any job is tested: none then waits for the LDS stores of the job before
+#pragma unroll
+            for (int i = 0; i < kGroupSlots; ++i) asm volatile("" : "+v"(gr.mem[i]), "+v"(gr.sm[i]), "+v"(gr.at[i]));
+        };
+        auto swap_in = [&](int b) {
+#pragma unroll
+            for (int i = 0; i < kGroupSlots; ++i) {
+                const int h = (cur * kWaveSize + lane) * kGroupSlots + i;
+                s_mem[h] = gr.mem[i];
+                s_sm[h] = gr.sm[i];
+                s_at[h] = gr.at[i];
+            }
+            cur = b;
+            load();
+        };
+        const uint32_t groups = (2u << ((G - 1) / (kGroupSlots * kWaveSize))) - 1u;
+        const double inf = __builtin_inf();
+        double none_m = inf, none_s = inf;                 // lanes b and 32 + b: needs group b had no GPU for
+        double fail_m = inf, fail_s = inf;                 // lane f: a need that found no room
+        int fail_g = 0x7fffffff;
+        int n_fail = 0, ring = 0;
+        uint64_t fresh = 0, fresh_prev = 0;                // entries the gathering wavefronts have not seen
+        __syncthreads();
+        load();
+        __syncthreads();
+        for (int c = 0; c < chunks; ++c) {
+            // (the batches of this chunk were tested against the list of the end of chunk c - 2)
+            for (int q = 0; q < kPackChunk; ++q) {
+                const int n = __builtin_amdgcn_readfirstlane(s_n[c & 1][q]);
+                if (n == 0) continue;
+                const int j0 = (c * kPackChunk + q) * kWaveSize;
+                const PackBatch &in = s_batch[c & 1][q];
+                double nm_l = in.mem[lane], ns_l = in.sm[lane];
+                int gj_l = in.gj[lane];
+                // arrived before the loop: no job then waits for the LDS stores of the one before
+                asm volatile("" : "+v"(nm_l), "+v"(ns_l), "+v"(gj_l));
+                const int g_l = gj_l & 15;
+                int out = lane >= n;
+                for (uint64_t fs = fresh | fresh_prev; fs != 0; fs &= fs - 1) {
+                    const int f = __builtin_ctzll(fs);
+                    out |= static_cast<int>(g_l >= lane_i(fail_g, f)) & static_cast<int>(nm_l >= lane_d(fail_m, f)) &
+                           static_cast<int>(ns_l >= lane_d(fail_s, f));
                 }
-#pragma unroll
-                for (int i = 0; i < kPerLane; ++i) {
-                    fit[i] = (cv[i] < kMaxPerGpu) & (mv[i] >= nm) & (sv[i] >= ns);
-                    const uint64_t bal = __ballot(fit[i]);
-                    before += __popcll(bal & below);
-                    total += __popcll(bal);
-                }
-                int rank = found + before;
-#pragma unroll
-                for (int i = 0; i < kPerLane; ++i) {
-                    if (fit[i]) {
-                        if (rank < g) s_sel[rank] = h0 + i;
-                        ++rank;
+                uint64_t todo = __ballot(out == 0);
+                // The next job's need is read into scalars while a job is placed.
+                int gj_n;
+                double nm_n, ns_n;
+                auto fetch = [&]() {
+                    const int t = __builtin_ctzll(todo | (1ull << (kWaveSize - 1)));   // (some lane's when none is left)
+                    gj_n = lane_i(gj_l, t);
+                    nm_n = lane_d(nm_l, t);
+                    ns_n = lane_d(ns_l, t);
+                };
+                fetch();
+                while (todo != 0) {
+                    int g, job;
+                    double nm, ns;
+                    uint32_t cand;
+                    Room r;
+                    // one share on the first GPU of r (all: r.any())
+                    auto put = [&](uint64_t all) {
+                        const Room t = r.first(all);
+                        const int w = gr.take(t, nm, ns);
+                        const uint64_t bit = all & (0 - all);
+                        if (__builtin_amdgcn_inverse_ballot_w64(bit)) s_occ[w] = job;
+                        if (__builtin_expect((__ballot((w & (kMaxPerGpu - 1)) == kMaxPerGpu - 1) & bit) != 0, 0))
+                            gr.close(t);
+                        return t;
+                    };
+                    // most jobs: one share, room in the group in registers, no group before it that may have room
+                    // (a loop of its own, so that its state stays in place in the registers)
+                    bool here = false;
+                    const uint32_t cur_bit = 1u << cur;
+                    do {
+                        g = gj_n & 15;
+                        job = j0 + (gj_n >> 4);
+                        nm = nm_n;
+                        ns = ns_n;
+                        todo &= todo - 1;
+                        const uint64_t none_a = __ballot(nm >= none_m), none_b = __ballot(ns >= none_s);
+                        r = gr.room(nm, ns);
+                        fetch();
+                        const uint64_t none = none_a & none_b;
+                        cand = ~static_cast<uint32_t>(none | (none >> 32)) & groups;
+                        here = (static_cast<uint32_t>(g ^ 1) | ((cand & (0u - cand)) ^ cur_bit)) == 0;
+                        if (!here) break;
+                        const uint64_t all = r.any();
+                        here = all != 0;
+                        if (!here) break;
+                        put(all);
+                    } while (todo != 0);
+                    if (here) break;
+                    // group by group: count the room up to g GPUs, then place (all or nothing)
+                    int found = 0;
+                    for (uint32_t cs = cand; cs != 0 && found < g; cs &= cs - 1u) {
+                        const int b = __builtin_ctz(cs);
+                        if (b != cur) {
+                            swap_in(b);
+                            r = gr.room(nm, ns);
+                        }
+                        const int k = r.count();
+                        if (k == 0) {
+                            // group b has no GPU for this need: kept in place of a need at or above it, else of
+                            // the second
+                            const uint64_t over = __ballot(none_m >= nm) & __ballot(none_s >= ns);
+                            const bool mine = lane == (((over >> b) & 1u) ? b : 32 + b);
+                            none_m = mine ? nm : none_m;
+                            none_s = mine ? ns : none_s;
+                        }
+                        found += k;
                     }
-                }
-                if (found + total < g) {
-                    // the block cannot complete the share: make its summary
-                    // exact from the values just read
-                    double xm = -__builtin_inf(), xs = -__builtin_inf();
-                    int xc = kMaxPerGpu;
+                    if (found >= g) {
+                        int rem = g;
+                        for (uint32_t cs = cand; rem > 0; cs &= cs - 1u) {
+                            const int b = __builtin_ctz(cs);
+                            if (b != cur) {
+                                swap_in(b);
+                                r = gr.room(nm, ns);
+                            }
+                            for (; rem > 0 && r.any() != 0; --rem) {
+                                const Room t = put(r.any());
 #pragma unroll
-                    for (int i = 0; i < kPerLane; ++i) {
-                        const bool open = cv[i] < kMaxPerGpu;
-                        xm = open ? fmax(xm, mv[i]) : xm;
-                        xs = open ? fmax(xs, sv[i]) : xs;
-                        xc = min(xc, cv[i]);
+                                for (int i = 0; i < kGroupSlots; ++i) r.mk[i] &= ~t.mk[i];
+                            }
+                        }
+                        continue;
                     }
-                    wave_max2_min(xm, xs, xc);
-                    if (lane == c) {
-                        sum_m = xm;
-                        sum_s = xs;
-                        sum_c = xc;
-                    }
-                }
-                found += total;
-            }
-            if (found < g) {                               // all or nothing
-                if (lane == (n_fail & (kWaveSize - 1))) {
-                    fail_g = g;
-                    fail_m = nm;
-                    fail_s = ns;
-                }
-                ++n_fail;
-                wave_sync();
-                continue;
-            }
-            if (visited == 1) {
-                // The share lies in one block: each selected GPU's lane updates
-                // it from the values it holds (no second round trip through
-                // LDS).  The block's summary is left as it was: residuals only
-                // shrink and counts only grow, so it stays an upper bound, and
-                // skipping the blocks it rules out stays exact; it is made exact
-                // again when a visit finds the block unable to complete a share.
-                int rank = before;
-#pragma unroll
-                for (int i = 0; i < kPerLane; ++i) {
-                    const bool take = fit[i] & (rank < g);
-                    rank += fit[i] ? 1 : 0;
-                    if (take) {
-                        s_mem[h0 + i] = mv[i] - nm;
-                        s_sm[h0 + i] = sv[i] - ns;
-                        s_occ[h0 + i][cv[i]] = j0 + t;
-                        s_cnt[h0 + i] = cv[i] + 1;
-                    }
-                }
-                wave_sync();
-                continue;
-            }
-            wave_sync();
-            if (lane < g) {
-                const int h = s_sel[lane];
-                const double mh = s_mem[h], sh_ = s_sm[h];
-                const int ch_ = s_cnt[h];
-                s_mem[h] = mh - nm;
-                s_sm[h] = sh_ - ns;
-                s_occ[h][ch_] = j0 + t;
-                s_cnt[h] = ch_ + 1;
-            }
-            wave_sync();
-            // refresh the summaries of the blocks that changed
-            int last = -1;
-            for (int i = 0; i < g; ++i) {
-                const int cb = s_sel[i] / kStep;
-                if (cb == last) continue;
-                last = cb;
-                const int hb = cb * kStep + lane * kPerLane;
-                double xm = -__builtin_inf(), xs = -__builtin_inf();
-                int xc = kMaxPerGpu;
-#pragma unroll
-                for (int q = 0; q < kPerLane; ++q) {
-                    const int cq = s_cnt[hb + q];
-                    const double mq = s_mem[hb + q], sq = s_sm[hb + q];
-                    const bool open = cq < kMaxPerGpu;           // GPUs that can still take a job
-                    xm = open ? fmax(xm, mq) : xm;
-                    xs = open ? fmax(xs, sq) : xs;
-                    xc = min(xc, cq);
-                }
-                wave_max2_min(xm, xs, xc);
-                if (lane == cb) {
-                    sum_m = xm;
-                    sum_s = xs;
-                    sum_c = xc;
+                    // no room: remember the need in place of one at or above it (unused entries are), else the oldest
+                    const uint64_t over = __ballot(fail_g >= g) & __ballot(fail_m >= nm) & __ballot(fail_s >= ns);
+                    const int f = over != 0 ? __builtin_ctzll(over) : ring;
+                    if (over == 0) ring = (ring + 1) & (kWaveSize - 1);
+                    fail_g = lane == f ? g : fail_g;
+                    fail_m = lane == f ? nm : fail_m;
+                    fail_s = lane == f ? ns : fail_s;
+                    n_fail = max(n_fail, f + 1);
+                    fresh |= 1ull << f;
+                    todo &= ~(__ballot(g_l >= g) & __ballot(nm_l >= nm) & __ballot(ns_l >= ns));
+                    fetch();
                 }
             }
+            // the list as it stands, for the gather of chunk c + 2 (which starts after the barrier)
+            PackFails &fl = s_fail[c & 1];
+            fl.mem[lane] = fail_m;
+            fl.sm[lane] = fail_s;
+            fl.g[lane] = fail_g;
+            if (lane == 0) fl.n = n_fail;
+            fresh_prev = fresh;
+            fresh = 0;
+            __syncthreads();
         }
     }
+
     // thresholds of Eq. 11
     int used = 0;
-    for (int h = lane; h < G; h += kWaveSize) used += s_cnt[h] > 0;
-#pragma unroll
-    for (int off = kWaveSize / 2; off > 0; off >>= 1) used += __shfl_xor(used, off);
-    double q = static_cast<double>(used) / static_cast<double>(G);
+    for (int h = tid; h < G; h += kPackThreads) used += s_occ[h * kMaxPerGpu] >= 0;
+    if (used) atomicAdd(&s_used, used);
+    __syncthreads();
+    double q = static_cast<double>(s_used) / static_cast<double>(G);
     q = q / m.u_target;
     const double w = q - 1.0;
     double add = m.beta * w;
@@ -602,43 +718,70 @@ __global__ __launch_bounds__(kWaveSize) void k_pack_iac(KArgs a, IacArgs m) {
     const double *tb = m.tau_base + static_cast<size_t>(cl) * N;
     unsigned long long *inc = reinterpret_cast<unsigned long long *>(m.inc) + static_cast<size_t>(cl) * N;
     int V = 0;
-    for (int h = lane; h < G; h += kWaveSize) {
-        const int n = s_cnt[h];
-        for (int x = 0; x < n; ++x)
-            for (int y = x + 1; y < n; ++y) {
-                const int jx = s_occ[h][x], jy = s_occ[h][y];
-                const int64_t ex = m.offsets[jx] + ch[jx], ey = m.offsets[jy] + ch[jy];
-                double sxy = static_cast<double>(sa[ex]) * static_cast<double>(pb[ey]);
-                sxy = 1.0 + sxy;
-                double syx = static_cast<double>(sa[ey]) * static_cast<double>(pb[ex]);
-                syx = 1.0 + syx;
-                const double ox = sxy - (tb[jx] + add);
-                const double oy = syx - (tb[jy] + add);
-                if (ox > 0.0) atomicMax(&inc[jx], static_cast<unsigned long long>(__double_as_longlong(ox)));
-                if (oy > 0.0) atomicMax(&inc[jy], static_cast<unsigned long long>(__double_as_longlong(oy)));
+    for (int h = tid; h < G; h += kPackThreads) {
+        // the GPU's jobs: all loads of a step in flight together (free slots read job 0, then are ignored)
+        int j[kMaxPerGpu];
+        int64_t e[kMaxPerGpu];
+        double sv[kMaxPerGpu], pv[kMaxPerGpu], tv[kMaxPerGpu];
+        if (s_occ[h * kMaxPerGpu + 1] < 0) continue;       // at most one job: no pair
+#pragma unroll
+        for (int x = 0; x < kMaxPerGpu; ++x) {
+            j[x] = s_occ[h * kMaxPerGpu + x];
+            const int jc = max(j[x], 0);
+            e[x] = m.offsets[jc] + ch[jc];
+            e[x] = j[x] >= 0 ? e[x] : 0;
+            tv[x] = tb[jc] + add;
+        }
+#pragma unroll
+        for (int x = 0; x < kMaxPerGpu; ++x) {
+            sv[x] = static_cast<double>(sa[e[x]]);
+            pv[x] = static_cast<double>(pb[e[x]]);
+        }
+#pragma unroll
+        for (int x = 0; x < kMaxPerGpu; ++x)
+#pragma unroll
+            for (int y = x + 1; y < kMaxPerGpu; ++y) {
+                if (j[y] < 0) continue;
+                const double sxy = 1.0 + sv[x] * pv[y];
+                const double syx = 1.0 + sv[y] * pv[x];
+                const double ox = sxy - tv[x];
+                const double oy = syx - tv[y];
+                if (ox > 0.0) atomicMax(&inc[j[x]], static_cast<unsigned long long>(__double_as_longlong(ox)));
+                if (oy > 0.0) atomicMax(&inc[j[y]], static_cast<unsigned long long>(__double_as_longlong(oy)));
                 V += (ox > 0.0 || oy > 0.0) ? 1 : 0;
             }
     }
+    if (V) atomicAdd(&s_viol, V);
+    __threadfence();                                       // the maxima are complete before they are read
+    __syncthreads();
+    V = s_viol;
+    // Gamma: whoever takes a job's largest excess (and leaves 0) raises its penalty
+    if (V > 0) {
+        float *pcol = col + static_cast<size_t>(m.pen_col) * a.col_len;
+        for (int h = tid; h < G; h += kPackThreads) {
+            int j[kMaxPerGpu];
+            unsigned long long bits[kMaxPerGpu];
 #pragma unroll
-    for (int off = kWaveSize / 2; off > 0; off >>= 1) V += __shfl_xor(V, off);
-    __threadfence();                                   // the maxima are complete before they are read
-    float *pcol = col + static_cast<size_t>(R + 1) * a.col_len;
-    for (int j = lane; j < N; j += kWaveSize) {
-        const unsigned long long bits = __hip_atomic_load(&inc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (bits == 0ull) continue;
-        __hip_atomic_store(&inc[j], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const double x = __longlong_as_double(static_cast<long long>(bits));
-        const size_t e = (a.K > 0 ? static_cast<size_t>(j) * a.K : static_cast<size_t>(a.jobs[j].slot)) + ch[j];
-        const uint32_t old = __float_as_uint(pcol[e]);
-        const float mag = __uint_as_float(old & 0x7fffffffu);
-        const float nv = __double2float_rn(static_cast<double>(mag) + m.kappa * x);
-        pcol[e] = __uint_as_float(__float_as_uint(nv) | (old & 0x80000000u));
+            for (int x = 0; x < kMaxPerGpu; ++x) {
+                j[x] = s_occ[h * kMaxPerGpu + x];
+                bits[x] = j[x] >= 0 ? atomicExch(&inc[j[x]], 0ull) : 0ull;
+            }
+#pragma unroll
+            for (int x = 0; x < kMaxPerGpu; ++x) {
+                if (bits[x] == 0ull) continue;
+                const double ex = __longlong_as_double(static_cast<long long>(bits[x]));
+                const size_t e = (a.K > 0 ? static_cast<size_t>(j[x]) * a.K : static_cast<size_t>(a.jobs[j[x]].slot)) +
+                                 ch[j[x]];
+                const uint32_t old = __float_as_uint(pcol[e]);
+                const float mag = __uint_as_float(old & 0x7fffffffu);
+                const float nv = __double2float_rn(static_cast<double>(mag) + m.kappa * ex);
+                pcol[e] = __uint_as_float(__float_as_uint(nv) | (old & 0x80000000u));
+            }
+        }
     }
     int32_t *gj = m.gpu_jobs + static_cast<size_t>(cl) * m.gmax * kMaxPerGpu;
-    for (int h = lane; h < m.gmax; h += kWaveSize)
-#pragma unroll
-        for (int i = 0; i < kMaxPerGpu; ++i) gj[h * kMaxPerGpu + i] = h < G ? s_occ[h][i] : -1;
-    if (lane == 0) {
+    for (int i = tid; i < m.gmax * kMaxPerGpu; i += kPackThreads) gj[i] = i < G * kMaxPerGpu ? s_occ[i] : -1;
+    if (tid == 0) {
         m.violations[cl] = V;
         m.rounds_used[cl] = m.round;
         if (V == 0) a.flags[cl] = a.flags[cl] | kFlagFrozen;
@@ -689,16 +832,12 @@ hipError_t launch_nearest(int R, const KArgs &a, const NearestArgs &na, hipStrea
 #undef CALL
 }
 
-template <int R>
-static hipError_t launch_pack_iac_r(const KArgs &a, const IacArgs &m, int B, hipStream_t s) {
-    hipLaunchKernelGGL((k_pack_iac<R>), dim3(static_cast<unsigned>(B)), dim3(kWaveSize), 0, s, a, m);
-    return hipGetLastError();
-}
-
 hipError_t launch_pack_iac(int R, const KArgs &a, const IacArgs &m, int B, hipStream_t s) {
-#define CALL(RR) launch_pack_iac_r<RR>(a, m, B, s)
-    ESP_DISPATCH_R(R, CALL)
-#undef CALL
+    IacArgs mm = m;
+    mm.pen_col = R + 1;
+    const dim3 grid(static_cast<unsigned>(B)), block(kPackThreads);
+    hipLaunchKernelGGL(k_pack_iac, grid, block, 0, s, a, mm);
+    return hipGetLastError();
 }
 
 hipError_t launch_iac_reset(int R, const KArgs &a, int B, int zero_gamma, hipStream_t s) {

@@ -50,10 +50,10 @@ constexpr int kDirWords = 16;                       // one 64-byte record
 constexpr int kDirFamilies = 4 * (kDirWords - 1);   // 60 sizes of one byte
 static_assert(kMaxFamily <= 256, "family sizes minus one fit a byte");
 
-// Outer ESP-IAC rounds (Alg. 1): one wavefront per cluster packs the
+// Outer ESP-IAC rounds (Alg. 1): one workgroup per cluster packs the
 // selection onto GPUs (first fit), evaluates co-located pairs and raises the
 // penalties of offending configurations.
-constexpr int kMaxGpus = 2048;                      // GPUs per cluster (LDS-resident residuals)
+constexpr int kMaxGpus = 2048;                      // GPUs per cluster (residuals in one wavefront's registers)
 constexpr int kMaxPerGpu = 4;                       // jobs sharing one GPU
 constexpr int kMaxShards = 8;                       // GPUs of one job
 
@@ -75,6 +75,7 @@ struct IacArgs {
     int32_t *rounds_used;          // [B] out
     int32_t *violations;           // [B] out
     int32_t round;                 // 1-based
+    int32_t pen_col;               // column of the penalties (set by the launcher)
 };
 
 

@@ -74,6 +74,29 @@ def test_schedule_matches_oracle(name):
         _compare(inst, model, M, T)
 
 
+# GPUs around the 64-GPU slots, the 256-GPU groups and the register instances
+# (256, 512, 1024, 2048 GPUs) of the packing kernel; jobs around its batches of
+# 64 and chunks of 14 batches; T = 0 takes every job's favourite configuration
+# (8 whole GPUs, shares split over groups, many failures), T = 3 small shares.
+@pytest.mark.parametrize("gpus,n_jobs", [(1, 1), (3, 63), (64, 65), (65, 128), (255, 300), (256, 895), (257, 896),
+                                         (300, 897), (512, 1793), (513, 700), (1024, 1500), (1025, 2700),
+                                         (2047, 3000), (2048, 2048)])
+def test_packing_edges(gpus, n_jobs):
+    _say(f"packing edges: {gpus} GPUs, {n_jobs} jobs")
+    dense = workloads.make("small", n_jobs=n_jobs)
+    ragged = workloads.make("ragged", n_jobs=n_jobs)
+    for inst, mem, T in ((dense, 80.0, 0), (dense, 80.0, 3), (dense, 40.0, 3), (ragged, 60.0, 1)):
+        model = workloads.iac_model(inst, gpus=[gpus], gpu_memory=mem, gpu_compute=2.0 if mem == 40.0 else 1.0)
+        _compare(inst, model, 2, T)
+
+
+def test_packing_mixed_cluster_sizes():
+    """One launch over clusters far below and at the instance's size."""
+    inst = workloads.make("batched", n_jobs=500, n_clusters=4)
+    _say("packing of clusters with 1, 64, 700 and 2048 GPUs")
+    _compare(inst, workloads.iac_model(inst, gpus=[1, 64, 700, 2048]), 2, 2)
+
+
 def test_schedule_with_switching_cost_and_tolerance():
     """Switching costs stay through Gamma's reset; rounds use a stop
     tolerance (the persistent driver)."""
