@@ -66,7 +66,9 @@ enum { ESP_STEP_CONST = 0, ESP_STEP_INV_SQRT = 1 };
 enum {
     ESP_MODE_AUTO = 0,        /* resident (below) when the table fits; else persistent for
                                  short passes (packed table of at most
-                                 ESP_AUTO_PERSISTENT_BYTES), where launch latency would dominate,
+                                 ESP_AUTO_PERSISTENT_BYTES), where launch latency would dominate
+                                 (a dense table that fits the registers and LDS of the device
+                                 stays there for the launch),
                                  and for solves with tol > 0 (the loop ends on the device once
                                  every cluster has converged); one launch per iteration
                                  otherwise, where the two drivers run at about the same speed; falls
@@ -81,7 +83,7 @@ enum {
                                  (every wavefront of the grid holds at most two 256-entry tiles:
                                  tables of up to about 2,000 tiles per cluster); each iteration
                                  is completed inside the launch, the workgroups of a cluster
-                                 exchanging their exact sums through tagged words (cooperative
+                                 exchanging their exact sums through counted words (cooperative
                                  launch; ESP_ERR_DEVICE when the grid cannot be co-resident).
                                  esp_create returns ESP_ERR_SHAPE when the table does not fit.
                                  ESP_MODE_AUTO takes this driver whenever the table fits. */

@@ -39,12 +39,13 @@ struct Plan {
     int tiles = 0;      // per cluster
     size_t col_len = 0; // floats per column
     int nblk = 0;       // workgroups per cluster
+    int nblk_res = 0;   // the same in resident launches (at most; see resident_shape)
     int aos_stride = 0; // floats per entry of the entry-major copy, 0 when there is none
     int64_t aos_lines = 0;  // kStoreLine-byte lines of one cluster's entry-major copy
     // workspace offsets (bytes)
     size_t o_table = 0, o_meta = 0, o_jobs = 0, o_shift = 0, o_cap = 0, o_eta = 0, o_part = 0,
            o_tick = 0, o_flags = 0, o_iters = 0, o_sync = 0, o_swc = 0, o_status = 0, o_capp = 0, o_offs = 0, o_inc = 0, o_gpus = 0,
-           o_aos = 0, o_dir = 0, o_lamws = 0, o_conv = 0, o_xch = 0, total = 0;
+           o_aos = 0, o_dir = 0, o_lamws = 0, o_conv = 0, total = 0;
     size_t columns() const { return static_cast<size_t>(R) + 1 + (pen ? 1 : 0); }
 };
 
@@ -153,6 +154,18 @@ esp_status make_plan(const esp_problem *p, const esp_options *opt, Plan *pl) {
     int nblk = (opt && opt->blocks_per_cluster > 0) ? opt->blocks_per_cluster
                                                      : std::max(1, (total + pl->B - 1) / pl->B);
     pl->nblk = std::min(nblk, max_useful);
+    // Resident launches of dense tables read no table in their loop: they use
+    // every compute unit (fewer tiles per wavefront), one workgroup on each.
+    // A table whose tiles fit one workgroup's registers stays in one: the
+    // exchange between workgroups costs more than the tiles (64 jobs x 64 x 8,
+    // 16 tiles: 2.6 us an iteration against 3.0 on four workgroups, and no
+    // cooperative launch, 28 against 46 us for a one-iteration solve; at 25
+    // tiles 3.9 against 3.2).
+    pl->nblk_res = pl->nblk;
+    if (!pl->csr && !(opt && opt->blocks_per_cluster > 0)) {
+        if (pl->tiles <= 2 * kResidentWaves) pl->nblk_res = 1;
+        else pl->nblk_res = std::max(pl->nblk, std::min(std::max(1, cus / pl->B), max_useful));
+    }
     if (static_cast<int64_t>(pl->nblk) * pl->B > INT32_MAX) return ESP_ERR_SHAPE;
 
     const size_t B = pl->B, R = pl->R;
@@ -189,7 +202,6 @@ esp_status make_plan(const esp_problem *p, const esp_options *opt, Plan *pl) {
     pl->o_dir = o;   o = align_up(o + dir_bytes);
     pl->o_lamws = o; o = align_up(o + 2 * B * R * sizeof(double));
     pl->o_conv = o;  o = align_up(o + B * sizeof(int32_t));
-    pl->o_xch = o;   o = align_up(o + 2 * B * pl->nblk * R * kMaxLimbs * sizeof(uint64_t));
     pl->total = o;
     return ESP_OK;
 }
@@ -249,7 +261,7 @@ char *resolve_scratch(int dev) {
 // Byte offsets of the per-solve scratch regions of a plan inside the static
 // array, each 256-byte aligned; the last value is the size.
 struct ScratchLayout {
-    size_t part = 0, tick = 0, iters = 0, sync = 0, lamws = 0, conv = 0, xch = 0, total = 0;
+    size_t part = 0, tick = 0, iters = 0, sync = 0, lamws = 0, conv = 0, total = 0;
 };
 
 ScratchLayout scratch_layout(const Plan &pl) {
@@ -262,7 +274,6 @@ ScratchLayout scratch_layout(const Plan &pl) {
     L.sync = o;  o = align_up(o + B * kSyncSlots * kSyncStride * sizeof(uint32_t));
     L.lamws = o; o = align_up(o + 2 * B * R * sizeof(double));
     L.conv = o;  o = align_up(o + B * sizeof(int32_t));
-    L.xch = o;   o = align_up(o + 2 * B * pl.nblk * R * kMaxLimbs * sizeof(uint64_t));
     L.total = o;
     return L;
 }
@@ -283,7 +294,8 @@ struct esp_ctx {
     int mode = ESP_MODE_AUTO;
     bool auto_mode = false;            // the caller asked for ESP_MODE_AUTO
     bool fell_back = false;            // AUTO: the device refused a co-resident grid
-    bool resident_ok = false;          // persistent solves may hold the tiles in registers
+    bool resident_ok = false;          // the table fits ESP_MODE_RESIDENT
+    bool on_chip = false;              // persistent solves of AUTO keep the tiles on chip
     std::vector<int64_t> off;          // family offsets (host copy)
     std::vector<int64_t> slot_of;      // first table slot of each family
     KArgs base{};
@@ -382,20 +394,20 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
     if (capturing && (c->mode == ESP_MODE_PERSISTENT || c->mode == ESP_MODE_RESIDENT)) return ESP_ERR_INVALID_ARG;
     // The loop driver: persistent launches (one per chunk of up to
     // kLaunchChunk iterations) or one launch per iteration.  Persistent
-    // launches run over register-resident tiles when every wavefront of the
-    // grid holds at most two tiles (tables of up to a few MB, where the
-    // latency of an iteration, not the bandwidth, sets the pace): each launch
-    // then completes all of its iterations itself.
+    // launches keep the table on chip when it fits there (see esp_create;
+    // there the latency of an iteration, not the bandwidth, sets the pace):
+    // each launch then completes all of its iterations itself.
     bool persistent =
         !capturing && !c->fell_back && (c->mode != ESP_MODE_STREAM || (c->auto_mode && tol > 0.0));
-    bool resident = persistent && (c->mode == ESP_MODE_RESIDENT || (c->auto_mode && c->resident_ok));
+    bool resident = persistent && (c->mode == ESP_MODE_RESIDENT || (c->auto_mode && c->on_chip));
+    const int nblk_res = c->pl.nblk_res;
     {
         // validates the prices, turns -0.0 into +0.0 in place, resets the
         // per-solve state (and the exchange words of a resident solve)
         KArgs p = kb;
         p.iters_done = d_iters;
-        p.xch_clear = (resident && c->pl.nblk > 1)
-                          ? 2 * static_cast<size_t>(B) * c->pl.nblk * static_cast<size_t>(kb.xch_stride) : 0;
+        p.xch_clear = (resident && nblk_res > 1)
+                          ? static_cast<size_t>(B) * kSyncSlots * kSyncStride / 2 : 0;
         if ((st = dev(launch_prepare(R, p, prices, prices, B, s))) != ESP_OK) return st;
     }
     // With several workgroups per cluster and no resident launch, every
@@ -449,8 +461,9 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
     for (int32_t i0 = 0; i0 < iters; i0 += kLaunchChunk) {
         const int n = std::min<int32_t>(kLaunchChunk, iters - i0);
         if (persistent) {
-            const KArgs a = iteration_launch(i0, n);
+            KArgs a = iteration_launch(i0, n);
             hipError_t e;
+            if (resident) a.nblk = nblk_res;
             if (resident)
                 e = c->pl.csr ? launch_csr_resident(R, a, B, s) : launch_dense_resident(R, c->pl.lpj, a, B, s);
             else
@@ -601,18 +614,23 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
             shift[static_cast<size_t>(b) * R + r] = lo;
         }
 
-    // Resident persistent launches (ESP_MODE_RESIDENT): every wavefront of
-    // the grid holds at most two tiles, and with several workgroups per
-    // cluster each lane reads at most kXchPerThread exchange words (sums in
-    // 48-bit limbs) per round: wavefront w of a workgroup reads workgroups
-    // w, w + 4, ..., with 64 / (R limbs) lanes per limb position.
-    const int limbs = std::max(1, (need_bits + 47) / 48);
-    bool resident_ok = false;
-    {
-        const int64_t waves = static_cast<int64_t>(pl.nblk) * kBlockWaves;
-        const int groups = kWaveSize / (R * limbs);
-        resident_ok = static_cast<int64_t>(pl.tiles) <= 2 * waves &&
-                      (pl.nblk == 1 || (groups >= 1 && pl.nblk <= kXchPerThread * kBlockWaves * groups));
+    // Resident launches.  ESP_MODE_RESIDENT takes tables of at most two tiles
+    // per wavefront of the plan's grid, and of at most 32 workgroups per group
+    // of 64 / (R limbs) lanes of 48-bit limbs: resident_ok.  AUTO also keeps
+    // larger dense tables on chip, with lds_tiles per wavefront in LDS:
+    // on_chip.  (The exchange's count fields hold up to 255 workgroups a copy.)
+    int limbs = std::max(1, (need_bits + 47) / 48);
+    const int groups = kWaveSize / (R * limbs);
+    const bool resident_ok = static_cast<int64_t>(pl.tiles) <= 2ll * pl.nblk * kBlockWaves &&
+                             (pl.nblk == 1 || (groups >= 1 && pl.nblk <= 32 * groups && pl.nblk <= 4 * 255));
+    if (need_bits <= kCountShift) limbs = 1;
+    int lds_tiles = 0;
+    bool on_chip = resident_ok;
+    if (!pl.csr) {
+        const int64_t waves = static_cast<int64_t>(pl.nblk_res) * kResidentWaves;
+        const int64_t per_wave = (pl.tiles + waves - 1) / waves;
+        lds_tiles = static_cast<int>(std::max<int64_t>(0, std::min<int64_t>(per_wave, 1 << 20) - 2));
+        on_chip = pl.nblk_res <= 4 * 255 && resident_lds(static_cast<int>(pl.columns()), lds_tiles) <= resident_lds_limit(R, pl.lpj);
     }
     if (options && options->mode == ESP_MODE_RESIDENT && !resident_ok) return ESP_ERR_SHAPE;
 
@@ -863,10 +881,10 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     k.conv_at = reinterpret_cast<int32_t *>(ws + pl.o_conv);
     k.sweep_alt = c->sweep == 0 ? 1 : 0;
     k.limbs = limbs;
-    k.xch_stride = R * limbs;
-    k.xch = reinterpret_cast<uint64_t *>(ws + pl.o_xch);
     k.xch_clear = 0;
+    k.lds_tiles = on_chip ? lds_tiles : 0;
     c->resident_ok = resident_ok;
+    c->on_chip = on_chip;
     *out = c;
     return ESP_OK;
 }
@@ -934,7 +952,6 @@ esp_status esp_solve_noalloc(esp_ctx *c, double *prices, int32_t iters, int32_t 
     k.sync = reinterpret_cast<uint32_t *>(c->scratch + L.sync);
     k.lam_ws = reinterpret_cast<double *>(c->scratch + L.lamws);
     k.conv_at = reinterpret_cast<int32_t *>(c->scratch + L.conv);
-    k.xch = reinterpret_cast<uint64_t *>(c->scratch + L.xch);
     return solve_with(c, k, reinterpret_cast<int32_t *>(c->scratch + L.iters), prices, iters, t_start, tol, choice,
                       demand, trace, iters_done, stream);
 }

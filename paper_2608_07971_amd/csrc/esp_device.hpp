@@ -83,14 +83,19 @@ __device__ __forceinline__ void wave_sync() {
 // ceil(log2(N + 1))), so the shift is exact and N of them cannot overflow A.
 template <typename A>
 __device__ __forceinline__ A fx_of(float v, int sh) {
-    constexpr int kMax = static_cast<int>(sizeof(A)) * 8 - 1;
-    const uint32_t bits = __float_as_uint(v);
-    const uint32_t e = bits >> 23;
-    const uint32_t m = (bits & 0x7fffffu) | (e ? 0x800000u : 0u);
-    int s = (e ? static_cast<int>(e) : 1) - 150 - sh;
-    s = s > kMax ? kMax : (s < -kMax ? -kMax : s);       // (zero: m = 0 shifts to 0 either way)
-    const A mm = m;
-    return s >= 0 ? (mm << s) : (mm >> (-s));
+    if constexpr (sizeof(A) <= 8) {
+        // v * 2^-sh is a whole number below 2^63 in binary64: exact at each step
+        return static_cast<A>(ldexp(static_cast<double>(v), -sh));
+    } else {
+        constexpr int kMax = static_cast<int>(sizeof(A)) * 8 - 1;
+        const uint32_t bits = __float_as_uint(v);
+        const uint32_t e = bits >> 23;
+        const uint32_t m = (bits & 0x7fffffu) | (e ? 0x800000u : 0u);
+        int s = (e ? static_cast<int>(e) : 1) - 150 - sh;
+        s = s > kMax ? kMax : (s < -kMax ? -kMax : s);       // (zero: m = 0 shifts to 0 either way)
+        const A mm = m;
+        return s >= 0 ? (mm << s) : (mm >> (-s));
+    }
 }
 
 // Round a * 2^sh to the nearest binary64, ties to even.
@@ -108,18 +113,10 @@ __device__ __forceinline__ double fx_to_double(u128 a, int sh) {
     return ldexp(static_cast<double>(m), drop + sh);
 }
 
-// The same for a 64-bit accumulator (fewer instructions where the sums are
-// known to fit 64 bits).
+// The same for a 64-bit accumulator: the conversion rounds to nearest even
+// (a < 2^63), the scaling is exact (a 2^sh is far above the subnormals).
 __device__ __forceinline__ double fx_to_double(uint64_t a, int sh) {
-    if (a == 0) return 0.0;
-    const int h = 63 - __clzll(a);
-    if (h <= 52) return ldexp(static_cast<double>(a), sh);
-    const int drop = h - 52;
-    uint64_t m = a >> drop;
-    const uint64_t rem = a & ((1ull << drop) - 1);
-    const uint64_t half = 1ull << (drop - 1);
-    if (rem > half || (rem == half && (m & 1u))) m += 1;   // m <= 2^53: exact as a double
-    return ldexp(static_cast<double>(m), drop + sh);
+    return ldexp(static_cast<double>(a), sh);
 }
 
 // Partial-sum buffer k of cluster cl: [nblk][R][2] 64-bit words (low, high).

@@ -29,10 +29,23 @@ constexpr int kSyncStride = 64;                     // uint32 words between barr
 constexpr int kPartialBuffers = 3;
 constexpr int kInLaunchBuffer = 2;
 // Resident launches with several workgroups per cluster exchange their sums
-// as limbs of 48 bits (at most 3 for 127-bit sums) in tagged 64-bit words;
-// each thread of a workgroup reads at most kXchPerThread words per round.
+// as limbs (at most 3 for 127-bit sums) in counted 64-bit words: the count of
+// workgroups above kCountShift, their limbs' sum below.
 constexpr int kMaxLimbs = 3;
-constexpr int kXchPerThread = 8;
+constexpr int kCountShift = 56;
+// Dense resident workgroups: 8 wavefronts, two per SIMD (a lone wavefront
+// issues an instruction every 7 cycles or so while it scores), one workgroup
+// per CU.  Tiles beyond two per wavefront lie in LDS: the CU's 160 KB less
+// what the kernel itself uses (step sizes, staged demands, sums).
+constexpr int kResidentWaves = 8;
+constexpr int kResidentThreads = kResidentWaves * kWaveSize;
+constexpr size_t resident_lds(int columns, int tiles_per_wave) {
+    return static_cast<size_t>(kResidentWaves) * tiles_per_wave * columns * kTileEntries * sizeof(float);
+}
+constexpr size_t resident_lds_limit(int R, int lpj) {
+    return (160u << 10) - (kLaunchChunk * sizeof(double) + sizeof(float) * kResidentWaves * (kWaveSize / lpj) * R +
+                           16u * kResidentWaves * R + 1024u);
+}
 
 // Flags per cluster (device int32).
 constexpr int kFlagStopped = 1;                     // converged under tol: skip further updates
@@ -122,11 +135,10 @@ struct KArgs {
     int32_t *conv_at;              // [B] iteration whose completion met tol, 0 while none has
     double *trace_lam;             // [iters][B][R]: row m - 1 receives lambda_{m+1}, or NULL
     double *trace_U;               // [iters][B][R]: row m - 1 receives U_m, or NULL
-    // Resident launches (tiles held in registers, every iteration completed
-    // in the launch): tagged exchange words [2][B][nblk][xch_stride].
-    uint64_t *xch;
-    int32_t xch_stride;            // words per workgroup = R * limbs
-    int32_t limbs;                 // 48-bit limbs per workgroup sum
+    // Resident launches (tiles kept on chip, every iteration completed in the
+    // launch): exchange words in the space of `sync`.
+    int32_t limbs;                 // limbs per workgroup sum
+    int32_t lds_tiles;             // tiles per wavefront kept in LDS (dense resident launches)
     size_t xch_clear;              // words k_prepare sets to 0 before a resident solve (0: none)
 };
 
@@ -140,8 +152,9 @@ hipError_t launch_dense(int R, int lpj, const KArgs &a, int B, hipStream_t s);
 hipError_t launch_dense_persistent(int R, int lpj, const KArgs &a, int B, hipStream_t s);
 hipError_t launch_csr(int R, const KArgs &a, int B, hipStream_t s);
 hipError_t launch_csr_persistent(int R, const KArgs &a, int B, hipStream_t s);
-// Multi-iteration launches over register-resident tiles (at most two per
-// wavefront), each iteration completed in the launch (see kResident).
+// Multi-iteration launches over tiles kept on chip (two per wavefront in
+// registers; dense: a.lds_tiles more in LDS), each iteration completed in the
+// launch (see kResident and k_resident).
 hipError_t launch_dense_resident(int R, int lpj, const KArgs &a, int B, hipStream_t s);
 hipError_t launch_csr_resident(int R, const KArgs &a, int B, hipStream_t s);
 hipError_t launch_gather(int R, const KArgs &a, int B, hipStream_t s);

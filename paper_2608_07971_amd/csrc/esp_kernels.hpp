@@ -299,35 +299,121 @@ __device__ bool wait_iteration(const KArgs &a, int cl, int blk, int m, int *s_go
 }
 
 // ---------------------------------------------------------------------------
-// Resident launches with several workgroups per cluster: the exact sums of
-// iteration m are exchanged through tagged words, and every workgroup
-// completes the iteration itself.
+// Resident launches: every iteration is completed inside the launch; with
+// several workgroups per cluster their exact sums meet in counted words.
 // ---------------------------------------------------------------------------
 
-// Workgroup w's sum for resource r is split into a.limbs limbs of kLimbBits
-// bits; limb l travels in one 64-bit word whose top 16 bits carry the tag of
-// the iteration, (m - 1) mod 65535 + 1 (never 0, the value the solve's
-// prologue clears the words to, and different for m and m - 2).  Tag and
-// limb are one single-copy-atomic 64-bit store, so a reader that sees the
-// tag of iteration m sees that iteration's limb: the exchange needs no fence
-// and no counter.  Words of iteration m live in half m & 1 of a.xch
-// ([2][B][nblk][R * limbs]); a workgroup writes half m & 1 again (iteration
-// m + 2) only after it has read every workgroup's words of iteration m + 1,
-// which each workgroup wrote after it had read all words of iteration m.
+// A workgroup's sum for resource r is split into a.limbs limbs (one when the
+// cluster's total fits kCountShift bits, else kLimbBits each): words of a
+// 64-bit value below kCountShift and a count above.  The limbs of iteration m
+// take three steps, each with agent-scope atomics only:
+//  1. every workgroup adds its words, each with a count of one, to one of
+//     `copies` copies of them (copy blk mod copies) with a returning atomic
+//     add; the add that completes a copy's count returns the copy's sum;
+//  2. that lane adds the copy's sum to the root words the same way, and the
+//     add that completes the root has the cluster's total;
+//  3. that lane stores the total, tagged with m, to `replicas` release words;
+//     every workgroup polls its replica for the tag.
+// So adds to one address stay few (each takes the memory side about 11 ns),
+// and polls never touch a line that is still being added to: polling the
+// copies themselves cost 0.4 to 1.5 us more at 128 to 256 workgroups.  An
+// exchange alone takes 1.67 us for 64 to 256 workgroups; one in which each
+// workgroup reads every other's words 2.4 and 4.2 us for 128 and 256.
+//
+// Copies and root have two sets, by the parity of m.  The lane that completes
+// a word's count clears it at once (no other add to it comes before m + 2):
+// it waits for the clear to have been performed before its own next add, in
+// m + 1, and nobody adds to m + 2 before m + 1 is complete.  Release words
+// alternate too; the tag tells m from m - 2.  The words take the place of the
+// persistent driver's barrier words, which resident launches do not use; the
+// solve's prologue clears them.
 constexpr int kLimbBits = 48;
 constexpr uint64_t kLimbMask = (1ull << kLimbBits) - 1;
+constexpr int kSlotWords = kSyncStride / 2;    // 64-bit words of a 256-byte slot of the barrier words
+constexpr int kReplicas = 4;
 
-__device__ __forceinline__ uint64_t *xch_words(const KArgs &a, int cl, int m) {
-    return a.xch + (static_cast<size_t>(m & 1) * a.B + cl) * static_cast<size_t>(a.nblk) * a.xch_stride;
+// Where this lane's word (lane = limb * R + resource) is added and released;
+// fixed per launch.  Copies lie in slots of their own; with at most 8 words
+// both sets fill a slot's first 128-byte line, and a release line its second.
+struct Exchange {
+    uint64_t *copy, *root, *release;           // set 0 of each
+    int set_words, release_words;              // words from set 0 to set 1
+    int replica_words;                         // words between replicas
+    int words;                                 // R * limbs (lanes that take part)
+    int in_copy;                               // workgroups that add to this copy
+    int copies, replicas, first_replica;
+};
+template <int R>
+__device__ __forceinline__ Exchange exchange_of(const KArgs &a, int cl, int blk, int lane) {
+    uint64_t *const base = reinterpret_cast<uint64_t *>(a.sync + static_cast<size_t>(cl) * kSyncSlots * kSyncStride);
+    Exchange x;
+    x.words = R * a.limbs;
+    const int q = lane < x.words ? lane : 0;
+    const int line = (x.words + 7) / 8 * 8;                // 8, 16 or 24 words
+    const int span = (2 * line + kSlotWords - 1) / kSlotWords * kSlotWords;   // both sets of a copy
+    x.copies = min(a.nblk, line == 8 ? 16 : line == 16 ? 8 : 4);
+    x.replicas = min(a.nblk, kReplicas);
+    const int mine = blk % x.copies;
+    x.in_copy = a.nblk / x.copies + (mine < a.nblk % x.copies ? 1 : 0);
+    x.set_words = line;
+    x.copy = base + mine * span + q;
+    const int top = line == 8 ? 16 : line == 16 ? 8 : 4;
+    x.root = base + top * span + q;
+    // 17 slots: 16 copies and the root with release lines in the second halves, or 8 (4) copies, the
+    // root and 8 release lines of 16 (24) words
+    static_assert(kSyncSlots * kSlotWords >= 5 * 64 + 2 * kReplicas * 24, "4 copies of 24 words fit");
+    static_assert(kSyncSlots >= 17, "16 copies and the root fit");
+    x.release_words = line == 8 ? kSlotWords : line;
+    x.replica_words = 2 * x.release_words;
+    x.first_replica = blk % x.replicas;
+    x.release = base + (line == 8 ? kSlotWords / 2 : (top + 1) * span) + q;
+    return x;
 }
 
-__device__ __forceinline__ double readlane_d(double v, int lane) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<unsigned>(b)), lane);
-    const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
-    return __longlong_as_double(static_cast<long long>(
-        (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)));
+// Sum of v over the lanes with the same index modulo RP (a power of two up to
+// 8), in every lane: rotations inside the 16-lane rows, then row swaps.
+template <typename A, typename Move>
+__device__ __forceinline__ A add_moved(A v, Move &&move) {
+    constexpr int kWords = static_cast<int>(sizeof(A) / 4);
+    A o = 0;
+#pragma unroll
+    for (int i = 0; i < kWords; ++i)
+        o |= static_cast<A>(static_cast<uint32_t>(move(static_cast<int>(static_cast<uint32_t>(v >> (32 * i)))))) << (32 * i);
+    return v + o;
 }
+template <int RP, typename A>
+__device__ __forceinline__ A lane_sum(A v) {
+    constexpr int kRor1 = 0x121, kRor2 = 0x122, kRor4 = 0x124, kRor8 = 0x128;
+    if constexpr (RP <= 1) v = add_moved(v, [](int x) { return dpp_i<kRor1>(x); });
+    if constexpr (RP <= 2) v = add_moved(v, [](int x) { return dpp_i<kRor2>(x); });
+    if constexpr (RP <= 4) v = add_moved(v, [](int x) { return dpp_i<kRor4>(x); });
+    v = add_moved(v, [](int x) { return dpp_i<kRor8>(x); });
+    // both halves of a swap of x with itself: the other row in every lane of one of them
+    constexpr int kWords = static_cast<int>(sizeof(A) / 4);
+    A lo = 0, hi = 0;
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+        const uint32_t x = static_cast<uint32_t>(v >> (32 * i));
+        const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        lo |= static_cast<A>(p[0]) << (32 * i);
+        hi |= static_cast<A>(p[1]) << (32 * i);
+    }
+    v = lo + hi;
+    lo = hi = 0;
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+        const uint32_t x = static_cast<uint32_t>(v >> (32 * i));
+        const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        lo |= static_cast<A>(p[0]) << (32 * i);
+        hi |= static_cast<A>(p[1]) << (32 * i);
+    }
+    return lo + hi;
+}
+
+// The smallest power of two not below R: in resident launches lane l
+// accumulates resource l mod RP (the lanes with l mod RP >= R nothing).
+template <int R>
+constexpr int kResidentStep = R <= 1 ? 1 : R <= 2 ? 2 : R <= 4 ? 4 : 8;
 
 // Step sizes eta_t of all iterations of a resident launch, computed once at
 // its start by the whole workgroup (the same IEEE operations as step_size, so
@@ -335,148 +421,161 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
 // path.  The caller synchronizes the workgroup before the first read.
 __device__ __forceinline__ const double *resident_etas(const KArgs &a, int cl) {
     __shared__ double s_eta[kLaunchChunk];
-    for (int i = threadIdx.x; i < a.n_iters; i += kBlockThreads) s_eta[i] = step_size(a, cl, a.t + i);
+    for (int i = threadIdx.x; i < a.n_iters; i += blockDim.x) s_eta[i] = step_size(a, cl, a.t + i);
     return s_eta;
 }
 
-// End of iteration a.iter_no in a resident launch.  `acc` is this lane's
-// exact partial sum for resource lane % R (acc_lane: the lane accumulates);
-// lam holds the iteration's prices and receives lambda_{m+1}.  Every
-// wavefront completes the iteration itself, with one workgroup barrier (two
-// when the workgroups of a cluster exchange their sums):
-//  1. each wavefront totals its lanes' sums per resource through LDS (lanes
-//     r < R hold them) and posts them; after the barrier every wavefront adds
-//     the four wavefronts' sums;
-//  2. with several workgroups per cluster, wavefront 0 publishes the
-//     workgroup's sums as tagged limbs and all four wavefronts read every
-//     workgroup's words (wavefront w the workgroups w, w + 4, ...; each lane
-//     one limb position of up to kXchPerThread workgroups, its loads in
-//     flight together, polling until every tag matches, bounded by about 2 s
-//     of the real-time counter); after a second barrier every wavefront adds
-//     the four partial totals;
-//  3. lanes r < R compute U_r (exact total rounded once), lambda_r of Eq. 8
-//     and the stop test, and the new prices reach every lane by readlane, in
-//     the same bits in every wavefront and workgroup; wavefront 0 of
-//     workgroup 0 writes the prices, trace rows, update count and stop flag.
-// Returns false when the cluster stops here or a wait timed out.
-template <int R, typename A>
-__device__ bool resident_complete(const KArgs &a, int cl, int blk, int wave, int lane, A acc, bool acc_lane,
-                                  double eta, double (&lam)[R]) {
-    constexpr int Q = kWaveSize / R;
-    __shared__ A s_lane[kBlockWaves][kWaveSize];
-    __shared__ A s_wave[2][kBlockWaves][R];
-    __shared__ unsigned long long s_limb[kBlockWaves][kWaveSize];
-    __shared__ unsigned long long s_xw[2][kBlockWaves][R * kMaxLimbs];
-    __shared__ int s_go;
-    const int m = a.iter_no;
+// What does not change between the iterations, or is carried over, in lanes
+// r < R of wavefront 0.
+struct ResidentCtx {
+    double lo;            // the iteration's price of resource r
+    double cap;           // its capacity and fixed-point window
+    int shift;
+    int done;             // iterations completed in this launch
+    bool stop;            // the last one met the tolerance
+};
+
+// prices: the launch's starting prices of the cluster, [R]
+template <int R>
+__device__ __forceinline__ ResidentCtx resident_ctx(const KArgs &a, int cl, int lane, const double *prices) {
+    const int r = lane < R ? lane : R - 1;
+    ResidentCtx c;
+    c.lo = prices[r];
+    c.cap = a.cap[static_cast<size_t>(cl) * R + r];
+    c.shift = a.shift[static_cast<size_t>(cl) * R + r];
+    c.done = 0;
+    c.stop = false;
+    // loaded before the loop: a load still counted as pending there would make
+    // every iteration wait for all of its own stores
+    asm volatile("" : "+v"(c.lo), "+v"(c.cap), "+v"(c.shift));
+    return c;
+}
+
+// The exchange of iteration m: this lane's word `v` (lanes below xch.words)
+// becomes the cluster's total.  Returns false when another workgroup has
+// recorded an error, or after about 2 s.
+__device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &xch, int m, int lane, uint64_t &v) {
+    constexpr uint64_t kOne = 1ull << kCountShift, kLow = kOne - 1;
     const int par = m & 1;
-    // 1. wavefront sums per resource
-    s_lane[wave][lane] = acc_lane ? acc : A(0);
-    wave_sync();
-    // (every partial sum fits the accumulator type A: the packer sized A for
-    // the whole column's total)
-    if (lane < R) {
-        A ws = 0;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) ws += s_lane[wave][q * R + lane];
-        s_wave[par][wave][lane] = ws;
+    const uint64_t tag = static_cast<uint64_t>(m % 255 + 1) << kCountShift;
+    uint64_t *const release = xch.release + par * xch.release_words;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the clears of iteration m - 1 have been performed
+    if (lane < xch.words) {
+        uint64_t *const copy = xch.copy + par * xch.set_words;
+        const uint64_t c = __hip_atomic_fetch_add(copy, kOne + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (static_cast<int>(c >> kCountShift) == xch.in_copy - 1) {
+            v += c & kLow;
+            uint64_t *const root = xch.root + par * xch.set_words;
+            const uint64_t t = __hip_atomic_fetch_add(root, kOne + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(copy, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (static_cast<int>(t >> kCountShift) == xch.copies - 1) {
+                v += t & kLow;
+                for (int k = 0; k < xch.replicas; ++k)
+                    __hip_atomic_store(release + k * xch.replica_words, tag | v, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(root, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
     }
-    if (threadIdx.x == 0) s_go = 1;
+    const uint64_t *const from = release + xch.first_replica * xch.replica_words;
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    for (int tries = 1;; ++tries) {
+        const uint64_t x = __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__ballot((x & ~kLow) != tag) == 0) {           // (lanes without a word read word 0)
+            v = x & kLow;
+            return true;
+        }
+        if ((tries & 63) == 0 && (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
+                                  __builtin_amdgcn_s_memrealtime() - t0 > 200000000ull)) {
+            if (lane == 0) atomicCAS(a.status, 0, kStatusTimeout);
+            return false;
+        }
+    }
+}
+
+// End of iteration `it` (0-based) of a resident launch.  `acc` is this lane's
+// exact partial sum for resource lane mod kResidentStep<R> (0 in lanes without
+// one); lam receives lambda_{m+1}.  An iteration is one dependent chain, so
+// only its latency counts:
+//  1. each wavefront totals its lanes in registers and posts R sums in LDS;
+//  2. after the barrier wavefront 0 adds the wavefronts' sums, and with
+//     several workgroups exchanges them;
+//  3. its lanes r < R compute U_r (exact total rounded once), lambda_r of Eq. 8
+//     and the stop test, in the same bits in every workgroup, and post the new
+//     prices for a second barrier (in workgroup 0 they also write the trace
+//     rows; the prices and counts are written once, by resident_outputs).
+// Returns false when the cluster stops here or a wait timed out.
+template <int R, int Waves, typename A>
+__device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl, int blk, int wave, int lane, A acc,
+                                                  double eta, double (&lam)[R], ResidentCtx &ctx, const Exchange &xch) {
+    __shared__ A s_wave[Waves][R];
+    __shared__ double s_price[R];
+    __shared__ int s_go;
+    const A ws = lane_sum<kResidentStep<R>>(acc);
+    if (lane < R) s_wave[wave][lane] = ws;
     __syncthreads();
-    A tot = 0;
-    if (lane < R) {
+    if (wave == 0) {
+        // (every partial sum fits the accumulator type A: the packer sized A for
+        // the whole column's total)
+        A tot = 0;
 #pragma unroll
-        for (int w = 0; w < kBlockWaves; ++w) tot += s_wave[par][w][lane];
-    }
-    if (a.nblk > 1) {
-        // 2. the exchange between the workgroups of the cluster
-        const int L = a.limbs;
-        const int RL = R * L;
-        const uint64_t tag = static_cast<uint64_t>((m - 1) % 65535 + 1);
-        uint64_t *words = xch_words(a, cl, m);
-        if (wave == 0 && lane < R) {
-            for (int l = 0; l < L; ++l) {
-                const uint64_t v = static_cast<uint64_t>(static_cast<u128>(tot) >> (kLimbBits * l)) & kLimbMask;
-                __hip_atomic_store(words + static_cast<size_t>(blk) * a.xch_stride + lane * L + l,
-                                   (tag << kLimbBits) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int w = 0; w < Waves; ++w) tot += s_wave[w][lane % R];
+        bool go = true;
+        if (a.nblk > 1) {
+            // lane l R + r exchanges limb l of resource r
+            uint64_t v = static_cast<uint64_t>(tot);
+            if (xch.words > R)
+                v = static_cast<uint64_t>(static_cast<u128>(tot) >> (kLimbBits * (lane < xch.words ? lane / R : 0))) & kLimbMask;
+            go = exchange_total(a, xch, a.iter_no + it, lane, v);
+            if (xch.words == R) {
+                tot = static_cast<A>(v);
+            } else {
+                u128 t = 0;
+                for (int l = 0; l < a.limbs; ++l)
+                    t += static_cast<u128>(static_cast<uint64_t>(
+                             __shfl(static_cast<unsigned long long>(v), l * R + lane % R))) << (kLimbBits * l);
+                tot = static_cast<A>(t);         // the exact total, which fits A
             }
         }
-        const int G = kWaveSize / RL;                 // lane groups per wavefront
-        const int g = lane / RL, q = lane - g * RL;
-        unsigned long long sum = 0;
-        if (g < G) {
-            const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-            while (true) {
-                bool all = true;
-                sum = 0;
-#pragma unroll
-                for (int u = 0; u < kXchPerThread; ++u) {
-                    const int b = wave + kBlockWaves * (g + G * u);
-                    const int bc = b < a.nblk ? b : a.nblk - 1;          // clamped: no branch around the load
-                    const uint64_t x = __hip_atomic_load(words + static_cast<size_t>(bc) * a.xch_stride + q,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const bool valid = b < a.nblk;
-                    all &= !valid | ((x >> kLimbBits) == tag);
-                    sum += valid ? (x & kLimbMask) : 0ull;
-                }
-                if (all) break;
-                if (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                    __builtin_amdgcn_s_memrealtime() - t0 > 200000000ull) {
-                    atomicCAS(a.status, 0, kStatusTimeout);
-                    s_go = 0;                          // every wavefront still reaches the barrier
-                    break;
-                }
-            }
-        }
-        s_limb[wave][lane] = sum;
-        wave_sync();
-        if (lane < RL) {
-            unsigned long long ps = 0;
-            for (int gg = 0; gg < G; ++gg) ps += s_limb[wave][gg * RL + lane];
-            s_xw[par][wave][lane] = ps;
-        }
-        __syncthreads();
-        if (s_go == 0) return false;
-        tot = 0;
-        if (lane < R) {
-            u128 t128 = 0;
-            for (int l = 0; l < L; ++l) {
-                u128 ls = 0;
-#pragma unroll
-                for (int w = 0; w < kBlockWaves; ++w) ls += s_xw[par][w][lane * L + l];
-                t128 += ls << (kLimbBits * l);
-            }
-            tot = static_cast<A>(t128);          // the exact total, which fits A
-        }
-    }
-    // 3. U, Eq. 8 and the stop test in lanes r < R
-    double lo = lam[0];
-#pragma unroll
-    for (int r = 1; r < R; ++r) lo = (lane == r) ? lam[r] : lo;
-    double U = 0.0, ln = 0.0;
-    bool ok = true;
-    if (lane < R) {
-        const size_t i = static_cast<size_t>(cl) * R + lane;
-        U = fx_to_double(tot, a.shift[i]);
-        const double gd = U - a.cap[i];
+        // U, Eq. 8 and the stop test in lanes r < R
+        const double lo = ctx.lo;
+        const double U = fx_to_double(tot, ctx.shift);
+        const double gd = U - ctx.cap;
         const double x = lo + eta * gd;
-        ln = (x > 0.0) ? x : 0.0;
+        const double ln = (x > 0.0) ? x : 0.0;
         const double scale = lo > 1.0 ? lo : 1.0;
-        ok = fabs(ln - lo) <= a.tol * scale;
-        if (wave == 0 && blk == 0) {
-            a.lam_out[i] = ln;
-            if (a.tr_lam) a.tr_lam[i] = ln;
-            if (a.tr_U) a.tr_U[i] = U;
+        const bool ok = (lane >= R) | (fabs(ln - lo) <= a.tol * scale);
+        const bool stop = (a.tol > 0.0) & (__ballot(!ok) == 0);
+        if (lane < R) s_price[lane] = ln;
+        if (lane == 0) s_go = go & !stop;
+        if (go) {
+            ctx.lo = ln;
+            ctx.done = it + 1;
+            ctx.stop = stop;
+            if ((blk == 0) & (lane < R)) {
+                const size_t row = (static_cast<size_t>(it) * a.B + cl) * R + lane;
+                if (a.tr_lam) a.tr_lam[row] = ln;
+                if (a.tr_U) a.tr_U[row] = U;
+            }
         }
     }
-    const bool stop = (a.tol > 0.0) & (__ballot(!ok) == 0);      // wave-uniform, the same in every wavefront
-    if (wave == 0 && blk == 0 && lane == 0) {
-        if (a.iters_done) a.iters_done[cl] = m;
-        if (stop) atomicOr(&a.flags[cl], kFlagStopped);
-    }
+    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) lam[r] = readlane_d(ln, r);
-    return !stop;
+    for (int r = 0; r < R; ++r) lam[r] = s_price[r];
+    return s_go != 0;
+}
+
+// End of a resident launch: the prices, the update count and the stop flag of
+// its last completed iteration.
+template <int R>
+__device__ __forceinline__ void resident_outputs(const KArgs &a, int cl, int blk, int wave, int lane,
+                                                 const ResidentCtx &ctx) {
+    if ((blk != 0) | (wave != 0) | (ctx.done == 0)) return;
+    if (lane < R) a.lam_out[static_cast<size_t>(cl) * R + lane] = ctx.lo;
+    if (lane == 0) {
+        if (a.iters_done) a.iters_done[cl] = a.iter_no + ctx.done - 1;
+        if (ctx.stop) atomicOr(&a.flags[cl], kFlagStopped);
+    }
 }
 
 // Per-iteration view of the arguments of a persistent launch.
@@ -515,10 +614,11 @@ __device__ __forceinline__ bool next_prices_local(double *s_lam, const double *s
 constexpr int kOnePass = 0;          // one iteration or one selection per launch
 constexpr int kPersistLocal = 1;     // several iterations, one workgroup per cluster
 constexpr int kPersistDeferred = 2;  // cooperative, several iterations, deferred completion between them
-// Several iterations over tiles held in registers for the whole launch (each
-// wavefront has at most two: no table loads inside the loop); the launch
-// completes every iteration itself, with one workgroup per cluster or
-// through the tagged exchange between the workgroups of a cluster.
+// CSR tables: several iterations over tiles held in registers for the whole
+// launch (each wavefront has at most two: no table loads inside the loop); the
+// launch completes every iteration itself, with one workgroup per cluster or
+// through the tagged exchange between the workgroups of a cluster.  (Dense
+// tables have k_resident.)
 constexpr int kResident = 3;
 
 template <int R, int LPJ, typename A, int Mode>
@@ -633,42 +733,27 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
         load_tile(min(tile0 + stride, last), rev, ub, db, pb);
     };
     Pending<R, A> pend;
-    if constexpr (Mode != kResident) pending_loads<R, A>(a, cl, conv, pend);   // issued first: they return first
-    prefetch_two(a.reverse);                   // in flight during a pending completion; a resident
-                                               // launch's tiles for all its iterations
-    const double *etas = nullptr;
-    if constexpr (Mode == kResident) etas = resident_etas(a, cl);   // read after launch_prices' barrier
+    pending_loads<R, A>(a, cl, conv, pend);    // issued first: they return first
+    prefetch_two(a.reverse);                   // in flight during a pending completion
     if (!launch_prices<R, A>(a, cl, blk, pend, s_lam, s_newlam, s_acc)) return;
 #pragma unroll
     for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
     for (int it = 0; it < a.n_iters; ++it) {
         const KArgs ai = iteration_args<R>(a, it);
         const int rev = ai.reverse;
-        if constexpr (Mode == kResident) {
-            // the wavefront's tiles stay in ua / ub (loaded front to back)
-            if (tile0 < a.tiles) process(ai, tile0, ua, da, pa);
-            if (tile0 + stride < a.tiles) process(ai, tile0 + stride, ub, db, pb);
-        } else {
-            // Loads past the end are clamped to the last tile (never
-            // processed): without branches around them the compiler waits
-            // for each tile's own loads only.
-            for (int tile = tile0; tile < a.tiles; tile += 3 * stride) {
-                const int t1 = tile + stride, t2 = tile + 2 * stride;
-                load_tile(min(t2, last), rev, uc, dc, pc);
-                process(ai, tile, ua, da, pa);
-                load_tile(min(t2 + stride, last), rev, ua, da, pa);
-                if (t1 < a.tiles) process(ai, t1, ub, db, pb);
-                load_tile(min(t2 + 2 * stride, last), rev, ub, db, pb);
-                if (t2 < a.tiles) process(ai, t2, uc, dc, pc);
-            }
+        // Loads past the end are clamped to the last tile (never
+        // processed): without branches around them the compiler waits
+        // for each tile's own loads only.
+        for (int tile = tile0; tile < a.tiles; tile += 3 * stride) {
+            const int t1 = tile + stride, t2 = tile + 2 * stride;
+            load_tile(min(t2, last), rev, uc, dc, pc);
+            process(ai, tile, ua, da, pa);
+            load_tile(min(t2 + stride, last), rev, ua, da, pa);
+            if (t1 < a.tiles) process(ai, t1, ub, db, pb);
+            load_tile(min(t2 + 2 * stride, last), rev, ub, db, pb);
+            if (t2 < a.tiles) process(ai, t2, uc, dc, pc);
         }
         if (!ai.reduce) return;
-        if constexpr (Mode == kResident) {
-            const bool go = resident_complete<R, A>(ai, cl, blk, wave, lane, acc, acc_lane, etas[it], lam);
-            acc = 0;
-            if (!go || it + 1 == a.n_iters) break;
-            continue;
-        }
 
         // Workgroup sum per resource (integer adds: any order gives the same value).
         s_acc[threadIdx.x] = acc_lane ? static_cast<u128>(acc) : static_cast<u128>(0);
@@ -709,6 +794,153 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
 #pragma unroll
         for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
     }
+}
+
+// ---------------------------------------------------------------------------
+// Dense families, resident: several iterations over tiles kept on chip
+// ---------------------------------------------------------------------------
+
+// A wavefront keeps its first two tiles in registers and the others (a.lds_tiles
+// at most, none in ESP_MODE_RESIDENT) in LDS, loaded once per launch: at R = 8
+// a workgroup holds 32 tiles, 256 of them 75 MB.  Iterations follow each other
+// with no table loads, so their cost is the latency of scoring the wavefronts'
+// tiles (two wavefronts per SIMD overlap), the workgroup's sums and, with
+// several workgroups, one exchange through memory (resident_complete).
+// Streaming the same table costs a pass at memory bandwidth and a barrier of
+// the grid per iteration.  Measured per iteration, 64 configurations x 8
+// resources, against the streaming persistent driver: 9,000 jobs (20.7 MB)
+// 8.5 -> 3.6 us, 12,000 (27.6 MB) 9.9 -> 3.6, 24,000 (55 MB) 13.1 -> 5.5;
+// against four wavefronts per workgroup with every workgroup reading every
+// other's sums: 4,096 jobs x 32 x 4 4.1 -> 2.5, 64 x 8 x 4 1.25 -> 0.85.
+// A kernel of its own: the registers and branches of the streaming loops cost
+// every iteration here.
+template <int R, int LPJ, typename A>
+__global__ __launch_bounds__(kResidentThreads) void k_resident(KArgs a) {
+    constexpr int JPT = kWaveSize / LPJ;       // jobs per tile
+    constexpr int RS = kResidentStep<R>;       // lane l accumulates resource l mod RS
+    constexpr int Q = kWaveSize / RS;          // accumulating lanes per resource
+    constexpr int kPer = (JPT + Q - 1) / Q;    // jobs of a tile per accumulating lane
+    extern __shared__ f4 s_tiles[];            // [kResidentWaves][a.lds_tiles][columns][64 lanes]
+    __shared__ float s_stage[kResidentWaves][JPT][R];
+    const int cl = blockIdx.x / a.nblk;
+    const int blk = blockIdx.x - cl * a.nblk;
+    if (a.flags[cl] & a.skip_mask) return;
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float *col = a.table + cl * a.cluster_stride;
+    const bool acc_lane = lane % RS < R;
+    const int my_r = acc_lane ? lane % RS : 0;
+    const int my_q = lane / RS;
+    const int my_shift = a.shift[cl * R + my_r];
+    const int gl = lane % LPJ;                 // lane within its job group
+    const int jt = lane / LPJ;                 // job within the tile
+    // tile s of wavefront w: every workgroup's wavefront w before any's w + 1, so that the wavefronts
+    // that share a SIMD (w and w + 4) both have tiles only when there are more than 4 per workgroup
+    const int stride = a.nblk * kResidentWaves;
+    const int tile0 = wave * a.nblk + blk;
+    const int last = a.tiles - 1;
+    const double sw = a.has_pen ? a.switch_cost[cl] : 0.0;
+    auto load_tile = [&](int t, f4 &u, f4 (&d)[R], f4 &pn) {
+        const float *p = col + static_cast<size_t>(t) * kTileEntries + static_cast<size_t>(lane) * 4;
+        u = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p));
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            d[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p + (r + 1) * a.col_len));
+        if (a.has_pen) pn = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p + (R + 1) * a.col_len));
+    };
+    // tile s of this wavefront's LDS tiles (its tile tile0 + (2 + s) stride)
+    const int cols = R + 1 + (a.has_pen ? 1 : 0);
+    f4 *const mine = s_tiles + static_cast<size_t>(wave) * a.lds_tiles * cols * kWaveSize + lane;
+    auto lds_tile = [&](int s, f4 &u, f4 (&d)[R], f4 &pn) {
+        const f4 *p = mine + static_cast<size_t>(s) * cols * kWaveSize;
+        u = p[0];
+#pragma unroll
+        for (int r = 0; r < R; ++r) d[r] = p[(r + 1) * kWaveSize];
+        if (a.has_pen) pn = p[(R + 1) * kWaveSize];
+    };
+    double lam[R];                             // prices of the current iteration
+    A acc = 0;
+    int32_t *choice = nullptr;                 // the iteration's trace of choices
+    auto process = [&](int tl, const f4 &u, const f4 (&d)[R], const f4 &pn) {
+        double best = 0.0;
+        int bi = 0;
+        auto lane_best = [&](auto pen) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                double rent = static_cast<double>(d[0][i]) * lam[0];
+#pragma unroll
+                for (int r = 1; r < R; ++r) rent = rent + static_cast<double>(d[r][i]) * lam[r];
+                double sc = static_cast<double>(u[i]) - rent;
+                if constexpr (decltype(pen)::value) sc = penalize(sc, pn[i], sw);
+                if (i == 0 || sc > best) { best = sc; bi = i; }
+            }
+        };
+        if (a.has_pen) lane_best(std::true_type{});
+        else lane_best(std::false_type{});
+        int k = gl * 4 + bi;
+        group_argmax<LPJ>(best, k);
+        const int j = tl * JPT + jt;
+        const bool owner = ((k >> 2) == gl) & (j < a.N);   // this lane holds the winning entry
+        if (choice && owner) choice[static_cast<size_t>(cl) * a.N + j] = k;
+        const int w = k & 3;
+        float v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float lo = (w & 1) ? d[r][1] : d[r][0];
+            const float hi = (w & 1) ? d[r][3] : d[r][2];
+            v[r] = (w & 2) ? hi : lo;
+            v[r] = j < a.N ? v[r] : 0.0f;                  // jobs past N add nothing
+        }
+        if ((k >> 2) == gl) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) s_stage[wave][jt][r] = v[r];
+        }
+        wave_sync();
+        float x[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int q = my_q + i * Q;
+            x[i] = s_stage[wave][q < JPT ? q : JPT - 1][my_r];
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            acc += fx_of<A>((acc_lane & (my_q + i * Q < JPT)) ? x[i] : 0.0f, my_shift);
+        wave_sync();
+    };
+    f4 ua, ub, up, pa = {}, pb = {}, pp = {};
+    f4 da[R], db[R], dp[R];
+    load_tile(min(tile0, last), ua, da, pa);               // clamped: no branch
+    load_tile(min(tile0 + stride, last), ub, db, pb);
+    const int n_lds = max(0, min(a.lds_tiles, (a.tiles - tile0 - 2 * stride + stride - 1) / stride));
+#pragma unroll 1
+    for (int s = 0; s < n_lds; ++s) {
+        load_tile(tile0 + (2 + s) * stride, up, dp, pp);
+        f4 *p = mine + static_cast<size_t>(s) * cols * kWaveSize;
+        p[0] = up;
+#pragma unroll
+        for (int r = 0; r < R; ++r) p[(r + 1) * kWaveSize] = dp[r];
+        if (a.has_pen) p[(R + 1) * kWaveSize] = pp;
+    }
+    wave_sync();
+    const double *etas = resident_etas(a, cl);
+#pragma unroll
+    for (int r = 0; r < R; ++r) lam[r] = a.lam_in[cl * R + r];
+    const Exchange xch = exchange_of<R>(a, cl, blk, lane);
+    ResidentCtx ctx = resident_ctx<R>(a, cl, lane, a.lam_in + static_cast<size_t>(cl) * R);
+    __syncthreads();
+    for (int it = 0; it < a.n_iters; ++it) {
+        if (a.choice) choice = a.choice + static_cast<size_t>(it) * a.B * a.N;
+        acc = 0;
+        if (tile0 < a.tiles) process(tile0, ua, da, pa);
+        if (tile0 + stride < a.tiles) process(tile0 + stride, ub, db, pb);
+#pragma unroll 1   // (the SIMD's other wavefront fills the wait for LDS)
+        for (int s = 0; s < n_lds; ++s) {
+            lds_tile(s, up, dp, pp);
+            process(tile0 + (2 + s) * stride, up, dp, pp);
+        }
+        if (!resident_complete<R, kResidentWaves, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, ctx, xch)) break;
+    }
+    resident_outputs<R>(a, cl, blk, wave, lane, ctx);
 }
 
 // ---------------------------------------------------------------------------
@@ -764,7 +996,8 @@ __device__ __forceinline__ void seg_scan_step(double &s, int &f) {
 // one workgroup per CU at most: it may use the whole register file.
 template <int R, typename A, int Mode>
 __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_csr(KArgs a) {
-    constexpr int Q = kWaveSize / R;           // accumulating lanes per resource
+    constexpr int RS = Mode == kResident ? kResidentStep<R> : R;   // lane l accumulates resource l mod RS
+    constexpr int Q = kWaveSize / RS;          // accumulating lanes per resource
     __shared__ float s_stage[kBlockWaves][kTileEntries][R];
     __shared__ u128 s_acc[kBlockThreads];
     __shared__ u128 s_wsum[kBlockWaves][R];
@@ -783,9 +1016,9 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     if (threadIdx.x == 0) s_stop = 0;
 
     double lam[R];                             // prices of the current iteration
-    const int my_r = lane % R;
-    const int my_q = lane / R;
-    const bool acc_lane = lane < Q * R;
+    const bool acc_lane = Mode == kResident ? lane % RS < R : lane < Q * R;
+    const int my_r = acc_lane ? lane % RS : 0;
+    const int my_q = lane / RS;
     const int my_shift = a.shift[cl * R + my_r];
     A acc = 0;
 
@@ -947,6 +1180,12 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     if (!launch_prices<R, A>(a, cl, blk, pend, s_lam, s_newlam, s_acc)) return;
 #pragma unroll
     for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
+    ResidentCtx rctx = {};
+    Exchange xch = {};
+    if constexpr (Mode == kResident) {
+        rctx = resident_ctx<R>(a, cl, lane, s_lam);
+        xch = exchange_of<R>(a, cl, blk, lane);
+    }
     for (int it = 0; it < a.n_iters; ++it) {
         const KArgs ai = iteration_args<R>(a, it);
         const int rev = ai.reverse;
@@ -965,10 +1204,11 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
         }
         if (!ai.reduce) return;
         if constexpr (Mode == kResident) {
-            const bool go = resident_complete<R, A>(ai, cl, blk, wave, lane, acc, acc_lane, etas[it], lam);
+            const bool go = resident_complete<R, kBlockWaves, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, rctx, xch);
             acc = 0;
-            if (!go || it + 1 == a.n_iters) break;
-            continue;
+            if (go && it + 1 < a.n_iters) continue;
+            resident_outputs<R>(a, cl, blk, wave, lane, rctx);
+            break;
         }
 
         s_acc[threadIdx.x] = acc_lane ? static_cast<u128>(acc) : static_cast<u128>(0);
@@ -1107,8 +1347,9 @@ __global__ void k_update(KArgs a, const double *demand_in, int B) {
 template <int R>
 __global__ void k_prepare(KArgs a, const double *lam, double *canon, int B) {
     const int cl = blockIdx.x * blockDim.x + threadIdx.x;
-    // the resident exchange words start at tag 0 (a.xch_clear words, or none)
-    for (size_t i = cl; i < a.xch_clear; i += static_cast<size_t>(gridDim.x) * blockDim.x) a.xch[i] = 0ull;
+    // the resident exchange words start at 0 (a.xch_clear words, or none)
+    for (size_t i = cl; i < a.xch_clear; i += static_cast<size_t>(gridDim.x) * blockDim.x)
+        reinterpret_cast<uint64_t *>(a.sync)[i] = 0ull;
     if (cl >= B) return;
     bool ok = true;
     for (int r = 0; r < R; ++r) ok = ok && price_ok(lam[cl * R + r]);
@@ -1170,33 +1411,40 @@ hipError_t launch_dense_r(int lpj, const KArgs &a, int B, hipStream_t s) {
 
 // A cooperative launch of `blocks` workgroups of kernel f: refused on the host
 // when the device cannot hold them all at once (nothing is enqueued then).
-inline hipError_t launch_cooperative(const void *f, unsigned blocks, const KArgs &a, hipStream_t s) {
+inline hipError_t launch_cooperative(const void *f, unsigned blocks, const KArgs &a, int threads, size_t lds,
+                                     hipStream_t s) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kBlockThreads, 0) != hipSuccess)
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, lds) != hipSuccess)
         return hipErrorInvalidValue;
     if (static_cast<int64_t>(blocks) > static_cast<int64_t>(per_cu) * cus) return hipErrorCooperativeLaunchTooLarge;
     KArgs copy = a;
     void *args[] = {&copy};
-    return hipLaunchCooperativeKernel(f, dim3(blocks), dim3(kBlockThreads), args, 0, s);
+    return hipLaunchCooperativeKernel(f, dim3(blocks), dim3(threads), args, static_cast<unsigned>(lds), s);
 }
 
-// A multi-iteration launch of kernel f.  With one workgroup per cluster no
-// workgroup waits for another: an ordinary launch.  Otherwise a cooperative
-// one, so that the workgroups of a cluster are co-resident.
-inline hipError_t launch_multi(const void *f, unsigned blocks, const KArgs &a, hipStream_t s) {
+// A multi-iteration launch of kernel f with `lds` bytes of dynamic LDS.  With
+// one workgroup per cluster no workgroup waits for another: an ordinary
+// launch.  Otherwise a cooperative one, so that the workgroups of a cluster
+// are co-resident.
+inline hipError_t launch_multi(const void *f, unsigned blocks, const KArgs &a, hipStream_t s,
+                               int threads = kBlockThreads, size_t lds = 0) {
+    if (lds > 0) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        if (e != hipSuccess) return e;
+    }
     if (a.nblk == 1) {
         KArgs copy = a;
         void *args[] = {&copy};
-        return hipLaunchKernel(f, dim3(blocks), dim3(kBlockThreads), args, 0, s);
+        return hipLaunchKernel(f, dim3(blocks), dim3(threads), args, lds, s);
     }
-    return launch_cooperative(f, blocks, a, s);
+    return launch_cooperative(f, blocks, a, threads, lds, s);
 }
 
 template <int R, int LPJ, typename A>
 const void *dense_multi_kernel(const KArgs &a, bool resident) {
-    if (resident) return reinterpret_cast<const void *>(&k_dense<R, LPJ, A, kResident>);
+    if (resident) return reinterpret_cast<const void *>(&k_resident<R, LPJ, A>);
     return a.defer ? reinterpret_cast<const void *>(&k_dense<R, LPJ, A, kPersistDeferred>)
                    : reinterpret_cast<const void *>(&k_dense<R, LPJ, A, kPersistLocal>);
 }
@@ -1212,7 +1460,8 @@ hipError_t launch_dense_coop_ra(int lpj, const KArgs &a, int B, bool resident, h
         case 16: f = dense_multi_kernel<R, 16, A>(a, resident); break;
         default: return hipErrorInvalidValue;
     }
-    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, s);
+    const size_t lds = resident ? resident_lds(R + 1 + (a.has_pen ? 1 : 0), a.lds_tiles) : 0;
+    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, s, resident ? kResidentThreads : kBlockThreads, lds);
 }
 
 template <int R>

@@ -156,3 +156,78 @@ def test_resident_under_capture_is_refused():
             codes.append(e.code)
     assert codes == [esp.ESP_ERR_INVALID_ARG]
     s.close()
+
+
+def _dense(seed, n_jobs, k, r, **kw):
+    return workloads.random_small(seed, n_jobs, k, r, dense=True, **kw)
+
+
+# AUTO keeps dense tables beyond two tiles per wavefront on chip (8 wavefronts
+# per workgroup: 16 tiles in registers, the rest in LDS): tables around those
+# sizes and around the LDS limit (at R = 8: 32 tiles per workgroup, 33 are
+# streamed), last tiles partial, one to three limbs, 1 to 17 workgroups (the
+# exchange's 16 copies) and the whole device.
+ON_CHIP = {
+    # name: (instance, blocks_per_cluster (0 = library default), T)
+    "k64_r8_15tiles": (lambda: _dense(1, 60, 64, 8), 0, 40),
+    "k64_r8_16tiles": (lambda: _dense(2, 61, 64, 8), 0, 40),
+    "k64_r8_17tiles_1wg": (lambda: _dense(3, 65, 64, 8), 1, 40),
+    "k64_r8_32tiles_1wg": (lambda: _dense(4, 127, 64, 8), 1, 40),
+    "k64_r8_33tiles_1wg": (lambda: _dense(5, 129, 64, 8), 1, 40),
+    "k64_r8_2wg": (lambda: _dense(6, 230, 64, 8), 2, 40),
+    "k16_r5_3wg_2limbs": (lambda: _wide(_dense(7, 1700, 16, 5), 5, 14), 3, 30),
+    "k16_r7_3wg_3limbs": (lambda: _wide(_dense(8, 1300, 16, 7), 6, 36), 3, 30),
+    "k8_r8_9wg_3limbs": (lambda: _wide(_dense(9, 2500, 8, 8), 7, 36), 9, 30),
+    "k4_r1_2wg": (lambda: _dense(10, 3100, 4, 1), 2, 40),
+    "k32_r6_17wg": (lambda: _dense(11, 2611, 32, 6), 17, 40),
+    "k32_r3_3clusters": (lambda: _dense(12, 900, 32, 3, n_clusters=3), 4, 40),
+    "k8_r2_penalties": (lambda: workloads.with_penalties(_dense(13, 1500, 8, 2), 9), 2, 40),
+    "k64_r8_penalties_1wg": (lambda: workloads.with_penalties(_dense(14, 100, 64, 8), 9), 1, 40),
+    "k64_r8_9000jobs": (lambda: workloads.make("large", n_jobs=9000), 0, 12),
+    "300clusters": (lambda: _dense(15, 65, 64, 4, n_clusters=300), 0, 8),
+}
+
+
+@pytest.mark.parametrize("name", sorted(ON_CHIP))
+def test_auto_keeps_tables_on_chip(name):
+    make, blocks, T = ON_CHIP[name]
+    inst = make()
+    _say(f"on chip {name} B={inst.B} N={inst.N} R={inst.R} T={T} blocks={blocks}")
+    s = esp.Solver(inst, blocks_per_cluster=blocks)
+    ref = oracle.Oracle(inst).solve(iters=T, trace_choice=True)
+    for _ in range(2):                               # the second solve reuses the exchange words
+        g = s.solve(s.prices(inst.lam0), T, trace=True, trace_choice=True)
+        torch.cuda.synchronize()
+        assert s.device_status() == 0
+        assert np.array_equal(g["tr_choice"].cpu().numpy(), ref["tr_choice"])
+        assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
+        assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
+        assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
+        assert np.array_equal(g["U"].cpu().numpy(), ref["U"])
+        assert (g["iters_done"].cpu().numpy() == T).all()
+    s.close()
+
+
+def test_on_chip_long_solve_and_stops():
+    """Two launches (1,024 + 76 iterations) over LDS tiles with an exchange,
+    and clusters that stop at different iterations."""
+    inst = _dense(20, 230, 64, 8)
+    _say("on chip, T=1100 on 2 workgroups; staggered stops on 2 workgroups")
+    ref = oracle.Oracle(inst).solve(iters=1100, trace=True)
+    s = esp.Solver(inst, blocks_per_cluster=2)
+    g = s.solve(s.prices(inst.lam0), 1100, trace=True)
+    torch.cuda.synchronize()
+    assert s.device_status() == 0
+    assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
+    assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
+    s.close()
+    inst = _staggered()                              # 94 tiles per cluster
+    ref = oracle.Oracle(inst).solve(tol=1e-3, trace=True)
+    s = esp.Solver(inst, blocks_per_cluster=2)
+    g = s.solve(s.prices(inst.lam0), inst.iters, tol=1e-3)
+    torch.cuda.synchronize()
+    assert s.device_status() == 0
+    assert np.array_equal(g["iters_done"].cpu().numpy(), ref["iters_done"])
+    assert np.array_equal(g["lam"].cpu().numpy(), ref["lam"])
+    assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
+    s.close()
