@@ -235,7 +235,7 @@ __device__ __forceinline__ void partial_totals(const KArgs &a, int k, int cl, co
             for (int u = 0; u < kSumLoads; ++u) s += static_cast<u128>(w[u]);
         }
     }
-    s_red[t] = s;
+    if (t < kBlockThreads) s_red[t] = s;       // (workgroups may be larger)
     __syncthreads();
     // tree over the G groups (integer adds: the order does not matter)
 #pragma unroll

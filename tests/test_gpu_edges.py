@@ -84,3 +84,33 @@ def test_wide_spans_use_128_bit_sums(layout):
     _say(f"128-bit sums {layout}")
     for mode in (esp.ESP_MODE_STREAM, esp.ESP_MODE_PERSISTENT):
         _parity(inst, 60, mode)
+
+
+# Around the gather kernel's 1,024 threads, 4 jobs per thread and the plan's
+# workgroups, dense and CSR, 64- and 128-bit sums, several clusters.
+@pytest.mark.parametrize("n_jobs,k,r,clusters,blocks", [
+    (1, 4, 1, 1, 0), (63, 8, 3, 1, 1), (1023, 16, 8, 1, 1), (1024, 16, 5, 1, 1), (1025, 5, 7, 1, 1),
+    (4095, 4, 2, 1, 1), (4097, 12, 6, 1, 1), (5000, 32, 4, 3, 2), (9001, 7, 8, 2, 3), (3000, 64, 8, 1, 0)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_reduce_demand_edges(n_jobs, k, r, clusters, blocks, wide):
+    inst = workloads.random_small(n_jobs + k, n_jobs, k, r, dense=k != 12, n_clusters=clusters)
+    rng = np.random.default_rng(n_jobs)
+    if wide:
+        inst.demand = (inst.demand.astype(np.float64) *
+                       np.exp2(rng.integers(-30, 31, inst.demand.shape))).astype(np.float32)
+    _say(f"reduce_demand N={n_jobs} K={k} R={r} B={clusters} blocks={blocks} wide={wide}")
+    s = esp.Solver(inst, blocks_per_cluster=blocks)
+    sizes = np.diff(inst.offsets)
+    choice = (rng.random((clusters, n_jobs)) * sizes).astype(np.int32)
+    o = oracle.Oracle(inst)
+    for _ in range(2):
+        U = s.reduce_demand(torch.as_tensor(choice, device="cuda"))
+        torch.cuda.synchronize()
+        for b in range(clusters):
+            assert np.array_equal(U.cpu().numpy()[b], o.demand_sum(b, choice[b])), b
+    choice[-1, -1] = sizes[-1]                         # outside the last job's family
+    U = s.reduce_demand(torch.as_tensor(choice, device="cuda"))
+    torch.cuda.synchronize()
+    assert np.isnan(U.cpu().numpy()[-1]).all() and not np.isnan(U.cpu().numpy()[:-1]).any()
+    assert s.device_status() == esp.ESP_ERR_INVALID_ARG
+    s.close()
