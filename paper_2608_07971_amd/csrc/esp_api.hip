@@ -894,14 +894,12 @@ esp_status esp_score_select(esp_ctx *c, const double *prices, int32_t *choice, v
     if (st != ESP_OK) return st;
     if (prices == nullptr || choice == nullptr) return ESP_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    KArgs p = c->base;
-    p.iters_done = nullptr;
-    if ((st = dev(launch_prepare(c->pl.R, p, prices, nullptr, c->pl.B, s))) != ESP_OK) return st;
+    // the launch checks the prices itself and records bad ones
     KArgs a = c->base;
     a.lam_in = prices;
     a.choice = choice;
     a.reduce = 0;
-    a.skip_mask = kFlagError;
+    a.check = 1;
     return dev(launch_select(c, a, s));
 }
 

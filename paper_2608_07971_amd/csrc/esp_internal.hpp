@@ -104,6 +104,7 @@ struct KArgs {
     int32_t *iters_done;           // [B] or NULL
     int32_t iter_no;               // updates made including this one (1-based)
     double tol;                    // > 0 enables the stop test
+    int32_t check;                 // one-pass launches: validate lam_in in the launch (skip_mask unused)
     int32_t reduce;                // 0: select only (no demand, no ticket)
     int32_t reverse;               // sweep tiles back to front (iteration 0 of the launch)
     int32_t acc128;                // demand accumulators are 128-bit (else 64-bit)

@@ -608,6 +608,28 @@ __device__ __forceinline__ bool next_prices_local(double *s_lam, const double *s
 // Dense families: K = 4 * LPJ configurations per job, LPJ lanes per job
 // ---------------------------------------------------------------------------
 
+// A valid price (Eq. 8): finite and not negative.
+__device__ __forceinline__ bool price_ok(double x) {
+    return x >= 0.0 && x <= 0x1p400;            // false for NaN and +-Inf
+}
+
+// Whether a launch has nothing to do for cluster cl.  A launch that checks its
+// prices itself (a.check: a selection at the caller's prices, which then needs
+// no launch of k_prepare before it, 2 us and the gap to the next launch) skips
+// a cluster with a bad price; its first workgroup records what k_prepare would.
+template <int R>
+__device__ __forceinline__ bool skip_cluster(const KArgs &a, int cl, int blk) {
+    if (!a.check) return a.flags && (a.flags[cl] & a.skip_mask);
+    bool ok = true;
+#pragma unroll
+    for (int r = 0; r < R; ++r) ok = ok && price_ok(a.lam_in[cl * R + r]);
+    if (blk == 0 && threadIdx.x == 0) {
+        a.flags[cl] = (a.flags[cl] & kFlagFrozen) | (ok ? 0 : kFlagError);
+        if (!ok) atomicCAS(a.status, 0, kStatusNonfinite);
+    }
+    return !ok;
+}
+
 // Launch modes of the fused kernels, one instance each, so that the
 // one-iteration instance does without the code (and the registers) of the
 // multi-iteration ones.
@@ -637,7 +659,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
     const int cl = blockIdx.x / a.nblk;
     const int blk = blockIdx.x - cl * a.nblk;
     const int conv = a.conv_at[cl];            // with the flags: one wait for both
-    if (a.flags && (a.flags[cl] & a.skip_mask)) return;
+    if (Mode == kOnePass ? skip_cluster<R>(a, cl, blk) : (a.flags && (a.flags[cl] & a.skip_mask))) return;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x == 0) s_stop = 0;
@@ -1010,7 +1032,7 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     const int cl = blockIdx.x / a.nblk;
     const int blk = blockIdx.x - cl * a.nblk;
     const int conv = a.conv_at[cl];            // with the flags: one wait for both
-    if (a.flags && (a.flags[cl] & a.skip_mask)) return;
+    if (Mode == kOnePass ? skip_cluster<R>(a, cl, blk) : (a.flags && (a.flags[cl] & a.skip_mask))) return;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x == 0) s_stop = 0;
@@ -1360,10 +1382,6 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(KArgs a) {
 // ---------------------------------------------------------------------------
 // Granular price update (esp_update_prices) and price validation
 // ---------------------------------------------------------------------------
-
-__device__ __forceinline__ bool price_ok(double x) {
-    return x >= 0.0 && x <= 0x1p400;            // false for NaN and +-Inf
-}
 
 template <int R>
 __global__ void k_update(KArgs a, const double *demand_in, int B) {

@@ -114,3 +114,29 @@ def test_reduce_demand_edges(n_jobs, k, r, clusters, blocks, wide):
     assert np.isnan(U.cpu().numpy()[-1]).all() and not np.isnan(U.cpu().numpy()[:-1]).any()
     assert s.device_status() == esp.ESP_ERR_INVALID_ARG
     s.close()
+
+
+def test_score_select_checks_prices_per_cluster():
+    """A selection validates its own prices: clusters with a bad price keep
+    their choices untouched and are reported; the others are selected."""
+    inst = workloads.random_small(3, 700, 16, 3, dense=True, n_clusters=5)
+    csr = workloads.random_small(4, 700, 40, 3, n_clusters=5)
+    for prob in (inst, csr):
+        s = esp.Solver(prob)
+        o = oracle.Oracle(prob)
+        lam = np.full((5, 3), 0.25)
+        for bad in (np.nan, np.inf, -1.0, 2.0 ** 401):
+            _say(f"select with a bad price {bad}")
+            lam[1, 2] = lam[4, 0] = bad
+            ch = torch.full((5, 700), -7, dtype=torch.int32, device="cuda")
+            esp.esp_score_select(s.ctx, s.prices(lam), ch)
+            assert s.device_status() == esp.ESP_ERR_NONFINITE
+            for b in range(5):
+                got = ch[b].cpu().numpy()
+                assert (got == -7).all() if b in (1, 4) else np.array_equal(got, o.select(b, lam[b])), b
+        lam[1, 2] = lam[4, 0] = -0.0
+        ch = s.score_select(s.prices(lam))
+        assert s.device_status() == 0
+        for b in range(5):
+            assert np.array_equal(ch[b].cpu().numpy(), o.select(b, lam[b]))
+        s.close()
