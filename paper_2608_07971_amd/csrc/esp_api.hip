@@ -686,7 +686,7 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
                 fill = 0;
                 meta[tile].first_job = static_cast<uint32_t>(j);
             }
-            meta[tile].head[fill / 32] |= 1u << (fill % 32);
+            meta[tile].head[fill % 4] |= 1ull << (fill / 4);
             slot_of[j] = tile * kTileEntries + fill;
             jobs[j].slot = static_cast<uint32_t>(slot_of[j]);
             jobs[j].size = static_cast<uint32_t>(k);
@@ -874,6 +874,14 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     k.status = reinterpret_cast<int32_t *>(ws + pl.o_status);
     k.skip_mask = kFlagError;
     k.acc128 = need_bits > 63 ? 1 : 0;
+    // a lane adds at most 4 winners per tile, each below 2^(need_bits - lgN) units of the window
+    {
+        const int64_t waves = static_cast<int64_t>(pl.nblk) * kBlockWaves;
+        const int64_t adds = 4 * std::max<int64_t>(2, (pl.tiles + waves - 1) / waves);
+        int lg = 0;
+        while ((static_cast<int64_t>(1) << lg) < adds) ++lg;
+        k.lane_f64 = (pl.csr && need_bits <= 63 && need_bits - lgN + lg <= 53) ? 1 : 0;
+    }
     k.n_iters = 1;
     k.B = B;
     k.sync = reinterpret_cast<uint32_t *>(ws + pl.o_sync);

@@ -61,20 +61,18 @@ __global__ __launch_bounds__(kBlockThreads) void k_reserve(KArgs a, ReserveArgs 
             heads = 0;                         // K >= 4: a lane's 4 entries share one job
         } else {
             const TileMeta &m = a.meta[tile];
-            const int e0 = lane * 4, w = e0 >> 5, bit = e0 & 31;
+            const uint64_t lower = (1ull << lane) - 1ull;
             int before = 0, total = 0;
+            heads = 0;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int c = __popc(m.head[q]);
-                total += c;
-                before += (q < w) ? c : 0;
+            for (int i = 0; i < 4; ++i) {
+                total += __popcll(m.head[i]);
+                before += __popcll(m.head[i] & lower);
+                heads |= static_cast<uint32_t>((m.head[i] >> lane) & 1ull) << i;
             }
-            const uint32_t word = m.head[w];
-            const uint32_t upto = (bit == 31) ? 0xffffffffu : ((2u << bit) - 1u);
             first_job = static_cast<int>(m.first_job);
             njobs = total;
-            jt = before + __popc(word & upto) - 1; // entry 0 of a tile always starts a job
-            heads = (word >> bit) & 0xfu;
+            jt = before + static_cast<int>(heads & 1u) - 1; // entry 0 of a tile always starts a job
         }
         uint32_t mn[R];
 #pragma unroll

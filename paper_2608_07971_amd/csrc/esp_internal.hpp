@@ -57,10 +57,11 @@ constexpr int kStatusNonfinite = 3;
 constexpr int kStatusInvalid = 1;
 constexpr int kStatusRange = 7;
 
-// Tile metadata of the CSR layout: bit i of `head` is set when table slot i of
-// the tile starts a job; `first_job` is the job owning slot 0.
+// Tile metadata of the CSR layout: bit l of head[i] is set when slot 4 l + i of
+// the tile (entry i of lane l) starts a job, so that a word is a lane mask of the
+// wavefront that scores the tile; `first_job` is the job owning slot 0.
 struct TileMeta {
-    uint32_t head[8];
+    uint64_t head[4];
     uint32_t first_job;
     uint32_t pad[7];
 };
@@ -108,6 +109,7 @@ struct KArgs {
     int32_t reduce;                // 0: select only (no demand, no ticket)
     int32_t reverse;               // sweep tiles back to front (iteration 0 of the launch)
     int32_t acc128;                // demand accumulators are 128-bit (else 64-bit)
+    int32_t lane_f64;              // 64-bit, and a lane's sums of a CSR pass are exact in binary64
     // Persistent launches run n_iters iterations; t, rows of the traces and the
     // per-iteration choice advance by B, B*R and B*N per iteration, and the
     // sweep direction alternates.

@@ -505,14 +505,19 @@ __device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &x
 //     prices for a second barrier (in workgroup 0 they also write the trace
 //     rows; the prices and counts are written once, by resident_outputs).
 // Returns false when the cluster stops here or a wait timed out.
-template <int R, int Waves, typename A>
+// Group > 0: `acc` is the wavefront's total already, of resource lane / Group.
+template <int R, int Waves, int Group, typename A>
 __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl, int blk, int wave, int lane, A acc,
                                                   double eta, double (&lam)[R], ResidentCtx &ctx, const Exchange &xch) {
     __shared__ A s_wave[Waves][R];
     __shared__ double s_price[R];
     __shared__ int s_go;
-    const A ws = lane_sum<kResidentStep<R>>(acc);
-    if (lane < R) s_wave[wave][lane] = ws;
+    if constexpr (Group > 0) {
+        if (lane % Group == 0 && lane / Group < R) s_wave[wave][lane / Group] = acc;
+    } else {
+        const A ws = lane_sum<kResidentStep<R>>(acc);
+        if (lane < R) s_wave[wave][lane] = ws;
+    }
     __syncthreads();
     if (wave == 0) {
         // (every partial sum fits the accumulator type A: the packer sized A for
@@ -960,7 +965,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(KArgs a) {
             lds_tile(s, up, dp, pp);
             process(tile0 + (2 + s) * stride, up, dp, pp);
         }
-        if (!resident_complete<R, kResidentWaves, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, ctx, xch)) break;
+        if (!resident_complete<R, kResidentWaves, 0, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, ctx, xch)) break;
     }
     resident_outputs<R>(a, cl, blk, wave, lane, ctx);
 }
@@ -977,20 +982,19 @@ constexpr int kDppRowBcast15 = 0x142;
 constexpr int kDppRowBcast31 = 0x143;
 constexpr int kDppWaveShr1 = 0x138;
 
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp_or_i(int old, int v) {
-    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROW_MASK, 0xf, false);
-}
-
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_or_d(double old, double v) {
-    const long long ob = __double_as_longlong(old), vb = __double_as_longlong(v);
-    const int lo = dpp_or_i<CTRL, ROW_MASK>(static_cast<int>(static_cast<unsigned>(ob)),
-                                            static_cast<int>(static_cast<unsigned>(vb)));
-    const int hi = dpp_or_i<CTRL, ROW_MASK>(static_cast<int>(ob >> 32), static_cast<int>(vb >> 32));
+// A lane move whose result is used only in lanes that have a source.
+template <int CTRL>
+__device__ __forceinline__ double dpp_any_d(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(static_cast<unsigned>(b)), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
     return __longlong_as_double(static_cast<long long>(
         (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)));
 }
+
+// Lanes of a wave-wide mask as a per-lane condition, and back.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ uint64_t mask_of(bool c) { return __builtin_amdgcn_ballot_w64(c); }
 
 // acc plus the number of set bits of a wave-wide mask in the lanes below this one.
 __device__ __forceinline__ unsigned below_lane(uint64_t m, unsigned acc) {
@@ -998,17 +1002,94 @@ __device__ __forceinline__ unsigned below_lane(uint64_t m, unsigned acc) {
                                      __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), acc));
 }
 
-// One step of an inclusive segmented max-scan over lanes of (best score,
-// segment-start flag): a lane without a segment start combines the value
-// arriving from lower lanes.  A lane with no source receives its own score
-// and a clear flag, which changes nothing.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void seg_scan_step(double &s, int &f) {
-    const double os = dpp_or_d<CTRL, ROW_MASK>(s, s);
-    const int of = dpp_or_i<CTRL, ROW_MASK>(0, f);
-    // selects and bitwise operators, not branches (the lanes diverge on f)
-    s = ((f == 0) & (os > s)) ? os : s;
-    f = f | of;
+// s = max(s, o) in the lanes of m (no NaN among the scores): one instruction
+// under EXEC, which is saved and restored.  The last two instructions are the
+// wait states a DPP read of s needs (not seen by the compiler behind assembly).
+__device__ __forceinline__ void max_in_lanes(double &s, double o, uint64_t m) {
+    uint64_t ex;
+    asm volatile("s_mov_b64 %[ex], exec\n\t"
+                 "s_mov_b64 exec, %[m]\n\t"
+                 "v_max_f64 %[s], %[s], %[o]\n\t"
+                 "s_mov_b64 exec, %[ex]\n\t"
+                 "s_nop 1"
+                 : [s] "+v"(s), [ex] "=&s"(ex)
+                 : [o] "v"(o), [m] "s"(m));
+}
+
+// One step of an inclusive segmented max-scan over lanes: the lanes of m have
+// no segment start between the lane the value comes from (exclusive) and
+// themselves.
+template <int CTRL>
+__device__ __forceinline__ void seg_scan_step(double &s, uint64_t m) {
+    max_in_lanes(s, dpp_any_d<CTRL>(s), m);
+}
+
+// Segmented inclusive max-scan of s over the lanes, segments starting at the
+// lanes of `starts`.  Which lanes take part in a step follows from `starts`
+// alone, in scalar registers.
+__device__ __forceinline__ void seg_scan(double &s, uint64_t starts) {
+    const uint64_t n1 = ~starts;                         // no start in this lane,
+    const uint64_t n2 = n1 & (n1 << 1);                  // nor in the one below,
+    const uint64_t n4 = n2 & (n2 << 2);                  // the last four lanes,
+    const uint64_t n8 = n4 & (n4 << 4);                  // eight (each limited to its row of 16 below)
+    seg_scan_step<kDppRowShr1>(s, n1 & 0xfffefffefffefffeull);
+    seg_scan_step<kDppRowShr2>(s, n2 & 0xfffcfffcfffcfffcull);
+    seg_scan_step<kDppRowShr4>(s, n4 & 0xfff0fff0fff0fff0ull);
+    seg_scan_step<kDppRowShr8>(s, n8 & 0xff00ff00ff00ff00ull);
+    // rows 1 and 3 (then lanes 32..63): the lanes before the first start there, i.e.
+    // the run of ones from the bottom, which adding one at the bottom clears
+    const uint64_t odd = n1 & 0xffff0000ffff0000ull;
+    seg_scan_step<kDppRowBcast15>(s, odd & ~(odd + 0x0001000000010000ull));
+    const uint32_t up = static_cast<uint32_t>(n1 >> 32);
+    seg_scan_step<kDppRowBcast31>(s, static_cast<uint64_t>(up & ~(up + 1u)) << 32);
+}
+
+// The lanes of m whose next higher lane of m is in `next` (a subset of m).
+// Mirrored, the next lane of m above each lane of `next`: a bit added just
+// above it carries through the zeros of m.
+__device__ __forceinline__ uint64_t lanes_before(uint64_t m, uint64_t next) {
+    const uint64_t rm = __builtin_bitreverse64(m), rn = __builtin_bitreverse64(next);
+    return __builtin_bitreverse64((~rm + (rn << 1)) & rm);
+}
+
+// A uniform 64-bit word of the tile metadata (never written on the device), as a scalar load.
+__device__ __forceinline__ uint64_t scalar_word(const void *p, int i) {
+    typedef const __attribute__((address_space(4))) uint64_t *Words;
+    return ((Words)(uintptr_t)p)[i];
+}
+
+// The sums of x[0..R-1] over the wavefront's lanes: lane l gets the sum of
+// x[l / 8] (0 past R).  Halving exchanges between the lane halves, row pairs
+// and row halves first, so that 7 + 3 additions do for 8 values.
+template <int R>
+__device__ __forceinline__ uint64_t wave_totals(const uint64_t (&x)[R]) {
+    auto word = [](uint64_t v, int i) { return static_cast<uint32_t>(v >> (32 * i)); };
+    auto pair32 = [&](uint64_t a, uint64_t b) {            // lanes 0..31: sum of a, 32..63: of b
+        const auto lo = __builtin_amdgcn_permlane32_swap(word(a, 0), word(b, 0), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(word(a, 1), word(b, 1), false, false);
+        return ((static_cast<uint64_t>(hi[0]) << 32) | lo[0]) + ((static_cast<uint64_t>(hi[1]) << 32) | lo[1]);
+    };
+    auto pair16 = [&](uint64_t a, uint64_t b) {            // even rows: sum of a, odd rows: of b
+        const auto lo = __builtin_amdgcn_permlane16_swap(word(a, 0), word(b, 0), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(word(a, 1), word(b, 1), false, false);
+        return ((static_cast<uint64_t>(hi[0]) << 32) | lo[0]) + ((static_cast<uint64_t>(hi[1]) << 32) | lo[1]);
+    };
+    uint64_t y[4], z[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = i < R ? pair32(x[i < R ? i : 0], i + 4 < R ? x[i + 4 < R ? i + 4 : 0] : 0) : 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) z[i] = i < R ? pair16(y[i], y[i + 2]) : 0;
+    const bool upper = (threadIdx.x & 8) != 0;
+    const uint64_t keep = upper ? z[1] : z[0], give = upper ? z[0] : z[1];
+    auto moved = [&](uint64_t v, auto &&move) {
+        return (static_cast<uint64_t>(static_cast<uint32_t>(move(static_cast<int>(word(v, 1))))) << 32) |
+               static_cast<uint32_t>(move(static_cast<int>(word(v, 0))));
+    };
+    uint64_t v = keep + moved(give, [](int w) { return dpp_i<0x128>(w); });      // row_ror:8
+    v += moved(v, [](int w) { return dpp_i<kDppXor1>(w); });
+    v += moved(v, [](int w) { return dpp_i<kDppXor2>(w); });
+    v += moved(v, [](int w) { return dpp_i<kDppHalfMirror>(w); });
+    return v;
 }
 
 // Two wavefronts per SIMD at least (at most 256 registers): the CSR grid holds
@@ -1016,11 +1097,25 @@ __device__ __forceinline__ void seg_scan_step(double &s, int &f) {
 // (the persistent instances at R = 8 would otherwise take a few more).  The
 // resident instance keeps two tiles live through every iteration and runs
 // one workgroup per CU at most: it may use the whole register file.
-template <int R, typename A, int Mode>
+//
+// The scoring is 76 of a tile's VALU instructions (R = 6); who wins is worked
+// out on lane masks in scalar registers, which leaves about 170 of the 351 that
+// per-lane flags, indices and staged winners took.  A pass over a small table
+// is bound by its tiles' latency, over a large one by memory.
+//
+// Direct: each lane adds the demands of its own winners in binary64, exactly:
+// the packer takes this form when a lane's sum of a pass fits 53 bits of the
+// column's fixed-point window (a.lane_f64).  Otherwise the winners' demands are
+// staged in LDS and added as fixed-point integers, resource by lane (more
+// instructions, and the LDS round trips of a tile's winners on its chain).
+// Measured with one launch per pass, 6 resources: 1,048,576 jobs (388 MB) 64.7 ->
+// 63.0 us, three register sets instead of two 62.6 but 24.1 against 23.0 on
+// 262,144 jobs x 12 x 8.
+template <int R, typename A, int Mode, bool Direct>
 __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_csr(KArgs a) {
     constexpr int RS = Mode == kResident ? kResidentStep<R> : R;   // lane l accumulates resource l mod RS
     constexpr int Q = kWaveSize / RS;          // accumulating lanes per resource
-    __shared__ float s_stage[kBlockWaves][kTileEntries][R];
+    __shared__ float s_stage[Direct ? 1 : kBlockWaves][Direct ? 1 : kTileEntries][R];
     __shared__ u128 s_acc[kBlockThreads];
     __shared__ u128 s_wsum[kBlockWaves][R];
     __shared__ u128 s_bsum[R];
@@ -1043,15 +1138,27 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     const int my_q = lane / RS;
     const int my_shift = a.shift[cl * R + my_r];
     A acc = 0;
+    double sum[R];                             // this lane's demand sums of the pass (Direct)
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum[r] = 0.0;
 
     const float *col = a.table + cl * a.cluster_stride;
     const size_t lane_off = static_cast<size_t>(lane) * 4;
-    const int hshift = (lane & 7) * 4;                   // this lane's 4 head bits in its word
-    const uint64_t above = lane == kWaveSize - 1 ? 0ull : ~0ull << (lane + 1);   // the lanes above this one
+    struct Heads { uint64_t m[4]; };           // m[i]: the lanes whose entry i starts a job
+    // Direct: the wavefront's totals, of resource l / 8 in lane l; the lanes' sums start again
+    auto take_totals = [&]() {
+        uint64_t x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            x[r] = static_cast<uint64_t>(ldexp(sum[r], -a.shift[cl * R + r]));
+            sum[r] = 0.0;
+        }
+        return wave_totals<R>(x);
+    };
     const double sw = a.has_pen ? a.switch_cost[cl] : 0.0;
     const int stride = a.nblk * kBlockWaves;
     const int last = a.tiles - 1;
-    auto load_tile = [&](int t, int rev, f4 &u, f4 (&d)[R], f4 &pn, uint32_t &hw) {
+    auto load_tile = [&](int t, int rev, f4 &u, f4 (&d)[R], f4 &pn, Heads &h) {
         const int tl = rev ? last - t : t;
         const float *p = col + static_cast<size_t>(tl) * kTileEntries + lane_off;
         u = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p));
@@ -1059,13 +1166,14 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
         for (int r = 0; r < R; ++r)
             d[r] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p + (r + 1) * a.col_len));
         if (a.has_pen) pn = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p + (R + 1) * a.col_len));
-        hw = a.meta[tl].head[lane >> 3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h.m[i] = scalar_word(a.meta + tl, i);
     };
-    // Score one tile, find every family's winner and stage the winners'
-    // demands (or write the choices).
-    auto process = [&](const KArgs &ai, int t, const f4 &u, const f4 (&d)[R], const f4 &pn, uint32_t hw) {
+    // Score one tile, find every family's winner and add up (or stage) the
+    // winners' demands, or write the choices.  Everything about where families
+    // start and who wins is a mask over the lanes in scalar registers.
+    auto process = [&](const KArgs &ai, int t, const f4 &u, const f4 (&d)[R], const f4 &pn, const Heads &h) {
         const int tl = ai.reverse ? last - t : t;
-        const uint32_t hbits = (hw >> hshift) & 0xFu;
         double sc[4];
         // the penalty test is taken once per tile (a uniform branch)
         auto scores = [&](auto pen) {
@@ -1080,102 +1188,84 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
         };
         if (a.has_pen) scores(std::true_type{});
         else scores(std::false_type{});
-        // Lane-local pass: one running best (lowest entry on ties) that
-        // restarts at every head.  At a head the run so far is either a
-        // segment that began at an earlier head of this lane (complete: its
-        // winner is marked) or, before the lane's first head, this lane's
-        // part of a segment from lower lanes (pre).  At the end the run is
-        // the segment left open at the lane's end.
-        // (selects, not branches: the lanes diverge on their head bits)
-        const bool h0 = hbits & 1u;
-        double run_s = sc[0], pre_s = sc[0];
-        int run_i = 0, pre_i = 0;
-        bool open = h0;
-        uint32_t local_win = 0;
+        // Lane-local pass: one running best (lowest entry on ties, at[q]: the
+        // lanes where it is entry q) that restarts at every head.  At a head
+        // the run so far is either a segment that began at an earlier head of
+        // this lane (complete: its winner is marked, win[q]) or, before the
+        // lane's first head, this lane's part of a segment from lower lanes
+        // (pre, entry q in the lanes pre_at[q]).  At the end the run is the
+        // segment left open at the lane's end.
+        double run = sc[0], pre = sc[0];
+        uint64_t at[4] = {~0ull, 0, 0, 0}, win[4] = {0, 0, 0, 0}, pre_at[3] = {0, 0, 0};
+        uint64_t open = h.m[0];
 #pragma unroll
         for (int i = 1; i < 4; ++i) {
-            const bool head = (hbits >> i) & 1u;
-            local_win |= static_cast<uint32_t>(head & open) << run_i;
-            const bool first = head & !open;
-            pre_s = first ? run_s : pre_s;
-            pre_i = first ? run_i : pre_i;
-            const bool take = head | (sc[i] > run_s);
-            run_s = take ? sc[i] : run_s;
-            run_i = take ? i : run_i;
-            open = open | head;
-        }
-        const bool has_head = hbits != 0;
-        const bool has_pre = has_head & !h0;
-        // Segment maxima across lanes: after the scan, ps is the largest score
-        // of the segment open at this lane's end, over its slots up to here.
-        double ps = run_s;
-        int pf = has_head ? 1 : 0;
-        seg_scan_step<kDppRowShr1, 0xf>(ps, pf);
-        seg_scan_step<kDppRowShr2, 0xf>(ps, pf);
-        seg_scan_step<kDppRowShr4, 0xf>(ps, pf);
-        seg_scan_step<kDppRowShr8, 0xf>(ps, pf);
-        seg_scan_step<kDppRowBcast15, 0xa>(ps, pf);
-        seg_scan_step<kDppRowBcast31, 0xc>(ps, pf);
-        // the same at the previous lane (lane 0: its own value)
-        const double qs = dpp_or_d<kDppWaveShr1, 0xf>(ps, ps);
-        // Each winner is marked by the lane that holds it.  The winner of a
-        // segment is its first slot with the segment's largest score: in the
-        // lane where the running maximum last rose (a head, or a run strictly
-        // above everything before it: lane `jump`), its run's best, unless the
-        // part of the next head lane before its first head (slots above all
-        // of the segment's others) beats it strictly (`pre_wins` there).
-        const bool jump = has_head | (ps > qs) | (lane == 0);
-        const bool pre_wins = has_pre & (pre_s > qs);
-        const uint64_t m_head = __ballot(has_head);
-        const uint64_t m_rise = __ballot(jump);
-        const uint64_t m_keep = m_head & ~__ballot(pre_wins);   // head lanes whose pre part loses
-        // the next lane above this one where the maximum rises or a segment starts
-        const uint64_t later = m_rise & above;
-        const int nxt = later ? __builtin_ctzll(later) : kWaveSize;
-        const bool run_wins = jump & ((nxt == kWaveSize) | (((m_keep >> (nxt & (kWaveSize - 1))) & 1ull) != 0ull));
-        const uint32_t wbits = local_win | (pre_wins ? 1u << pre_i : 0u) | (run_wins ? 1u << run_i : 0u);
-        // Rank of this lane's first winner among the tile's winners (slot
-        // order: lane, then entry): the winners in lower lanes, counted from
-        // one ballot per entry position; n_win is the same for every lane.
-        const uint64_t b0 = __ballot(wbits & 1u), b1 = __ballot(wbits & 2u);
-        const uint64_t b2 = __ballot(wbits & 4u), b3 = __ballot(wbits & 8u);
-        int rank = static_cast<int>(below_lane(b3, below_lane(b2, below_lane(b1, below_lane(b0, 0u)))));
-        const int n_win = __popcll(b0) + __popcll(b1) + __popcll(b2) + __popcll(b3);
-        if (wbits) {
-            uint32_t hwm[8];
-            if (ai.choice) {
+            const uint64_t done = h.m[i] & open, first = h.m[i] & ~open;
+            const uint64_t take = h.m[i] | mask_of(sc[i] > run);
+            pre = in_mask(first) ? run : pre;
+            run = in_mask(take) ? sc[i] : run;
 #pragma unroll
-                for (int q = 0; q < 8; ++q) hwm[q] = a.meta[tl].head[q];
+            for (int q = 0; q < i; ++q) {
+                win[q] |= done & at[q];
+                pre_at[q] |= first & at[q];
+                at[q] &= ~take;
             }
+            at[i] = take;
+            open |= h.m[i];
+        }
+        const uint64_t heads = open;           // lanes with a head
+        // Segment maxima across lanes: after the scan, top is the largest score
+        // of the segment open at this lane's end, over its slots up to here.
+        double top = run;
+        seg_scan(top, heads);
+        const double prev = dpp_any_d<kDppWaveShr1>(top);    // at the previous lane (a tile starts with a head)
+        // The winner of a segment is its first slot with the segment's largest
+        // score: in the lane where the running maximum last rose (a head, or a
+        // run strictly above everything before it), its run's best, unless the
+        // part of the next head lane before its first head (slots above all of
+        // the segment's others) beats it strictly (pre_wins there).
+        const uint64_t rise = heads | mask_of(top > prev);
+        const uint64_t pre_wins = heads & ~h.m[0] & mask_of(pre > prev);
+        const uint64_t run_wins = rise & ~lanes_before(rise, rise & ~(heads & ~pre_wins));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) win[q] |= (run_wins & at[q]) | (q < 3 ? pre_wins & pre_at[q < 3 ? q : 0] : 0ull);
+        if (ai.choice) {
+            // job = first_job + (heads at or before the slot) - 1;
+            // config = slot - (the last head at or before it)
+            int j = static_cast<int>(static_cast<uint32_t>(scalar_word(a.meta + tl, 4))) - 1 +
+                    static_cast<int>(below_lane(h.m[3], below_lane(h.m[2], below_lane(h.m[1], below_lane(h.m[0], 0u)))));
+            const int mine = lane * 4 + (in_mask(h.m[3]) ? 3 : in_mask(h.m[2]) ? 2 : in_mask(h.m[1]) ? 1 : 0);
+            const uint64_t lower = heads & ((1ull << lane) - 1ull);
+            int start = __shfl(mine, lower ? 63 - __clzll(lower) : 0);
+            int32_t *const out = ai.choice + static_cast<size_t>(cl) * a.N;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (!((wbits >> i) & 1u)) continue;
-                if (ai.reduce) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r) s_stage[wave][rank][r] = d[r][i];
-                }
-                ++rank;
-                if (ai.choice) {
-                    // job = first_job + (heads at or before the slot) - 1;
-                    // config = slot - (the last head at or before it)
-                    const int slot = lane * 4 + i;
-                    const int w = slot >> 5;
-                    int cnt = 0, hs = -1;
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        uint32_t m = hwm[q];
-                        if (q == w) m &= 0xffffffffu >> (31 - (slot & 31));
-                        if (q <= w) {
-                            cnt += __popc(m);
-                            if (m) hs = q * 32 + 31 - __clz(m);
-                        }
-                    }
-                    const int j = static_cast<int>(a.meta[tl].first_job) + cnt - 1;
-                    ai.choice[static_cast<size_t>(cl) * a.N + j] = slot - hs;
-                }
+                const bool head = in_mask(h.m[i]);
+                start = head ? lane * 4 + i : start;
+                j += head ? 1 : 0;
+                if (in_mask(win[i])) out[j] = lane * 4 + i - start;
             }
         }
-        if (ai.reduce) {
+        if (!ai.reduce) return;
+        if constexpr (Direct) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (!in_mask(win[i])) continue;
+#pragma unroll
+                for (int r = 0; r < R; ++r) sum[r] += static_cast<double>(d[r][i]);
+            }
+        } else {
+            // Rank of this lane's first winner among the tile's winners (slot
+            // order: lane, then entry); n_win is the same for every lane.
+            int rank = static_cast<int>(below_lane(win[3], below_lane(win[2], below_lane(win[1], below_lane(win[0], 0u)))));
+            const int n_win = __popcll(win[0]) + __popcll(win[1]) + __popcll(win[2]) + __popcll(win[3]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (!in_mask(win[i])) continue;
+#pragma unroll
+                for (int r = 0; r < R; ++r) s_stage[wave][rank][r] = d[r][i];
+                ++rank;
+            }
             wave_sync();
             if (acc_lane) {
 #pragma unroll 1
@@ -1190,7 +1280,7 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     // prefetched tile is scored where it landed, without copies.
     f4 nu, npn = {}, bu, bpn = {};
     f4 nd[R], bd[R];
-    uint32_t nhw = 0, bhw = 0;
+    Heads nhw = {}, bhw = {};
     const int tile0 = blk * kBlockWaves + wave;
     Pending<R, A> pend;
     if constexpr (Mode != kResident) pending_loads<R, A>(a, cl, conv, pend);   // issued first: they return first
@@ -1226,17 +1316,23 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
         }
         if (!ai.reduce) return;
         if constexpr (Mode == kResident) {
-            const bool go = resident_complete<R, kBlockWaves, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, rctx, xch);
+            if constexpr (Direct) acc = take_totals();
+            const bool go = resident_complete<R, kBlockWaves, Direct ? 8 : 0, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, rctx, xch);
             acc = 0;
             if (go && it + 1 < a.n_iters) continue;
             resident_outputs<R>(a, cl, blk, wave, lane, rctx);
             break;
         }
 
-        s_acc[threadIdx.x] = acc_lane ? static_cast<u128>(acc) : static_cast<u128>(0);
-        acc = 0;
-        __syncthreads();
-        if (threadIdx.x < kBlockWaves * R) {
+        if constexpr (Direct) {
+            const uint64_t tot = take_totals();
+            if ((lane & 7) == 0 && lane / 8 < R) s_wsum[wave][lane / 8] = tot;
+        } else {
+            s_acc[threadIdx.x] = acc_lane ? static_cast<u128>(acc) : static_cast<u128>(0);
+            acc = 0;
+            __syncthreads();
+        }
+        if (!Direct && threadIdx.x < kBlockWaves * R) {
             const int w = threadIdx.x / R, r = threadIdx.x % R;
             u128 v = 0;
 #pragma unroll   // independent LDS loads, all in flight
@@ -1571,24 +1667,28 @@ template <int R>
 hipError_t launch_csr_r(const KArgs &a, int B, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>(B) * a.nblk), block(kBlockThreads);
     if (a.acc128)
-        hipLaunchKernelGGL((k_csr<R, u128, kOnePass>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_csr<R, u128, kOnePass, false>), grid, block, 0, s, a);
+    else if (a.lane_f64)
+        hipLaunchKernelGGL((k_csr<R, uint64_t, kOnePass, true>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((k_csr<R, uint64_t, kOnePass>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_csr<R, uint64_t, kOnePass, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
-template <int R, typename A>
+template <int R, typename A, bool Direct>
 const void *csr_multi_kernel(const KArgs &a, bool resident) {
-    if (resident) return reinterpret_cast<const void *>(&k_csr<R, A, kResident>);
-    return a.defer ? reinterpret_cast<const void *>(&k_csr<R, A, kPersistDeferred>)
-                   : reinterpret_cast<const void *>(&k_csr<R, A, kPersistLocal>);
+    if (resident) return reinterpret_cast<const void *>(&k_csr<R, A, kResident, Direct>);
+    return a.defer ? reinterpret_cast<const void *>(&k_csr<R, A, kPersistDeferred, Direct>)
+                   : reinterpret_cast<const void *>(&k_csr<R, A, kPersistLocal, Direct>);
 }
 
 template <int R>
 hipError_t launch_csr_coop_r(const KArgs &a, int B, bool resident, hipStream_t s) {
     // several workgroups need deferred completion, or the resident exchange
     if (!resident && !a.defer && a.nblk != 1) return hipErrorInvalidValue;
-    const void *f = a.acc128 ? csr_multi_kernel<R, u128>(a, resident) : csr_multi_kernel<R, uint64_t>(a, resident);
+    const void *f = a.acc128 ? csr_multi_kernel<R, u128, false>(a, resident)
+                    : a.lane_f64 ? csr_multi_kernel<R, uint64_t, true>(a, resident)
+                                 : csr_multi_kernel<R, uint64_t, false>(a, resident);
     return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, s);
 }
 

@@ -86,6 +86,26 @@ def test_wide_spans_use_128_bit_sums(layout):
         _parity(inst, 60, mode)
 
 
+# CSR scans: one-entry families (256 winners in a tile), families that end with
+# a tile, families over many lanes, equal scores (dyadic), and demands whose
+# lanes' sums fit 53 bits (22 bits + the 3 of 8 additions) or need the 64-bit
+# fixed point (52 + 3 bits; 52 + 11 bits for the whole sum of up to 2,047 jobs).
+@pytest.mark.parametrize("sizes", ["ones", "k2", "k3", "k5", "k128", "k255", "k256", "mixed", "mixed_dyadic"])
+@pytest.mark.parametrize("bits", [22, 52])
+def test_csr_scan_edges(sizes, bits):
+    if sizes.startswith("mixed"):
+        inst = workloads.random_small(21, 900, 256, 6, iters=25, dyadic=sizes == "mixed_dyadic")
+    else:
+        k = 1 if sizes == "ones" else int(sizes[1:])
+        inst = workloads.random_small(k, 40 if k > 100 else 1500, k, 1 + k % 8, dense=True, iters=25, dyadic=k == 5)
+    d = np.floor(inst.demand.astype(np.float64) * 2.0 ** 20) / 2.0 ** 20
+    small = np.random.default_rng(9).random(d.shape) < 0.5
+    inst.demand = np.where(small, d * 2.0 ** (22 - bits), d).astype(np.float32)
+    for mode in (esp.ESP_MODE_STREAM, esp.ESP_MODE_PERSISTENT, esp.ESP_MODE_RESIDENT):
+        _say(f"csr {sizes} bits={bits} mode={mode}")
+        _parity(inst, 25, mode)
+
+
 # Around the gather kernel's 1,024 threads, 4 jobs per thread and the plan's
 # workgroups, dense and CSR, 64- and 128-bit sums, several clusters.
 @pytest.mark.parametrize("n_jobs,k,r,clusters,blocks", [
