@@ -71,14 +71,14 @@ enum {
                                  stays there for the launch),
                                  and for solves with tol > 0 (the loop ends on the device once
                                  every cluster has converged); one launch per iteration
-                                 otherwise, where the two drivers run at about the same speed; falls
+                                 otherwise, where the two drivers run within 3%; falls
                                  back to one launch per iteration when the device cannot hold
                                  the grid co-resident */
     ESP_MODE_STREAM = 1,      /* one fused launch per iteration */
     ESP_MODE_PERSISTENT = 2,  /* one cooperative launch runs all iterations, streaming the table
-                                 from memory every iteration; the workgroups of a cluster meet at
-                                 a barrier after each iteration (ESP_ERR_DEVICE when the grid
-                                 cannot be co-resident) */
+                                 from memory every iteration; the workgroups of a cluster
+                                 exchange their exact sums through counted words after each
+                                 iteration (ESP_ERR_DEVICE when the grid cannot be co-resident) */
     ESP_MODE_RESIDENT = 3     /* one launch runs all iterations over tiles held in registers
                                  (every wavefront of the grid holds at most two 256-entry tiles:
                                  tables of up to about 2,000 tiles per cluster); each iteration
@@ -89,7 +89,7 @@ enum {
                                  ESP_MODE_AUTO takes this driver whenever the table fits. */
 };
 
-#define ESP_AUTO_PERSISTENT_BYTES (64u << 20)
+#define ESP_AUTO_PERSISTENT_BYTES (256u << 20)   /* what the memory-side cache holds */
 
 /* Opaque context: packed table + launch plan, created by esp_create. */
 typedef struct esp_ctx esp_ctx;

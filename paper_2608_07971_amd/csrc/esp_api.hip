@@ -406,18 +406,18 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
         // per-solve state (and the exchange words of a resident solve)
         KArgs p = kb;
         p.iters_done = d_iters;
-        p.xch_clear = (resident && nblk_res > 1)
+        p.xch_clear = (persistent && (resident ? nblk_res : c->pl.nblk) > 1)
                           ? static_cast<size_t>(B) * kSyncSlots * kSyncStride / 2 : 0;
         if ((st = dev(launch_prepare(R, p, prices, prices, B, s))) != ESP_OK) return st;
     }
-    // With several workgroups per cluster and no resident launch, every
+    // With several workgroups per cluster and one launch per iteration, every
     // iteration only publishes its sums; the next launch (or the closing
-    // one) completes it.  With one workgroup per cluster, or in a resident
+    // one) completes it.  With one workgroup per cluster, or in a persistent
     // launch, the iteration is completed where it runs.
     bool defer = false;
     KArgs base;
     auto setup = [&]() {
-        defer = !resident && c->pl.nblk > 1;
+        defer = !persistent && c->pl.nblk > 1;
         base = kb;
         base.lam_in = prices;
         base.lam_dst = prices;
@@ -471,16 +471,12 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
             if (e == hipSuccess) continue;
             (void)hipGetLastError();           // not left for the next launch's error check
             // A refused grid enqueues nothing.  AUTO falls back to one launch
-            // per iteration: from here on for deferred persistent launches
-            // (same completion scheme), from the first iteration for resident
-            // ones (which can only be refused at their first launch).
-            if (!c->auto_mode || (resident && i0 > 0)) return ESP_ERR_DEVICE;
-            persistent = false;
+            // per iteration, from the first iteration (a grid is refused at its
+            // first launch or never).
+            if (!c->auto_mode || i0 > 0) return ESP_ERR_DEVICE;
+            persistent = resident = false;
             c->fell_back = true;
-            if (resident) {
-                resident = false;
-                setup();
-            }
+            setup();
         }
         for (int i = 0; i < n; ++i)
             if ((st = dev(launch_select(c, iteration_launch(i0 + i, 1), s))) != ESP_OK) return st;
@@ -623,7 +619,7 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     const int groups = kWaveSize / (R * limbs);
     const bool resident_ok = static_cast<int64_t>(pl.tiles) <= 2ll * pl.nblk * kBlockWaves &&
                              (pl.nblk == 1 || (groups >= 1 && pl.nblk <= 32 * groups && pl.nblk <= 4 * 255));
-    if (need_bits <= kCountShift) limbs = 1;
+    limbs = need_bits <= kCountShift ? 1 : (need_bits + kLimbBits - 1) / kLimbBits;   // as exchanged
     int lds_tiles = 0;
     bool on_chip = resident_ok;
     if (!pl.csr) {

@@ -18,21 +18,22 @@ constexpr int kMaxR = 8;
 constexpr int kMaxFamily = 256;                     // configurations per job
 constexpr int kLaunchChunk = 1024;                  // iterations per persistent launch
 constexpr int kColumnPadTiles = 7;                  // unused tiles at the end of every column
-// Barrier words of a cluster in a persistent deferred launch, each in its own
-// 256-byte line: arrival counters of kSyncGroups groups of workgroups (blk mod
-// kSyncGroups), the count of complete groups, and one release word per group.
-constexpr int kSyncGroups = 8;
-constexpr int kSyncSlots = 2 * kSyncGroups + 1;
-constexpr int kSyncStride = 64;                     // uint32 words between barrier words
+// Exchange words of a cluster in a multi-iteration launch: kSyncSlots slots of
+// kSyncStride uint32 words (256 bytes) each.
+constexpr int kSyncSlots = 17;
+constexpr int kSyncStride = 64;
 // Buffers of per-workgroup sums: 0 and 1 hold the sums of solve iterations by
 // iteration parity (deferred completion), 2 those of in-launch completion.
 constexpr int kPartialBuffers = 3;
 constexpr int kInLaunchBuffer = 2;
-// Resident launches with several workgroups per cluster exchange their sums
+// Multi-iteration launches with several workgroups per cluster exchange their sums
 // as limbs (at most 3 for 127-bit sums) in counted 64-bit words: the count of
 // workgroups above kCountShift, their limbs' sum below.
 constexpr int kMaxLimbs = 3;
 constexpr int kCountShift = 56;
+constexpr int kLimbBits = 45;                       // the limbs of 2,048 workgroups add up to kCountShift bits
+// Copies that share the first adds of `words` words (a slot line of 8, 16 or 24).
+__host__ __device__ constexpr int exchange_copies(int words) { return words <= 8 ? 16 : words <= 16 ? 8 : 4; }
 // Dense resident workgroups: 8 wavefronts, two per SIMD (a lone wavefront
 // issues an instruction every 7 cycles or so while it scores), one workgroup
 // per CU.  Tiles beyond two per wavefront lie in LDS: the CU's 160 KB less
@@ -115,8 +116,8 @@ struct KArgs {
     // sweep direction alternates.
     int32_t n_iters;               // 1 for a single-iteration launch
     int32_t B;                     // clusters
-    uint32_t *sync;                // [B][kSyncSlots][kSyncStride] barrier words of persistent
-                                   // deferred launches (reset per solve)
+    uint32_t *sync;                // [B][kSyncSlots][kSyncStride] exchange words of
+                                   // multi-iteration launches (cleared per solve)
     int32_t sweep_alt;             // alternate the sweep direction between iterations
     // Penalty of the ESP score (Eq. 7): column R + 1 of each cluster holds
     // |penalty| per entry, its sign bit set when the entry is not the job's
@@ -138,11 +139,10 @@ struct KArgs {
     int32_t *conv_at;              // [B] iteration whose completion met tol, 0 while none has
     double *trace_lam;             // [iters][B][R]: row m - 1 receives lambda_{m+1}, or NULL
     double *trace_U;               // [iters][B][R]: row m - 1 receives U_m, or NULL
-    // Resident launches (tiles kept on chip, every iteration completed in the
-    // launch): exchange words in the space of `sync`.
+    // Multi-iteration launches (every iteration completed in the launch).
     int32_t limbs;                 // limbs per workgroup sum
     int32_t lds_tiles;             // tiles per wavefront kept in LDS (dense resident launches)
-    size_t xch_clear;              // words k_prepare sets to 0 before a resident solve (0: none)
+    size_t xch_clear;              // words of `sync` k_prepare sets to 0 before a solve of such launches (0: none)
 };
 
 constexpr int kStatusTimeout = 8;  // a persistent wait exceeded its bound

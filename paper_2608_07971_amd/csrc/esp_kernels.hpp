@@ -129,11 +129,11 @@ __device__ bool finish_cluster(const KArgs &a, int cl, int blk, const u128 *bsum
 // is met.  The writer (workgroup 0 of the cluster) also stores
 // lambda_{m+1} into the caller's prices and lam_ws, the trace rows of
 // iteration m, the iteration count, and m as the stop iteration.
-template <int R, typename A, bool Coherent>
+template <int R, typename A>
 __device__ bool complete_iteration(const KArgs &a, int cl, int m, int t_m, bool writer, const double *lam_m,
                                    double *lam_next, u128 *s_red, const A (&v)[kSumLoads]) {
     __shared__ int s_ok[R];
-    partial_totals<R, A, Coherent>(a, m & 1, cl, v, s_red);
+    partial_totals<R, A, false>(a, m & 1, cl, v, s_red);
     const int t = threadIdx.x;
     if (t < R) {
         const size_t i = static_cast<size_t>(cl) * R + t;
@@ -208,7 +208,7 @@ __device__ bool launch_prices(const KArgs &a, int cl, int blk, const Pending<R, 
             if (t < R) s_tmp[t] = p.lam_m;
             __syncthreads();
             const bool stop =
-                complete_iteration<R, A, false>(a, cl, a.pend_m, a.pend_t, blk == 0, s_tmp, s_lam, s_red, p.v);
+                complete_iteration<R, A>(a, cl, a.pend_m, a.pend_t, blk == 0, s_tmp, s_lam, s_red, p.v);
             return !(stop && a.defer);
         }
         if (a.defer) return false;
@@ -220,45 +220,13 @@ __device__ bool launch_prices(const KArgs &a, int cl, int blk, const Pending<R, 
     return true;
 }
 
-// Barrier word i of cluster cl (see kSyncSlots).
-__device__ __forceinline__ uint32_t *sync_word(const KArgs &a, int cl, int i) {
-    return a.sync + (static_cast<size_t>(cl) * kSyncSlots + i) * kSyncStride;
-}
-
 // End of iteration m in a deferred launch: publish the workgroup's sums
-// (bsum, LDS) into buffer m & 1.  A one-iteration launch stores plainly: the
-// next launch reads the sums after the launch boundary.  A persistent launch
-// publishes with completed agent-scope exchanges and then arrives at the
-// cluster's barrier: one atomic add on its group's counter (blk mod
-// kSyncGroups); the group's last arrival adds one to the count of complete
-// groups, and the last group releases every group by storing m into the
-// groups' release words.  Adds to one address are serialized at the device
-// coherence point (about 11 ns each), so no word takes more than one add per
-// group member per iteration, and each group polls its own release word.
-template <int R, bool Persist>
+// (bsum, LDS) into buffer m & 1.  Plain stores: the next launch reads the sums
+// after the launch boundary.
+template <int R>
 __device__ __forceinline__ void publish_iteration(const KArgs &a, int cl, int blk, int m, const u128 *bsum) {
     const int t = threadIdx.x;
-    if constexpr (Persist) {
-        if (t < kWaveSize) {
-            publish_sums<R>(a, m & 1, cl, blk, bsum);
-            if (t == 0) {
-                const int g = blk % kSyncGroups;
-                const int groups = a.nblk < kSyncGroups ? a.nblk : kSyncGroups;
-                const uint32_t size = static_cast<uint32_t>((a.nblk - g + kSyncGroups - 1) / kSyncGroups);
-                const uint32_t um = static_cast<uint32_t>(m);
-                const uint32_t n = __hip_atomic_fetch_add(sync_word(a, cl, g), 1u, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT);
-                if (n + 1u == size * um) {
-                    const uint32_t c = __hip_atomic_fetch_add(sync_word(a, cl, kSyncGroups), 1u, __ATOMIC_RELAXED,
-                                                              __HIP_MEMORY_SCOPE_AGENT);
-                    if (c + 1u == static_cast<uint32_t>(groups) * um)
-                        for (int h = 0; h < groups; ++h)
-                            __hip_atomic_store(sync_word(a, cl, kSyncGroups + 1 + h), um, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-        }
-    } else if (t < R) {
+    if (t < R) {
         uint64_t *p = partials_of<R>(a, m & 1, cl) + (static_cast<size_t>(blk) * R + t) * 2;
         const u128 v = bsum[t];
         p[0] = static_cast<uint64_t>(v);
@@ -266,42 +234,15 @@ __device__ __forceinline__ void publish_iteration(const KArgs &a, int cl, int bl
     }
 }
 
-// Inside a persistent launch: wait until the workgroup's group is released
-// for iteration m (its release word reaches m, compared modulo 2^32), i.e.
-// every workgroup of the cluster has published iteration m.  The release
-// word is stored only after the last arrival add returned, every arrival add
-// is issued after the workgroup's exchanges completed, and the sums are
-// loaded only after the release value is back, all with agent-scope atomics
-// performed at the memory-side coherence point: the loads return the
-// published sums (the argument is spelled out at publish_sums).  Bounded: about
-// 2 s of the 100 MHz real-time counter, or until another workgroup has
-// recorded an error; then the status records a timeout and the function
-// returns false in every waiting workgroup.
-__device__ bool wait_iteration(const KArgs &a, int cl, int blk, int m, int *s_go) {
-    if (threadIdx.x == 0) {
-        const uint32_t *w = sync_word(a, cl, kSyncGroups + 1 + blk % kSyncGroups);
-        int go = 1;
-        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-        while (static_cast<int32_t>(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                                    static_cast<uint32_t>(m)) < 0) {
-            __builtin_amdgcn_s_sleep(4);
-            if (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                __builtin_amdgcn_s_memrealtime() - t0 > 200000000ull) {
-                atomicCAS(a.status, 0, kStatusTimeout);
-                go = 0;
-                break;
-            }
-        }
-        *s_go = go;
-    }
-    __syncthreads();
-    return *s_go != 0;
-}
-
 // ---------------------------------------------------------------------------
-// Resident launches: every iteration is completed inside the launch; with
-// several workgroups per cluster their exact sums meet in counted words.
+// Multi-iteration launches: every iteration is completed inside the launch;
+// with several workgroups per cluster their exact sums meet in counted words.
 // ---------------------------------------------------------------------------
+//
+// Streaming launches use it too: a barrier of the grid and every workgroup
+// reading every other's sums took 3 to 4 us more of each iteration (262,144
+// ragged jobs x 6 21.0 -> 18.6 us, 1,048,576 64.8 -> 62.0, 262,144 x 12 x 8 23.2 ->
+// 20.5), which also puts them ahead of one launch per iteration (21.6, 63.7, 22.9).
 
 // A workgroup's sum for resource r is split into a.limbs limbs (one when the
 // cluster's total fits kCountShift bits, else kLimbBits each): words of a
@@ -324,10 +265,8 @@ __device__ bool wait_iteration(const KArgs &a, int cl, int blk, int m, int *s_go
 // a word's count clears it at once (no other add to it comes before m + 2):
 // it waits for the clear to have been performed before its own next add, in
 // m + 1, and nobody adds to m + 2 before m + 1 is complete.  Release words
-// alternate too; the tag tells m from m - 2.  The words take the place of the
-// persistent driver's barrier words, which resident launches do not use; the
-// solve's prologue clears them.
-constexpr int kLimbBits = 48;
+// alternate too; the tag tells m from m - 2.  The solve's prologue clears the
+// words.
 constexpr uint64_t kLimbMask = (1ull << kLimbBits) - 1;
 constexpr int kSlotWords = kSyncStride / 2;    // 64-bit words of a 256-byte slot of the barrier words
 constexpr int kReplicas = 4;
@@ -351,13 +290,13 @@ __device__ __forceinline__ Exchange exchange_of(const KArgs &a, int cl, int blk,
     const int q = lane < x.words ? lane : 0;
     const int line = (x.words + 7) / 8 * 8;                // 8, 16 or 24 words
     const int span = (2 * line + kSlotWords - 1) / kSlotWords * kSlotWords;   // both sets of a copy
-    x.copies = min(a.nblk, line == 8 ? 16 : line == 16 ? 8 : 4);
+    x.copies = min(a.nblk, exchange_copies(x.words));
     x.replicas = min(a.nblk, kReplicas);
     const int mine = blk % x.copies;
     x.in_copy = a.nblk / x.copies + (mine < a.nblk % x.copies ? 1 : 0);
     x.set_words = line;
     x.copy = base + mine * span + q;
-    const int top = line == 8 ? 16 : line == 16 ? 8 : 4;
+    const int top = exchange_copies(x.words);
     x.root = base + top * span + q;
     // 17 slots: 16 copies and the root with release lines in the second halves, or 8 (4) copies, the
     // root and 8 release lines of 16 (24) words
@@ -506,9 +445,16 @@ __device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &x
 //     rows; the prices and counts are written once, by resident_outputs).
 // Returns false when the cluster stops here or a wait timed out.
 // Group > 0: `acc` is the wavefront's total already, of resource lane / Group.
-template <int R, int Waves, int Group, typename A>
+// between() runs in every wavefront before the second barrier: a streaming
+// launch issues its next tile loads there, wavefront 0 after its exchange
+// (memory returns in order: loads issued before would hold the exchange up).
+struct Nothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int R, int Waves, int Group, typename A, typename Between = Nothing>
 __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl, int blk, int wave, int lane, A acc,
-                                                  double eta, double (&lam)[R], ResidentCtx &ctx, const Exchange &xch) {
+                                                  double eta, double (&lam)[R], ResidentCtx &ctx, const Exchange &xch,
+                                                  Between &&between = {}) {
     __shared__ A s_wave[Waves][R];
     __shared__ double s_price[R];
     __shared__ int s_go;
@@ -564,6 +510,7 @@ __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl
             }
         }
     }
+    between();
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < R; ++r) lam[r] = s_price[r];
@@ -597,18 +544,6 @@ __device__ __forceinline__ KArgs iteration_args(const KArgs &a, int it) {
     return ai;
 }
 
-// Between the iterations of a persistent launch with one workgroup per
-// cluster: the workgroup computed the new prices itself (s_newlam) and
-// continues with them unless the cluster has stopped.
-template <int R>
-__device__ __forceinline__ bool next_prices_local(double *s_lam, const double *s_newlam, const int *s_stop) {
-    __syncthreads();
-    if (*s_stop) return false;
-    if (threadIdx.x < R) s_lam[threadIdx.x] = s_newlam[threadIdx.x];
-    __syncthreads();
-    return true;
-}
-
 // ---------------------------------------------------------------------------
 // Dense families: K = 4 * LPJ configurations per job, LPJ lanes per job
 // ---------------------------------------------------------------------------
@@ -637,28 +572,26 @@ __device__ __forceinline__ bool skip_cluster(const KArgs &a, int cl, int blk) {
 
 // Launch modes of the fused kernels, one instance each, so that the
 // one-iteration instance does without the code (and the registers) of the
-// multi-iteration ones.
+// multi-iteration ones.  Multi-iteration launches complete every iteration
+// themselves (resident_complete).
 constexpr int kOnePass = 0;          // one iteration or one selection per launch
-constexpr int kPersistLocal = 1;     // several iterations, one workgroup per cluster
-constexpr int kPersistDeferred = 2;  // cooperative, several iterations, deferred completion between them
+constexpr int kPersist = 1;          // several iterations, the table streamed in each
 // CSR tables: several iterations over tiles held in registers for the whole
-// launch (each wavefront has at most two: no table loads inside the loop); the
-// launch completes every iteration itself, with one workgroup per cluster or
-// through the tagged exchange between the workgroups of a cluster.  (Dense
-// tables have k_resident.)
-constexpr int kResident = 3;
+// launch (each wavefront has at most two: no table loads inside the loop).
+// (Dense tables have k_resident.)
+constexpr int kResident = 2;
 
 template <int R, int LPJ, typename A, int Mode>
 __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
     constexpr int JPT = kWaveSize / LPJ;       // jobs per tile
-    constexpr int Q = kWaveSize / R;           // accumulating lanes per resource
+    constexpr int RS = Mode == kPersist ? kResidentStep<R> : R;   // lane l accumulates resource l mod RS
+    constexpr int Q = kWaveSize / RS;          // accumulating lanes per resource
     __shared__ float s_stage[kBlockWaves][JPT][R];
     __shared__ u128 s_acc[kBlockThreads];
     __shared__ u128 s_wsum[kBlockWaves][R];
     __shared__ u128 s_bsum[R];
     __shared__ double s_lam[R];
     __shared__ double s_newlam[R];
-    __shared__ int s_go;
     __shared__ int s_stop;
 
     const int cl = blockIdx.x / a.nblk;
@@ -672,9 +605,9 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
     double lam[R];                             // prices of the current iteration
 
     const float *col = a.table + cl * a.cluster_stride;
-    const int my_r = lane % R;
-    const int my_q = lane / R;
-    const bool acc_lane = lane < Q * R;
+    const bool acc_lane = Mode == kPersist ? lane % RS < R : lane < Q * R;
+    const int my_r = acc_lane ? lane % RS : 0;
+    const int my_q = lane / RS;
     const int my_shift = a.shift[cl * R + my_r];
     const int gl = lane % LPJ;                 // lane within its job group
     const int jt = lane / LPJ;                 // job within the tile
@@ -748,7 +681,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
     // Three register buffers, rotated by unrolling: while one tile is scored
     // the loads of the next two are in flight (18 KB per wavefront at R = 8).
     // In a persistent launch the first two loads of the next iteration are
-    // issued before the wait for its prices.
+    // issued before its prices are there.
     f4 ua, ub, uc, pa = {}, pb = {}, pc = {};
     f4 da[R], db[R], dc[R];
     const int tile0 = blk * kBlockWaves + wave;
@@ -760,11 +693,23 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
         load_tile(min(tile0 + stride, last), rev, ub, db, pb);
     };
     Pending<R, A> pend;
-    pending_loads<R, A>(a, cl, conv, pend);    // issued first: they return first
+    if constexpr (Mode == kOnePass) pending_loads<R, A>(a, cl, conv, pend);    // issued first: they return first
     prefetch_two(a.reverse);                   // in flight during a pending completion
-    if (!launch_prices<R, A>(a, cl, blk, pend, s_lam, s_newlam, s_acc)) return;
+    const double *etas = nullptr;
+    ResidentCtx rctx = {};
+    Exchange xch = {};
+    if constexpr (Mode == kOnePass) {
+        if (!launch_prices<R, A>(a, cl, blk, pend, s_lam, s_newlam, s_acc)) return;
 #pragma unroll
-    for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
+        for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
+    } else {
+        etas = resident_etas(a, cl);
+#pragma unroll
+        for (int r = 0; r < R; ++r) lam[r] = a.lam_in[cl * R + r];
+        rctx = resident_ctx<R>(a, cl, lane, a.lam_in + static_cast<size_t>(cl) * R);
+        xch = exchange_of<R>(a, cl, blk, lane);
+        __syncthreads();
+    }
     for (int it = 0; it < a.n_iters; ++it) {
         const KArgs ai = iteration_args<R>(a, it);
         const int rev = ai.reverse;
@@ -781,6 +726,15 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
             if (t2 < a.tiles) process(ai, t2, uc, dc, pc);
         }
         if (!ai.reduce) return;
+        if constexpr (Mode == kPersist) {
+            // (the last iteration's loads go unused)
+            const bool go = resident_complete<R, kBlockWaves, 0, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, rctx, xch,
+                                                                    [&]() { prefetch_two(rev ^ a.sweep_alt); });
+            acc = 0;
+            if (go && it + 1 < a.n_iters) continue;
+            resident_outputs<R>(a, cl, blk, wave, lane, rctx);
+            break;
+        }
 
         // Workgroup sum per resource (integer adds: any order gives the same value).
         s_acc[threadIdx.x] = acc_lane ? static_cast<u128>(acc) : static_cast<u128>(0);
@@ -801,25 +755,9 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
             s_bsum[threadIdx.x] = v;
         }
         __syncthreads();
-        if (Mode == kPersistDeferred || (Mode == kOnePass && a.defer)) {
-            publish_iteration<R, Mode == kPersistDeferred>(ai, cl, blk, ai.iter_no, s_bsum);
-            if (Mode == kOnePass || it + 1 == a.n_iters) break;    // the next launch completes it
-            prefetch_two(rev ^ a.sweep_alt);
-            if (!wait_iteration(a, cl, blk, ai.iter_no, &s_go)) break;
-            A v[kSumLoads];
-            partial_loads<R, A, true>(ai, ai.iter_no & 1, cl, v);
-            if (complete_iteration<R, A, true>(ai, cl, ai.iter_no, ai.t, blk == 0, s_lam, s_newlam, s_acc, v)) break;
-            if (threadIdx.x < R) s_lam[threadIdx.x] = s_newlam[threadIdx.x];
-            __syncthreads();
-        } else {
-            // the next iteration's first tiles do not depend on the prices
-            if (Mode == kPersistLocal && it + 1 < a.n_iters) prefetch_two(rev ^ a.sweep_alt);
-            finish_cluster<R, false>(ai, cl, blk, s_bsum, s_lam, s_newlam, &s_stop);
-            if (Mode == kOnePass || it + 1 == a.n_iters) break;
-            if (!next_prices_local<R>(s_lam, s_newlam, &s_stop)) break;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
+        if (a.defer) publish_iteration<R>(ai, cl, blk, ai.iter_no, s_bsum);   // the next launch completes it
+        else finish_cluster<R, false>(ai, cl, blk, s_bsum, s_lam, s_newlam, &s_stop);
+        break;                                 // (one iteration per launch)
     }
 }
 
@@ -1113,7 +1051,7 @@ __device__ __forceinline__ uint64_t wave_totals(const uint64_t (&x)[R]) {
 // 262,144 jobs x 12 x 8.
 template <int R, typename A, int Mode, bool Direct>
 __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_csr(KArgs a) {
-    constexpr int RS = Mode == kResident ? kResidentStep<R> : R;   // lane l accumulates resource l mod RS
+    constexpr int RS = Mode != kOnePass ? kResidentStep<R> : R;   // lane l accumulates resource l mod RS
     constexpr int Q = kWaveSize / RS;          // accumulating lanes per resource
     __shared__ float s_stage[Direct ? 1 : kBlockWaves][Direct ? 1 : kTileEntries][R];
     __shared__ u128 s_acc[kBlockThreads];
@@ -1121,7 +1059,6 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     __shared__ u128 s_bsum[R];
     __shared__ double s_lam[R];
     __shared__ double s_newlam[R];
-    __shared__ int s_go;
     __shared__ int s_stop;
 
     const int cl = blockIdx.x / a.nblk;
@@ -1133,7 +1070,7 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     if (threadIdx.x == 0) s_stop = 0;
 
     double lam[R];                             // prices of the current iteration
-    const bool acc_lane = Mode == kResident ? lane % RS < R : lane < Q * R;
+    const bool acc_lane = Mode != kOnePass ? lane % RS < R : lane < Q * R;
     const int my_r = acc_lane ? lane % RS : 0;
     const int my_q = lane / RS;
     const int my_shift = a.shift[cl * R + my_r];
@@ -1283,20 +1220,24 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     Heads nhw = {}, bhw = {};
     const int tile0 = blk * kBlockWaves + wave;
     Pending<R, A> pend;
-    if constexpr (Mode != kResident) pending_loads<R, A>(a, cl, conv, pend);   // issued first: they return first
+    if constexpr (Mode == kOnePass) pending_loads<R, A>(a, cl, conv, pend);   // issued first: they return first
     load_tile(min(tile0, last), a.reverse, nu, nd, npn, nhw);   // in flight during a pending completion (clamped: no branch)
     if constexpr (Mode == kResident)
         load_tile(min(tile0 + stride, last), a.reverse, bu, bd, bpn, bhw);   // the launch's second tile
     const double *etas = nullptr;
-    if constexpr (Mode == kResident) etas = resident_etas(a, cl);   // read after launch_prices' barrier
-    if (!launch_prices<R, A>(a, cl, blk, pend, s_lam, s_newlam, s_acc)) return;
-#pragma unroll
-    for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
     ResidentCtx rctx = {};
     Exchange xch = {};
-    if constexpr (Mode == kResident) {
-        rctx = resident_ctx<R>(a, cl, lane, s_lam);
+    if constexpr (Mode == kOnePass) {
+        if (!launch_prices<R, A>(a, cl, blk, pend, s_lam, s_newlam, s_acc)) return;
+#pragma unroll
+        for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
+    } else {
+        etas = resident_etas(a, cl);
+#pragma unroll
+        for (int r = 0; r < R; ++r) lam[r] = a.lam_in[cl * R + r];
+        rctx = resident_ctx<R>(a, cl, lane, a.lam_in + static_cast<size_t>(cl) * R);
         xch = exchange_of<R>(a, cl, blk, lane);
+        __syncthreads();
     }
     for (int it = 0; it < a.n_iters; ++it) {
         const KArgs ai = iteration_args<R>(a, it);
@@ -1315,9 +1256,13 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
             }
         }
         if (!ai.reduce) return;
-        if constexpr (Mode == kResident) {
+        if constexpr (Mode != kOnePass) {
             if constexpr (Direct) acc = take_totals();
-            const bool go = resident_complete<R, kBlockWaves, Direct ? 8 : 0, A>(a, it, cl, blk, wave, lane, acc, etas[it], lam, rctx, xch);
+            const bool go = resident_complete<R, kBlockWaves, Direct ? 8 : 0, A>(
+                a, it, cl, blk, wave, lane, acc, etas[it], lam, rctx, xch, [&]() {
+                    // (the last iteration's loads go unused)
+                    if constexpr (Mode == kPersist) load_tile(min(tile0, last), rev ^ a.sweep_alt, nu, nd, npn, nhw);
+                });
             acc = 0;
             if (go && it + 1 < a.n_iters) continue;
             resident_outputs<R>(a, cl, blk, wave, lane, rctx);
@@ -1347,26 +1292,9 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
             s_bsum[threadIdx.x] = v;
         }
         __syncthreads();
-        if (Mode == kPersistDeferred || (Mode == kOnePass && a.defer)) {
-            publish_iteration<R, Mode == kPersistDeferred>(ai, cl, blk, ai.iter_no, s_bsum);
-            if (Mode == kOnePass || it + 1 == a.n_iters) break;    // the next launch completes it
-            load_tile(min(tile0, last), rev ^ a.sweep_alt, nu, nd, npn, nhw);
-            if (!wait_iteration(a, cl, blk, ai.iter_no, &s_go)) break;
-            A v[kSumLoads];
-            partial_loads<R, A, true>(ai, ai.iter_no & 1, cl, v);
-            if (complete_iteration<R, A, true>(ai, cl, ai.iter_no, ai.t, blk == 0, s_lam, s_newlam, s_acc, v)) break;
-            if (threadIdx.x < R) s_lam[threadIdx.x] = s_newlam[threadIdx.x];
-            __syncthreads();
-        } else {
-            // the next iteration's first tile does not depend on the prices
-            if (Mode == kPersistLocal && it + 1 < a.n_iters)
-                load_tile(min(tile0, last), rev ^ a.sweep_alt, nu, nd, npn, nhw);
-            finish_cluster<R, false>(ai, cl, blk, s_bsum, s_lam, s_newlam, &s_stop);
-            if (Mode == kOnePass || it + 1 == a.n_iters) break;
-            if (!next_prices_local<R>(s_lam, s_newlam, &s_stop)) break;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
+        if (a.defer) publish_iteration<R>(ai, cl, blk, ai.iter_no, s_bsum);   // the next launch completes it
+        else finish_cluster<R, false>(ai, cl, blk, s_bsum, s_lam, s_newlam, &s_stop);
+        break;                                 // (one iteration per launch)
     }
 }
 
@@ -1523,7 +1451,6 @@ __global__ void k_prepare(KArgs a, const double *lam, double *canon, int B) {
     if (a.iters_done) {
         a.iters_done[cl] = 0;
         a.tickets[cl] = 0u;          // 0 between launches; cleared for scratch shared between solves
-        for (int i = 0; i < kSyncSlots; ++i) a.sync[(static_cast<size_t>(cl) * kSyncSlots + i) * kSyncStride] = 0u;
         a.conv_at[cl] = 0;
         for (int r = 0; r < R; ++r) {
             const double v = lam[cl * R + r];
@@ -1589,8 +1516,10 @@ inline hipError_t launch_cooperative(const void *f, unsigned blocks, const KArgs
 // one workgroup per cluster no workgroup waits for another: an ordinary
 // launch.  Otherwise a cooperative one, so that the workgroups of a cluster
 // are co-resident.
-inline hipError_t launch_multi(const void *f, unsigned blocks, const KArgs &a, hipStream_t s,
+inline hipError_t launch_multi(const void *f, unsigned blocks, const KArgs &a, int words, hipStream_t s,
                                int threads = kBlockThreads, size_t lds = 0) {
+    // a copy's count field (the registers let no more workgroups be co-resident anyway)
+    if (a.nblk > 255 * exchange_copies(words)) return hipErrorCooperativeLaunchTooLarge;
     if (lds > 0) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         if (e != hipSuccess) return e;
@@ -1604,31 +1533,29 @@ inline hipError_t launch_multi(const void *f, unsigned blocks, const KArgs &a, h
 }
 
 template <int R, int LPJ, typename A>
-const void *dense_multi_kernel(const KArgs &a, bool resident) {
+const void *dense_multi_kernel(bool resident) {
     if (resident) return reinterpret_cast<const void *>(&k_resident<R, LPJ, A>);
-    return a.defer ? reinterpret_cast<const void *>(&k_dense<R, LPJ, A, kPersistDeferred>)
-                   : reinterpret_cast<const void *>(&k_dense<R, LPJ, A, kPersistLocal>);
+    return reinterpret_cast<const void *>(&k_dense<R, LPJ, A, kPersist>);
 }
 
 template <int R, typename A>
 hipError_t launch_dense_coop_ra(int lpj, const KArgs &a, int B, bool resident, hipStream_t s) {
     const void *f = nullptr;
     switch (lpj) {
-        case 1: f = dense_multi_kernel<R, 1, A>(a, resident); break;
-        case 2: f = dense_multi_kernel<R, 2, A>(a, resident); break;
-        case 4: f = dense_multi_kernel<R, 4, A>(a, resident); break;
-        case 8: f = dense_multi_kernel<R, 8, A>(a, resident); break;
-        case 16: f = dense_multi_kernel<R, 16, A>(a, resident); break;
+        case 1: f = dense_multi_kernel<R, 1, A>(resident); break;
+        case 2: f = dense_multi_kernel<R, 2, A>(resident); break;
+        case 4: f = dense_multi_kernel<R, 4, A>(resident); break;
+        case 8: f = dense_multi_kernel<R, 8, A>(resident); break;
+        case 16: f = dense_multi_kernel<R, 16, A>(resident); break;
         default: return hipErrorInvalidValue;
     }
     const size_t lds = resident ? resident_lds(R + 1 + (a.has_pen ? 1 : 0), a.lds_tiles) : 0;
-    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, s, resident ? kResidentThreads : kBlockThreads, lds);
+    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s, resident ? kResidentThreads : kBlockThreads, lds);
 }
 
 template <int R>
 hipError_t launch_dense_coop_r(int lpj, const KArgs &a, int B, bool resident, hipStream_t s) {
-    // several workgroups need deferred completion, or the resident exchange
-    if (!resident && !a.defer && a.nblk != 1) return hipErrorInvalidValue;
+    if (a.defer) return hipErrorInvalidValue;              // these launches complete their iterations
     return a.acc128 ? launch_dense_coop_ra<R, u128>(lpj, a, B, resident, s)
                     : launch_dense_coop_ra<R, uint64_t>(lpj, a, B, resident, s);
 }
@@ -1676,20 +1603,18 @@ hipError_t launch_csr_r(const KArgs &a, int B, hipStream_t s) {
 }
 
 template <int R, typename A, bool Direct>
-const void *csr_multi_kernel(const KArgs &a, bool resident) {
+const void *csr_multi_kernel(bool resident) {
     if (resident) return reinterpret_cast<const void *>(&k_csr<R, A, kResident, Direct>);
-    return a.defer ? reinterpret_cast<const void *>(&k_csr<R, A, kPersistDeferred, Direct>)
-                   : reinterpret_cast<const void *>(&k_csr<R, A, kPersistLocal, Direct>);
+    return reinterpret_cast<const void *>(&k_csr<R, A, kPersist, Direct>);
 }
 
 template <int R>
 hipError_t launch_csr_coop_r(const KArgs &a, int B, bool resident, hipStream_t s) {
-    // several workgroups need deferred completion, or the resident exchange
-    if (!resident && !a.defer && a.nblk != 1) return hipErrorInvalidValue;
-    const void *f = a.acc128 ? csr_multi_kernel<R, u128, false>(a, resident)
-                    : a.lane_f64 ? csr_multi_kernel<R, uint64_t, true>(a, resident)
-                                 : csr_multi_kernel<R, uint64_t, false>(a, resident);
-    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, s);
+    if (a.defer) return hipErrorInvalidValue;              // these launches complete their iterations
+    const void *f = a.acc128 ? csr_multi_kernel<R, u128, false>(resident)
+                    : a.lane_f64 ? csr_multi_kernel<R, uint64_t, true>(resident)
+                                 : csr_multi_kernel<R, uint64_t, false>(resident);
+    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s);
 }
 
 

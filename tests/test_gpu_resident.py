@@ -231,3 +231,23 @@ def test_on_chip_long_solve_and_stops():
     assert np.array_equal(g["lam"].cpu().numpy(), ref["lam"])
     assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
     s.close()
+
+
+@pytest.mark.parametrize("mode", ["resident", "persistent"])
+def test_limbs_of_512_workgroups(mode):
+    """128-bit sums of 512 workgroups: the low limbs are arbitrary, so their
+    total nears 512 times the largest limb and must not reach the count."""
+    inst = workloads.random_small(12, 80000, 7, 1, dense=True, iters=6)
+    rng = np.random.default_rng(3)
+    inst.demand = (inst.demand.astype(np.float64) *
+                   np.exp2(rng.integers(-36, 37, inst.demand.shape))).astype(np.float32)
+    inst.eta0 = np.full(inst.B, 1e-14)
+    print(f"[gpu-case] 512 workgroups {mode}", flush=True)
+    s = esp.Solver(inst, mode=esp.ESP_MODE_RESIDENT if mode == "resident" else esp.ESP_MODE_PERSISTENT)
+    g = s.solve(s.prices(inst.lam0), 6, trace=True)
+    torch.cuda.synchronize()
+    ref = oracle.Oracle(inst).solve(iters=6, trace=True)
+    assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
+    assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
+    assert s.device_status() == 0
+    s.close()
