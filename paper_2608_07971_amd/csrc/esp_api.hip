@@ -870,6 +870,7 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     k.status = reinterpret_cast<int32_t *>(ws + pl.o_status);
     k.skip_mask = kFlagError;
     k.acc128 = need_bits > 63 ? 1 : 0;
+    k.sum_f64 = need_bits <= 53 ? 1 : 0;
     // a lane adds at most 4 winners per tile, each below 2^(need_bits - lgN) units of the window
     {
         const int64_t waves = static_cast<int64_t>(pl.nblk) * kBlockWaves;

@@ -3,6 +3,8 @@
 // sums, and the cross-workgroup completion of a cluster's sums.
 #pragma once
 
+#include <type_traits>
+
 #include "esp_internal.hpp"
 
 #pragma clang fp contract(off)
@@ -81,9 +83,12 @@ __device__ __forceinline__ void wave_sync() {
 // packer guarantees that every nonzero value of the column has its lowest set
 // bit at or above 2^sh and its highest below 2^(sh + bits(A) - 1 -
 // ceil(log2(N + 1))), so the shift is exact and N of them cannot overflow A.
+// (A = double: the value itself, where every sum fits 53 bits.)
 template <typename A>
 __device__ __forceinline__ A fx_of(float v, int sh) {
-    if constexpr (sizeof(A) <= 8) {
+    if constexpr (std::is_floating_point_v<A>) {
+        return static_cast<A>(v);
+    } else if constexpr (sizeof(A) <= 8) {
         // v * 2^-sh is a whole number below 2^63 in binary64: exact at each step
         return static_cast<A>(ldexp(static_cast<double>(v), -sh));
     } else {
@@ -118,6 +123,12 @@ __device__ __forceinline__ double fx_to_double(u128 a, int sh) {
 __device__ __forceinline__ double fx_to_double(uint64_t a, int sh) {
     return ldexp(static_cast<double>(a), sh);
 }
+
+// A sum held in binary64 is the total; as words to exchange, its integer multiple of 2^sh.
+__device__ __forceinline__ double fx_to_double(double a, int) { return a; }
+__device__ __forceinline__ uint64_t fx_words(double a, int sh) { return static_cast<uint64_t>(ldexp(a, -sh)); }
+template <typename A>
+__device__ __forceinline__ uint64_t fx_words(A a, int) { return static_cast<uint64_t>(a); }
 
 // Partial-sum buffer k of cluster cl: [nblk][R][2] 64-bit words (low, high).
 template <int R>

@@ -311,42 +311,41 @@ __device__ __forceinline__ Exchange exchange_of(const KArgs &a, int cl, int blk,
 
 // Sum of v over the lanes with the same index modulo RP (a power of two up to
 // 8), in every lane: rotations inside the 16-lane rows, then row swaps.
+template <typename A>
+struct Words {                                 // a value as 32-bit words
+    uint32_t w[sizeof(A) / 4];
+};
 template <typename A, typename Move>
-__device__ __forceinline__ A add_moved(A v, Move &&move) {
-    constexpr int kWords = static_cast<int>(sizeof(A) / 4);
-    A o = 0;
+__device__ __forceinline__ A moved(A v, Move &&move) {
+    Words<A> x = __builtin_bit_cast(Words<A>, v);
 #pragma unroll
-    for (int i = 0; i < kWords; ++i)
-        o |= static_cast<A>(static_cast<uint32_t>(move(static_cast<int>(static_cast<uint32_t>(v >> (32 * i)))))) << (32 * i);
-    return v + o;
+    for (uint32_t &w : x.w) w = static_cast<uint32_t>(move(static_cast<int>(w)));
+    return __builtin_bit_cast(A, x);
 }
 template <int RP, typename A>
 __device__ __forceinline__ A lane_sum(A v) {
     constexpr int kRor1 = 0x121, kRor2 = 0x122, kRor4 = 0x124, kRor8 = 0x128;
-    if constexpr (RP <= 1) v = add_moved(v, [](int x) { return dpp_i<kRor1>(x); });
-    if constexpr (RP <= 2) v = add_moved(v, [](int x) { return dpp_i<kRor2>(x); });
-    if constexpr (RP <= 4) v = add_moved(v, [](int x) { return dpp_i<kRor4>(x); });
-    v = add_moved(v, [](int x) { return dpp_i<kRor8>(x); });
+    if constexpr (RP <= 1) v += moved(v, [](int x) { return dpp_i<kRor1>(x); });
+    if constexpr (RP <= 2) v += moved(v, [](int x) { return dpp_i<kRor2>(x); });
+    if constexpr (RP <= 4) v += moved(v, [](int x) { return dpp_i<kRor4>(x); });
+    v += moved(v, [](int x) { return dpp_i<kRor8>(x); });
     // both halves of a swap of x with itself: the other row in every lane of one of them
-    constexpr int kWords = static_cast<int>(sizeof(A) / 4);
-    A lo = 0, hi = 0;
+    Words<A> lo = __builtin_bit_cast(Words<A>, v), hi = lo;
 #pragma unroll
-    for (int i = 0; i < kWords; ++i) {
-        const uint32_t x = static_cast<uint32_t>(v >> (32 * i));
-        const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-        lo |= static_cast<A>(p[0]) << (32 * i);
-        hi |= static_cast<A>(p[1]) << (32 * i);
+    for (size_t i = 0; i < sizeof(A) / 4; ++i) {
+        const auto p = __builtin_amdgcn_permlane16_swap(lo.w[i], hi.w[i], false, false);
+        lo.w[i] = p[0];
+        hi.w[i] = p[1];
     }
-    v = lo + hi;
-    lo = hi = 0;
+    v = __builtin_bit_cast(A, lo) + __builtin_bit_cast(A, hi);
+    lo = hi = __builtin_bit_cast(Words<A>, v);
 #pragma unroll
-    for (int i = 0; i < kWords; ++i) {
-        const uint32_t x = static_cast<uint32_t>(v >> (32 * i));
-        const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-        lo |= static_cast<A>(p[0]) << (32 * i);
-        hi |= static_cast<A>(p[1]) << (32 * i);
+    for (size_t i = 0; i < sizeof(A) / 4; ++i) {
+        const auto p = __builtin_amdgcn_permlane32_swap(lo.w[i], hi.w[i], false, false);
+        lo.w[i] = p[0];
+        hi.w[i] = p[1];
     }
-    return lo + hi;
+    return __builtin_bit_cast(A, lo) + __builtin_bit_cast(A, hi);
 }
 
 // The smallest power of two not below R: in resident launches lane l
@@ -474,11 +473,13 @@ __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl
         bool go = true;
         if (a.nblk > 1) {
             // lane l R + r exchanges limb l of resource r
-            uint64_t v = static_cast<uint64_t>(tot);
-            if (xch.words > R)
+            uint64_t v = fx_words(tot, ctx.shift);
+            if constexpr (!std::is_floating_point_v<A>) if (xch.words > R)
                 v = static_cast<uint64_t>(static_cast<u128>(tot) >> (kLimbBits * (lane < xch.words ? lane / R : 0))) & kLimbMask;
             go = exchange_total(a, xch, a.iter_no + it, lane, v);
-            if (xch.words == R) {
+            if constexpr (std::is_floating_point_v<A>) {
+                tot = fx_to_double(v, ctx.shift);
+            } else if (xch.words == R) {
                 tot = static_cast<A>(v);
             } else {
                 u128 t = 0;
@@ -778,7 +779,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_dense(KArgs a) {
 // against four wavefronts per workgroup with every workgroup reading every
 // other's sums: 4,096 jobs x 32 x 4 4.1 -> 2.5, 64 x 8 x 4 1.25 -> 0.85.
 // A kernel of its own: the registers and branches of the streaming loops cost
-// every iteration here.
+// every iteration here.  A = double when the whole sum fits 53 bits (a.sum_f64):
+// every partial sum is exact in binary64, so the conversions to and from fixed
+// point leave the chain (64 jobs x 8 x 4 1.04 -> 0.95 us an iteration, 4,096 x 32 x
+// 4 2.76 -> 2.55, 700 x 4 x 8 2.06 -> 1.76).
 template <int R, int LPJ, typename A>
 __global__ __launch_bounds__(kResidentThreads) void k_resident(KArgs a) {
     constexpr int JPT = kWaveSize / LPJ;       // jobs per tile
@@ -1533,7 +1537,9 @@ inline hipError_t launch_multi(const void *f, unsigned blocks, const KArgs &a, i
 }
 
 template <int R, int LPJ, typename A>
-const void *dense_multi_kernel(bool resident) {
+const void *dense_multi_kernel(const KArgs &a, bool resident) {
+    if constexpr (sizeof(A) == 8)
+        if (resident && a.sum_f64) return reinterpret_cast<const void *>(&k_resident<R, LPJ, double>);
     if (resident) return reinterpret_cast<const void *>(&k_resident<R, LPJ, A>);
     return reinterpret_cast<const void *>(&k_dense<R, LPJ, A, kPersist>);
 }
@@ -1542,11 +1548,11 @@ template <int R, typename A>
 hipError_t launch_dense_coop_ra(int lpj, const KArgs &a, int B, bool resident, hipStream_t s) {
     const void *f = nullptr;
     switch (lpj) {
-        case 1: f = dense_multi_kernel<R, 1, A>(resident); break;
-        case 2: f = dense_multi_kernel<R, 2, A>(resident); break;
-        case 4: f = dense_multi_kernel<R, 4, A>(resident); break;
-        case 8: f = dense_multi_kernel<R, 8, A>(resident); break;
-        case 16: f = dense_multi_kernel<R, 16, A>(resident); break;
+        case 1: f = dense_multi_kernel<R, 1, A>(a, resident); break;
+        case 2: f = dense_multi_kernel<R, 2, A>(a, resident); break;
+        case 4: f = dense_multi_kernel<R, 4, A>(a, resident); break;
+        case 8: f = dense_multi_kernel<R, 8, A>(a, resident); break;
+        case 16: f = dense_multi_kernel<R, 16, A>(a, resident); break;
         default: return hipErrorInvalidValue;
     }
     const size_t lds = resident ? resident_lds(R + 1 + (a.has_pen ? 1 : 0), a.lds_tiles) : 0;

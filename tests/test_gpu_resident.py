@@ -251,3 +251,27 @@ def test_limbs_of_512_workgroups(mode):
     assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
     assert s.device_status() == 0
     s.close()
+
+
+# The whole sum's bits (span + 9 for 500 jobs, + 13 for 5,000) on both sides of the
+# 53 that binary64 holds and of the 56 that one exchanged word holds.
+@pytest.mark.parametrize("n_jobs,log_jobs", [(500, 9), (5000, 13)])
+@pytest.mark.parametrize("need", [52, 53, 54, 56, 57, 63])
+def test_sums_at_the_accumulators_edges(n_jobs, log_jobs, need):
+    inst = workloads.random_small(n_jobs + need, n_jobs, 16, 5, dense=True, iters=15)
+    low = 2.0 ** (2 - (need - log_jobs))                   # values below 4: `need - log_jobs` bits
+    d = np.floor(inst.demand.astype(np.float64) * 2.0 ** 20) / 2.0 ** 20
+    small = np.random.default_rng(need).random(d.shape) < 0.5
+    d = np.where(small, np.floor(d * 2.0 ** 20) * low, d)
+    d[:, 0, :] = 3.75
+    d[:, 1, :] = low
+    inst.demand = d.astype(np.float32)
+    print(f"[gpu-case] need {need} bits, {n_jobs} jobs", flush=True)
+    s = esp.Solver(inst, mode=esp.ESP_MODE_RESIDENT)
+    g = s.solve(s.prices(inst.lam0), 15, trace=True)
+    torch.cuda.synchronize()
+    ref = oracle.Oracle(inst).solve(iters=15, trace=True)
+    assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
+    assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
+    assert s.device_status() == 0
+    s.close()
