@@ -39,7 +39,8 @@ struct Plan {
     int tiles = 0;      // per cluster
     size_t col_len = 0; // floats per column
     int nblk = 0;       // workgroups per cluster
-    int nblk_res = 0;   // the same in resident launches (at most; see resident_shape)
+    int nblk_res = 0;   // the same in resident launches
+    bool res_streams = false;   // resident driver of a ragged table: the streaming kernel
     int aos_stride = 0; // floats per entry of the entry-major copy, 0 when there is none
     int64_t aos_lines = 0;  // kStoreLine-byte lines of one cluster's entry-major copy
     // workspace offsets (bytes)
@@ -165,6 +166,15 @@ esp_status make_plan(const esp_problem *p, const esp_options *opt, Plan *pl) {
     if (!pl->csr && !(opt && opt->blocks_per_cluster > 0)) {
         if (pl->tiles <= 2 * kResidentWaves) pl->nblk_res = 1;
         else pl->nblk_res = std::max(pl->nblk, std::min(std::max(1, cus / pl->B), max_useful));
+    }
+    // Ragged ones too, with two tiles per wavefront at most; a table that fits the
+    // plan's grid but not this one (clusters that do not divide the compute
+    // units) is streamed instead.
+    if (pl->csr) {
+        const int most = pl->tiles <= 2 * kResidentWaves ? 1 : std::max(1, cus / pl->B);
+        pl->nblk_res = std::min(pl->nblk, most);
+        pl->res_streams = pl->tiles > 2ll * kResidentWaves * pl->nblk_res;
+        if (pl->res_streams) pl->nblk_res = pl->nblk;
     }
     if (static_cast<int64_t>(pl->nblk) * pl->B > INT32_MAX) return ESP_ERR_SHAPE;
 
@@ -464,7 +474,7 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
             KArgs a = iteration_launch(i0, n);
             hipError_t e;
             if (resident) a.nblk = nblk_res;
-            if (resident)
+            if (resident && !c->pl.res_streams)
                 e = c->pl.csr ? launch_csr_resident(R, a, B, s) : launch_dense_resident(R, c->pl.lpj, a, B, s);
             else
                 e = c->pl.csr ? launch_csr_persistent(R, a, B, s) : launch_dense_persistent(R, c->pl.lpj, a, B, s);

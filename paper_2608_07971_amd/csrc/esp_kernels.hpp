@@ -1034,11 +1034,13 @@ __device__ __forceinline__ uint64_t wave_totals(const uint64_t (&x)[R]) {
     return v;
 }
 
-// Two wavefronts per SIMD at least (at most 256 registers): the CSR grid holds
-// two workgroups per CU, and a cooperative launch needs them all resident
-// (the persistent instances at R = 8 would otherwise take a few more).  The
-// resident instance keeps two tiles live through every iteration and runs
-// one workgroup per CU at most: it may use the whole register file.
+// Two wavefronts per SIMD (at most 256 registers): two workgroups of 4 wavefronts
+// per CU, all of them resident in a cooperative launch, or one of 8 where the
+// tiles stay in registers (an iteration there costs an exchange, cheaper among
+// half as many workgroups, and the latency of a wavefront's one or two tiles:
+// 100 ragged jobs x 8 3.3 -> 2.1 us, 60,000 x 4 4.1 -> 3.9, 200,000 x 5 x 3 4.6 -> 4.2).
+constexpr int csr_waves(int mode) { return mode == kResident ? kResidentWaves : kBlockWaves; }
+
 //
 // The scoring is 76 of a tile's VALU instructions (R = 6); who wins is worked
 // out on lane masks in scalar registers, which leaves about 170 of the 351 that
@@ -1054,12 +1056,13 @@ __device__ __forceinline__ uint64_t wave_totals(const uint64_t (&x)[R]) {
 // 63.0 us, three register sets instead of two 62.6 but 24.1 against 23.0 on
 // 262,144 jobs x 12 x 8.
 template <int R, typename A, int Mode, bool Direct>
-__global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_csr(KArgs a) {
+__global__ __launch_bounds__(csr_waves(Mode) * kWaveSize, 2) void k_csr(KArgs a) {
+    constexpr int Waves = csr_waves(Mode);
     constexpr int RS = Mode != kOnePass ? kResidentStep<R> : R;   // lane l accumulates resource l mod RS
     constexpr int Q = kWaveSize / RS;          // accumulating lanes per resource
-    __shared__ float s_stage[Direct ? 1 : kBlockWaves][Direct ? 1 : kTileEntries][R];
-    __shared__ u128 s_acc[kBlockThreads];
-    __shared__ u128 s_wsum[kBlockWaves][R];
+    __shared__ float s_stage[Direct ? 1 : Waves][Direct ? 1 : kTileEntries][R];
+    __shared__ u128 s_acc[Mode == kOnePass ? kBlockThreads : 1];
+    __shared__ u128 s_wsum[Waves][R];
     __shared__ u128 s_bsum[R];
     __shared__ double s_lam[R];
     __shared__ double s_newlam[R];
@@ -1097,7 +1100,7 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
         return wave_totals<R>(x);
     };
     const double sw = a.has_pen ? a.switch_cost[cl] : 0.0;
-    const int stride = a.nblk * kBlockWaves;
+    const int stride = a.nblk * Waves;
     const int last = a.tiles - 1;
     auto load_tile = [&](int t, int rev, f4 &u, f4 (&d)[R], f4 &pn, Heads &h) {
         const int tl = rev ? last - t : t;
@@ -1222,7 +1225,8 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
     f4 nu, npn = {}, bu, bpn = {};
     f4 nd[R], bd[R];
     Heads nhw = {}, bhw = {};
-    const int tile0 = blk * kBlockWaves + wave;
+    // (resident: the wavefronts that share a SIMD both have a tile only with more than 4 per workgroup)
+    const int tile0 = Mode == kResident ? wave * a.nblk + blk : blk * Waves + wave;
     Pending<R, A> pend;
     if constexpr (Mode == kOnePass) pending_loads<R, A>(a, cl, conv, pend);   // issued first: they return first
     load_tile(min(tile0, last), a.reverse, nu, nd, npn, nhw);   // in flight during a pending completion (clamped: no branch)
@@ -1262,7 +1266,7 @@ __global__ __launch_bounds__(kBlockThreads, Mode == kResident ? 1 : 2) void k_cs
         if (!ai.reduce) return;
         if constexpr (Mode != kOnePass) {
             if constexpr (Direct) acc = take_totals();
-            const bool go = resident_complete<R, kBlockWaves, Direct ? 8 : 0, A>(
+            const bool go = resident_complete<R, Waves, Direct ? 8 : 0, A>(
                 a, it, cl, blk, wave, lane, acc, etas[it], lam, rctx, xch, [&]() {
                     // (the last iteration's loads go unused)
                     if constexpr (Mode == kPersist) load_tile(min(tile0, last), rev ^ a.sweep_alt, nu, nd, npn, nhw);
@@ -1620,7 +1624,7 @@ hipError_t launch_csr_coop_r(const KArgs &a, int B, bool resident, hipStream_t s
     const void *f = a.acc128 ? csr_multi_kernel<R, u128, false>(resident)
                     : a.lane_f64 ? csr_multi_kernel<R, uint64_t, true>(resident)
                                  : csr_multi_kernel<R, uint64_t, false>(resident);
-    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s);
+    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s, resident ? kResidentThreads : kBlockThreads);
 }
 
 

@@ -275,3 +275,22 @@ def test_sums_at_the_accumulators_edges(n_jobs, log_jobs, need):
     assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
     assert s.device_status() == 0
     s.close()
+
+
+# Ragged tables around one workgroup's 16 tiles (36 families of 7 in a tile),
+# the most that 85 workgroups hold for each of 3 clusters (1,360 tiles; above,
+# the table is streamed), and more clusters than compute units.
+@pytest.mark.parametrize("clusters,n_jobs", [(1, 576), (1, 577), (3, 48960), (3, 48961), (3, 49000), (300, 40)])
+def test_ragged_resident_shapes(clusters, n_jobs):
+    inst = workloads.random_small(5, n_jobs, 7, 2, dense=True, n_clusters=clusters, iters=4)
+    print(f"[gpu-case] ragged resident B={clusters} N={n_jobs}", flush=True)
+    s = esp.Solver(inst, mode=esp.ESP_MODE_RESIDENT)
+    assert s.loop_driver() == esp.ESP_MODE_RESIDENT
+    g = s.solve(s.prices(inst.lam0), 4, trace=True, trace_choice=True)
+    torch.cuda.synchronize()
+    ref = oracle.Oracle(inst).solve(iters=4, trace=True, trace_choice=True)
+    assert np.array_equal(g["tr_choice"].cpu().numpy(), ref["tr_choice"])
+    assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
+    assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
+    assert s.device_status() == 0
+    s.close()
