@@ -887,7 +887,7 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
         const int64_t adds = 4 * std::max<int64_t>(2, (pl.tiles + waves - 1) / waves);
         int lg = 0;
         while ((static_cast<int64_t>(1) << lg) < adds) ++lg;
-        k.lane_f64 = (pl.csr && need_bits <= 63 && need_bits - lgN + lg <= 53) ? 1 : 0;
+        k.lane_f64 = (need_bits <= 63 && need_bits - lgN + lg <= 53) ? 1 : 0;
     }
     k.n_iters = 1;
     k.B = B;

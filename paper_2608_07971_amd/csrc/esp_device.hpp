@@ -75,6 +75,100 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // ---------------------------------------------------------------------------
+// Lane masks and segmented scans over the lanes of a wavefront
+// ---------------------------------------------------------------------------
+
+constexpr int kDppRowShr1 = 0x111;
+constexpr int kDppRowShr2 = 0x112;
+constexpr int kDppRowShr4 = 0x114;
+constexpr int kDppRowShr8 = 0x118;
+constexpr int kDppRowBcast15 = 0x142;
+constexpr int kDppRowBcast31 = 0x143;
+constexpr int kDppWaveShr1 = 0x138;
+
+// A lane move whose result is used only in lanes that have a source.
+template <int CTRL>
+__device__ __forceinline__ double dpp_any_d(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(static_cast<unsigned>(b)), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(static_cast<long long>(
+        (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)));
+}
+
+// Lanes of a wave-wide mask as a per-lane condition, and back.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ uint64_t mask_of(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+
+// acc plus the number of set bits of a wave-wide mask in the lanes below this one.
+__device__ __forceinline__ unsigned below_lane(uint64_t m, unsigned acc) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), acc));
+}
+
+// The lanes that take part in each step of a segmented inclusive scan over the
+// lanes whose segments start at the lanes of `starts`: those with no start
+// between the lane a value comes from (exclusive) and themselves.  A function
+// of the starts alone, in scalar registers.
+struct ScanLanes {
+    uint64_t row1, row2, row4, row8;                     // from 1, 2, 4, 8 lanes below in the row of 16
+    uint64_t rows, halves;                               // rows 1 and 3 from the row below, lanes 32..63 from lane 31
+};
+__device__ __forceinline__ ScanLanes scan_lanes(uint64_t starts) {
+    const uint64_t n1 = ~starts;                         // no start in this lane,
+    const uint64_t n2 = n1 & (n1 << 1);                  // nor in the one below,
+    const uint64_t n4 = n2 & (n2 << 2);                  // the last four lanes,
+    const uint64_t n8 = n4 & (n4 << 4);                  // eight (each limited to its row below)
+    // the lanes of rows 1 and 3 (of 32..63) before the first start there: the run
+    // of ones from the bottom, which adding one at the bottom clears
+    const uint64_t odd = n1 & 0xffff0000ffff0000ull;
+    const uint32_t up = static_cast<uint32_t>(n1 >> 32);
+    return {n1 & 0xfffefffefffefffeull, n2 & 0xfffcfffcfffcfffcull, n4 & 0xfff0fff0fff0fff0ull,
+            n8 & 0xff00ff00ff00ff00ull, odd & ~(odd + 0x0001000000010000ull),
+            static_cast<uint64_t>(up & ~(up + 1u)) << 32};
+}
+
+// A uniform 64-bit word of the tile metadata (never written on the device), as a scalar load.
+__device__ __forceinline__ uint64_t scalar_word(const void *p, int i) {
+    typedef const __attribute__((address_space(4))) uint64_t *Words;
+    return ((Words)(uintptr_t)p)[i];
+}
+
+// The sums of x[0..R-1] over the wavefront's lanes: lane l gets the sum of
+// x[l / 8] (0 past R).  Halving exchanges between the lane halves, row pairs
+// and row halves first, so that 7 + 3 additions do for 8 values.
+template <int R>
+__device__ __forceinline__ uint64_t wave_totals(const uint64_t (&x)[R]) {
+    auto word = [](uint64_t v, int i) { return static_cast<uint32_t>(v >> (32 * i)); };
+    auto pair32 = [&](uint64_t a, uint64_t b) {            // lanes 0..31: sum of a, 32..63: of b
+        const auto lo = __builtin_amdgcn_permlane32_swap(word(a, 0), word(b, 0), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(word(a, 1), word(b, 1), false, false);
+        return ((static_cast<uint64_t>(hi[0]) << 32) | lo[0]) + ((static_cast<uint64_t>(hi[1]) << 32) | lo[1]);
+    };
+    auto pair16 = [&](uint64_t a, uint64_t b) {            // even rows: sum of a, odd rows: of b
+        const auto lo = __builtin_amdgcn_permlane16_swap(word(a, 0), word(b, 0), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(word(a, 1), word(b, 1), false, false);
+        return ((static_cast<uint64_t>(hi[0]) << 32) | lo[0]) + ((static_cast<uint64_t>(hi[1]) << 32) | lo[1]);
+    };
+    uint64_t y[4], z[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = i < R ? pair32(x[i < R ? i : 0], i + 4 < R ? x[i + 4 < R ? i + 4 : 0] : 0) : 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) z[i] = i < R ? pair16(y[i], y[i + 2]) : 0;
+    const bool upper = (threadIdx.x & 8) != 0;
+    const uint64_t keep = upper ? z[1] : z[0], give = upper ? z[0] : z[1];
+    auto moved = [&](uint64_t v, auto &&move) {
+        return (static_cast<uint64_t>(static_cast<uint32_t>(move(static_cast<int>(word(v, 1))))) << 32) |
+               static_cast<uint32_t>(move(static_cast<int>(word(v, 0))));
+    };
+    uint64_t v = keep + moved(give, [](int w) { return dpp_i<0x128>(w); });      // row_ror:8
+    v += moved(v, [](int w) { return dpp_i<kDppXor1>(w); });
+    v += moved(v, [](int w) { return dpp_i<kDppXor2>(w); });
+    v += moved(v, [](int w) { return dpp_i<kDppHalfMirror>(w); });
+    return v;
+}
+
+// ---------------------------------------------------------------------------
 // Exact fixed-point demand accumulation
 // ---------------------------------------------------------------------------
 

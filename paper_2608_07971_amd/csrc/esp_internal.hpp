@@ -111,7 +111,7 @@ struct KArgs {
     int32_t reverse;               // sweep tiles back to front (iteration 0 of the launch)
     int32_t acc128;                // demand accumulators are 128-bit (else 64-bit)
     int32_t sum_f64;               // 64-bit, and a cluster's whole sum is exact in binary64
-    int32_t lane_f64;              // 64-bit, and a lane's sums of a CSR pass are exact in binary64
+    int32_t lane_f64;              // 64-bit, and a lane's sums of a pass are exact in binary64
     // Persistent launches run n_iters iterations; t, rows of the traces and the
     // per-iteration choice advance by B, B*R and B*N per iteration, and the
     // sweep direction alternates.

@@ -916,34 +916,6 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(KArgs a) {
 // CSR families (ragged sizes 1..256): whole families packed into tiles
 // ---------------------------------------------------------------------------
 
-constexpr int kDppRowShr1 = 0x111;
-constexpr int kDppRowShr2 = 0x112;
-constexpr int kDppRowShr4 = 0x114;
-constexpr int kDppRowShr8 = 0x118;
-constexpr int kDppRowBcast15 = 0x142;
-constexpr int kDppRowBcast31 = 0x143;
-constexpr int kDppWaveShr1 = 0x138;
-
-// A lane move whose result is used only in lanes that have a source.
-template <int CTRL>
-__device__ __forceinline__ double dpp_any_d(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(static_cast<unsigned>(b)), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double(static_cast<long long>(
-        (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)));
-}
-
-// Lanes of a wave-wide mask as a per-lane condition, and back.
-__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-__device__ __forceinline__ uint64_t mask_of(bool c) { return __builtin_amdgcn_ballot_w64(c); }
-
-// acc plus the number of set bits of a wave-wide mask in the lanes below this one.
-__device__ __forceinline__ unsigned below_lane(uint64_t m, unsigned acc) {
-    return __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32),
-                                     __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), acc));
-}
-
 // s = max(s, o) in the lanes of m (no NaN among the scores): one instruction
 // under EXEC, which is saved and restored.  The last two instructions are the
 // wait states a DPP read of s needs (not seen by the compiler behind assembly).
@@ -966,24 +938,14 @@ __device__ __forceinline__ void seg_scan_step(double &s, uint64_t m) {
     max_in_lanes(s, dpp_any_d<CTRL>(s), m);
 }
 
-// Segmented inclusive max-scan of s over the lanes, segments starting at the
-// lanes of `starts`.  Which lanes take part in a step follows from `starts`
-// alone, in scalar registers.
-__device__ __forceinline__ void seg_scan(double &s, uint64_t starts) {
-    const uint64_t n1 = ~starts;                         // no start in this lane,
-    const uint64_t n2 = n1 & (n1 << 1);                  // nor in the one below,
-    const uint64_t n4 = n2 & (n2 << 2);                  // the last four lanes,
-    const uint64_t n8 = n4 & (n4 << 4);                  // eight (each limited to its row of 16 below)
-    seg_scan_step<kDppRowShr1>(s, n1 & 0xfffefffefffefffeull);
-    seg_scan_step<kDppRowShr2>(s, n2 & 0xfffcfffcfffcfffcull);
-    seg_scan_step<kDppRowShr4>(s, n4 & 0xfff0fff0fff0fff0ull);
-    seg_scan_step<kDppRowShr8>(s, n8 & 0xff00ff00ff00ff00ull);
-    // rows 1 and 3 (then lanes 32..63): the lanes before the first start there, i.e.
-    // the run of ones from the bottom, which adding one at the bottom clears
-    const uint64_t odd = n1 & 0xffff0000ffff0000ull;
-    seg_scan_step<kDppRowBcast15>(s, odd & ~(odd + 0x0001000000010000ull));
-    const uint32_t up = static_cast<uint32_t>(n1 >> 32);
-    seg_scan_step<kDppRowBcast31>(s, static_cast<uint64_t>(up & ~(up + 1u)) << 32);
+// Segmented inclusive max-scan of s over the lanes.
+__device__ __forceinline__ void seg_scan(double &s, const ScanLanes &l) {
+    seg_scan_step<kDppRowShr1>(s, l.row1);
+    seg_scan_step<kDppRowShr2>(s, l.row2);
+    seg_scan_step<kDppRowShr4>(s, l.row4);
+    seg_scan_step<kDppRowShr8>(s, l.row8);
+    seg_scan_step<kDppRowBcast15>(s, l.rows);
+    seg_scan_step<kDppRowBcast31>(s, l.halves);
 }
 
 // The lanes of m whose next higher lane of m is in `next` (a subset of m).
@@ -992,46 +954,6 @@ __device__ __forceinline__ void seg_scan(double &s, uint64_t starts) {
 __device__ __forceinline__ uint64_t lanes_before(uint64_t m, uint64_t next) {
     const uint64_t rm = __builtin_bitreverse64(m), rn = __builtin_bitreverse64(next);
     return __builtin_bitreverse64((~rm + (rn << 1)) & rm);
-}
-
-// A uniform 64-bit word of the tile metadata (never written on the device), as a scalar load.
-__device__ __forceinline__ uint64_t scalar_word(const void *p, int i) {
-    typedef const __attribute__((address_space(4))) uint64_t *Words;
-    return ((Words)(uintptr_t)p)[i];
-}
-
-// The sums of x[0..R-1] over the wavefront's lanes: lane l gets the sum of
-// x[l / 8] (0 past R).  Halving exchanges between the lane halves, row pairs
-// and row halves first, so that 7 + 3 additions do for 8 values.
-template <int R>
-__device__ __forceinline__ uint64_t wave_totals(const uint64_t (&x)[R]) {
-    auto word = [](uint64_t v, int i) { return static_cast<uint32_t>(v >> (32 * i)); };
-    auto pair32 = [&](uint64_t a, uint64_t b) {            // lanes 0..31: sum of a, 32..63: of b
-        const auto lo = __builtin_amdgcn_permlane32_swap(word(a, 0), word(b, 0), false, false);
-        const auto hi = __builtin_amdgcn_permlane32_swap(word(a, 1), word(b, 1), false, false);
-        return ((static_cast<uint64_t>(hi[0]) << 32) | lo[0]) + ((static_cast<uint64_t>(hi[1]) << 32) | lo[1]);
-    };
-    auto pair16 = [&](uint64_t a, uint64_t b) {            // even rows: sum of a, odd rows: of b
-        const auto lo = __builtin_amdgcn_permlane16_swap(word(a, 0), word(b, 0), false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap(word(a, 1), word(b, 1), false, false);
-        return ((static_cast<uint64_t>(hi[0]) << 32) | lo[0]) + ((static_cast<uint64_t>(hi[1]) << 32) | lo[1]);
-    };
-    uint64_t y[4], z[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] = i < R ? pair32(x[i < R ? i : 0], i + 4 < R ? x[i + 4 < R ? i + 4 : 0] : 0) : 0;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) z[i] = i < R ? pair16(y[i], y[i + 2]) : 0;
-    const bool upper = (threadIdx.x & 8) != 0;
-    const uint64_t keep = upper ? z[1] : z[0], give = upper ? z[0] : z[1];
-    auto moved = [&](uint64_t v, auto &&move) {
-        return (static_cast<uint64_t>(static_cast<uint32_t>(move(static_cast<int>(word(v, 1))))) << 32) |
-               static_cast<uint32_t>(move(static_cast<int>(word(v, 0))));
-    };
-    uint64_t v = keep + moved(give, [](int w) { return dpp_i<0x128>(w); });      // row_ror:8
-    v += moved(v, [](int w) { return dpp_i<kDppXor1>(w); });
-    v += moved(v, [](int w) { return dpp_i<kDppXor2>(w); });
-    v += moved(v, [](int w) { return dpp_i<kDppHalfMirror>(w); });
-    return v;
 }
 
 // Two wavefronts per SIMD (at most 256 registers): two workgroups of 4 wavefronts
@@ -1161,7 +1083,7 @@ __global__ __launch_bounds__(csr_waves(Mode) * kWaveSize, 2) void k_csr(KArgs a)
         // Segment maxima across lanes: after the scan, top is the largest score
         // of the segment open at this lane's end, over its slots up to here.
         double top = run;
-        seg_scan(top, heads);
+        seg_scan(top, scan_lanes(heads));
         const double prev = dpp_any_d<kDppWaveShr1>(top);    // at the previous lane (a tile starts with a head)
         // The winner of a segment is its first slot with the segment's largest
         // score: in the lane where the running maximum last rose (a head, or a

@@ -213,3 +213,28 @@ def test_epochs_cold_and_warm_match_oracle():
         assert np.array_equal(gw["choice"].cpu().numpy(), rw["choice"])
         lam_w_ref = rw["lam"].copy()
     assert a.device_status() == 0
+
+
+# One lane per segment end: families of one entry, at the edges of tiles and
+# lanes, and over many lanes; few and many tiles; sums that a lane holds in
+# binary64 (22 bits) or in 64-bit fixed point (52); masked configurations.
+@pytest.mark.parametrize("k,n_jobs,clusters,dense", [
+    (1, 1, 1, True), (1, 3000, 2, True), (2, 129, 1, True), (3, 2000, 1, True), (5, 51, 3, True), (7, 9000, 1, True),
+    (255, 40, 1, True), (256, 33, 1, True), (30, 1500, 2, False), (256, 700, 1, False), (4, 2047, 1, True),
+    (8, 31, 2, True), (16, 17, 1, True), (32, 1001, 1, True), (64, 5, 1, True)])
+@pytest.mark.parametrize("bits", [22, 52])
+def test_reserve_edges(k, n_jobs, clusters, dense, bits):
+    R = 1 + (k + n_jobs) % 8
+    queue = workloads.random_small(k + n_jobs, n_jobs, k, R, dense=dense, n_clusters=clusters)
+    d = np.floor(queue.demand.astype(np.float64) * 2.0 ** 20) / 2.0 ** 20
+    small = np.random.default_rng(k).random(d.shape) < 0.5
+    queue.demand = np.where(small, d * 2.0 ** (22 - bits), d).astype(np.float32)
+    _with_mask(queue, 5)
+    active = workloads.random_small(1, 20, 4, R, n_clusters=clusters)
+    a, q = esp.Solver(active), esp.Solver(queue)
+    for pend in (None, _pending(queue, 6), np.zeros((clusters, n_jobs), np.uint8)):
+        _say(f"reserve k={k} N={n_jobs} B={clusters} bits={bits} pending={'all' if pend is None else int(pend.sum())}")
+        _check(a, q, active.capacity, queue, 0.5, pend)
+    assert q.device_status() == 0
+    a.close()
+    q.close()
