@@ -134,8 +134,8 @@ def _check(code: int, where: str) -> None:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:                  # the handle alone: no Stream object per call
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 

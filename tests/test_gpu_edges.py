@@ -160,3 +160,11 @@ def test_score_select_checks_prices_per_cluster():
         for b in range(5):
             assert np.array_equal(ch[b].cpu().numpy(), o.select(b, lam[b]))
         s.close()
+
+
+def test_default_stream_is_the_callers():
+    side = torch.cuda.Stream()
+    assert esp._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert esp._stream(None) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+    assert esp._stream(side) == side.cuda_stream
