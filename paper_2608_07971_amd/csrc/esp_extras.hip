@@ -148,7 +148,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_reserve(KArgs a, ReserveArgs 
 // workgroup halve the tiles of each.  Measured, a call, against minima merged by
 // LDS atomics in 4 wavefronts: 131,072 ragged jobs x 6 (46 MB) 23.5 -> 20.2 us,
 // 20,000 x 64 x 8 25.6 -> 18.7, 500,000 x 4 x 3 19.3 -> 16.1; about 9 us are the
-// launch and the sums' way through memory.
+// launch and the sums' way through memory.  A table that a pass over another one
+// has put out of the caches takes 23.4 us either way (23.6 before): memory.
 __device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 template <int CTRL, int R>

@@ -965,7 +965,7 @@ constexpr int csr_waves(int mode) { return mode == kResident ? kResidentWaves : 
 
 //
 // The scoring is 76 of a tile's VALU instructions (R = 6); who wins is worked
-// out on lane masks in scalar registers, which leaves about 170 of the 351 that
+// out on lane masks in scalar registers, which leaves about 190 of the 351 that
 // per-lane flags, indices and staged winners took.  A pass over a small table
 // is bound by its tiles' latency, over a large one by memory.
 //
