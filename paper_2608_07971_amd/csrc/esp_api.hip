@@ -40,7 +40,7 @@ struct Plan {
     size_t col_len = 0; // floats per column
     int nblk = 0;       // workgroups per cluster
     int nblk_res = 0;   // the same in resident launches
-    bool res_streams = false;   // resident driver of a ragged table: the streaming kernel
+    bool res_lds = false;   // resident launches may keep tiles in LDS
     int aos_stride = 0; // floats per entry of the entry-major copy, 0 when there is none
     int64_t aos_lines = 0;  // kStoreLine-byte lines of one cluster's entry-major copy
     // workspace offsets (bytes)
@@ -155,27 +155,26 @@ esp_status make_plan(const esp_problem *p, const esp_options *opt, Plan *pl) {
     int nblk = (opt && opt->blocks_per_cluster > 0) ? opt->blocks_per_cluster
                                                      : std::max(1, (total + pl->B - 1) / pl->B);
     pl->nblk = std::min(nblk, max_useful);
-    // Resident launches of dense tables read no table in their loop: they use
-    // every compute unit (fewer tiles per wavefront), one workgroup on each.
+    // Resident launches read no table in their loop: dense ones use every
+    // compute unit (fewer tiles per wavefront).  A workgroup of 8 wavefronts
+    // fills a compute unit's registers, so the clusters share one workgroup per
+    // unit: the device refuses a grid beyond that (90 clusters x 3 workgroups,
+    // 150 x 2), and one launch per iteration would remain (50 iterations of 90
+    // clusters of 20 tiles x 4 resources 370 us against 180 on 2 workgroups each,
+    // 150 of 33 tiles 517 against 179 on one).
     // A table whose tiles fit one workgroup's registers stays in one: the
     // exchange between workgroups costs more than the tiles (64 jobs x 64 x 8,
     // 16 tiles: 2.6 us an iteration against 3.0 on four workgroups, and no
     // cooperative launch, 28 against 46 us for a one-iteration solve; at 25
-    // tiles 3.9 against 3.2).
-    pl->nblk_res = pl->nblk;
-    if (!pl->csr && !(opt && opt->blocks_per_cluster > 0)) {
-        if (pl->tiles <= 2 * kResidentWaves) pl->nblk_res = 1;
-        else pl->nblk_res = std::max(pl->nblk, std::min(std::max(1, cus / pl->B), max_useful));
-    }
-    // Ragged ones too, with two tiles per wavefront at most; a table that fits the
-    // plan's grid but not this one (clusters that do not divide the compute
-    // units) is streamed instead.
-    if (pl->csr) {
-        const int most = pl->tiles <= 2 * kResidentWaves ? 1 : std::max(1, cus / pl->B);
-        pl->nblk_res = std::min(pl->nblk, most);
-        pl->res_streams = pl->tiles > 2ll * kResidentWaves * pl->nblk_res;
-        if (pl->res_streams) pl->nblk_res = pl->nblk;
-    }
+    // tiles 3.9 against 3.2).  A caller's grid beyond one workgroup per unit is
+    // cut down only where the registers then still hold the table: with tiles
+    // in LDS as well, that would be fewer and busier workgroups than asked for.
+    const int per_unit = std::max(1, cus / pl->B);
+    const bool callers = opt && opt->blocks_per_cluster > 0;
+    if (pl->csr) pl->nblk_res = std::min(pl->nblk, pl->tiles <= 2 * kResidentWaves ? 1 : per_unit);
+    else if (callers) pl->nblk_res = std::min(pl->nblk, per_unit);
+    else pl->nblk_res = pl->tiles <= 2 * kResidentWaves ? 1 : std::min(per_unit, max_useful);
+    pl->res_lds = !pl->csr && !(callers && pl->nblk > per_unit);
     if (static_cast<int64_t>(pl->nblk) * pl->B > INT32_MAX) return ESP_ERR_SHAPE;
 
     const size_t B = pl->B, R = pl->R;
@@ -305,7 +304,7 @@ struct esp_ctx {
     bool auto_mode = false;            // the caller asked for ESP_MODE_AUTO
     bool fell_back = false;            // AUTO: the device refused a co-resident grid
     bool resident_ok = false;          // the table fits ESP_MODE_RESIDENT
-    bool on_chip = false;              // persistent solves of AUTO keep the tiles on chip
+    bool on_chip = false;              // resident launches: the tiles stay on chip
     std::vector<int64_t> off;          // family offsets (host copy)
     std::vector<int64_t> slot_of;      // first table slot of each family
     KArgs base{};
@@ -409,7 +408,7 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
     // each launch then completes all of its iterations itself.
     bool persistent =
         !capturing && !c->fell_back && (c->mode != ESP_MODE_STREAM || (c->auto_mode && tol > 0.0));
-    bool resident = persistent && (c->mode == ESP_MODE_RESIDENT || (c->auto_mode && c->on_chip));
+    bool resident = persistent && c->on_chip && (c->mode == ESP_MODE_RESIDENT || c->auto_mode);
     const int nblk_res = c->pl.nblk_res;
     {
         // validates the prices, turns -0.0 into +0.0 in place, resets the
@@ -474,7 +473,7 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
             KArgs a = iteration_launch(i0, n);
             hipError_t e;
             if (resident) a.nblk = nblk_res;
-            if (resident && !c->pl.res_streams)
+            if (resident)
                 e = c->pl.csr ? launch_csr_resident(R, a, B, s) : launch_dense_resident(R, c->pl.lpj, a, B, s);
             else
                 e = c->pl.csr ? launch_csr_persistent(R, a, B, s) : launch_dense_persistent(R, c->pl.lpj, a, B, s);
@@ -620,23 +619,27 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
             shift[static_cast<size_t>(b) * R + r] = lo;
         }
 
-    // Resident launches.  ESP_MODE_RESIDENT takes tables of at most two tiles
+    // Resident launches.  ESP_MODE_RESIDENT accepts tables of at most two tiles
     // per wavefront of the plan's grid, and of at most 32 workgroups per group
-    // of 64 / (R limbs) lanes of 48-bit limbs: resident_ok.  AUTO also keeps
-    // larger dense tables on chip, with lds_tiles per wavefront in LDS:
-    // on_chip.  (The exchange's count fields hold up to 255 workgroups a copy.)
+    // of 64 / (R limbs) lanes of 48-bit limbs: resident_ok (the limits of the
+    // interface, not of the exchange, whose count fields hold 255 workgroups a
+    // copy).  The tiles stay on chip when the resident grid's registers hold
+    // them, two per wavefront, and for dense tables also with lds_tiles more per
+    // wavefront in LDS: on_chip.  Accepted tables that do not (ragged ones of
+    // clusters that do not divide the compute units, a caller's grid cut down)
+    // are streamed by the persistent kernel.
     int limbs = std::max(1, (need_bits + 47) / 48);
     const int groups = kWaveSize / (R * limbs);
     const bool resident_ok = static_cast<int64_t>(pl.tiles) <= 2ll * pl.nblk * kBlockWaves &&
                              (pl.nblk == 1 || (groups >= 1 && pl.nblk <= 32 * groups && pl.nblk <= 4 * 255));
     limbs = need_bits <= kCountShift ? 1 : (need_bits + kLimbBits - 1) / kLimbBits;   // as exchanged
+    const int64_t res_waves = static_cast<int64_t>(pl.nblk_res) * kResidentWaves;
     int lds_tiles = 0;
-    bool on_chip = resident_ok;
-    if (!pl.csr) {
-        const int64_t waves = static_cast<int64_t>(pl.nblk_res) * kResidentWaves;
-        const int64_t per_wave = (pl.tiles + waves - 1) / waves;
-        lds_tiles = static_cast<int>(std::max<int64_t>(0, std::min<int64_t>(per_wave, 1 << 20) - 2));
-        on_chip = pl.nblk_res <= 4 * 255 && resident_lds(static_cast<int>(pl.columns()), lds_tiles) <= resident_lds_limit(R, pl.lpj);
+    bool on_chip = pl.tiles <= 2 * res_waves && (resident_ok || !pl.csr);
+    if (!on_chip && pl.res_lds) {
+        const int64_t per_wave = (pl.tiles + res_waves - 1) / res_waves;
+        lds_tiles = static_cast<int>(std::min<int64_t>(per_wave, 1 << 20) - 2);
+        on_chip = resident_lds(static_cast<int>(pl.columns()), lds_tiles) <= resident_lds_limit(R, pl.lpj);
     }
     if (options && options->mode == ESP_MODE_RESIDENT && !resident_ok) return ESP_ERR_SHAPE;
 

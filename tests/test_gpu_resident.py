@@ -294,3 +294,43 @@ def test_ragged_resident_shapes(clusters, n_jobs):
     assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
     assert s.device_status() == 0
     s.close()
+
+
+# Clusters whose planned workgroups (192 over the clusters, rounded up) are more
+# than one for each of 256 compute units: 86..95 x 3 and 129..191 x 2.  Tables of 20
+# tiles per cluster, of 33 and 60 (LDS tiles, or more than fit), and a tolerance.
+@pytest.mark.parametrize("clusters", [86, 90, 95, 129, 150, 191])
+@pytest.mark.parametrize("tiles,r", [(20, 4), (33, 6), (60, 2), (60, 6)])
+def test_dense_batches_keep_their_driver(clusters, tiles, r):
+    inst = _dense(clusters + tiles, tiles * 8 - 3, 32, r, n_clusters=clusters)
+    _say(f"dense batch B={clusters} tiles={tiles} R={r}")
+    for tol in (0.0, 1e-3):
+        s = esp.Solver(inst)
+        g = s.solve(s.prices(inst.lam0), 5, tol=tol, trace=True)
+        torch.cuda.synchronize()
+        assert s.device_status() == 0
+        assert s.loop_driver() != esp.ESP_MODE_STREAM              # no grid was refused
+        ref = oracle.Oracle(inst).solve(iters=5, tol=tol)
+        assert np.array_equal(g["iters_done"].cpu().numpy(), ref["iters_done"])
+        assert np.array_equal(g["lam"].cpu().numpy(), ref["lam"])
+        assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
+        s.close()
+
+
+# Grids of more than one workgroup per compute unit that ESP_MODE_RESIDENT
+# accepts: the plan's own (90 x 3) and a caller's (one cluster on 400 workgroups,
+# 40 on 8, 3 on 170 with tables that fewer workgroups hold, 130 on 3 with one that they do not).
+@pytest.mark.parametrize("clusters,tiles,r,blocks", [
+    (90, 20, 4, 0), (95, 24, 2, 0), (1, 2001, 2, 400), (40, 50, 3, 8), (3, 1350, 2, 170), (130, 24, 4, 3)])
+def test_explicit_resident_grids_beyond_the_device(clusters, tiles, r, blocks):
+    inst = _dense(tiles, tiles * 8 - 5, 32, r, n_clusters=clusters)
+    _say(f"explicit resident B={clusters} tiles={tiles} R={r} blocks={blocks}")
+    s = esp.Solver(inst, mode=esp.ESP_MODE_RESIDENT, blocks_per_cluster=blocks)
+    g = s.solve(s.prices(inst.lam0), 4, trace=True)
+    torch.cuda.synchronize()
+    assert s.device_status() == 0
+    ref = oracle.Oracle(inst).solve(iters=4, trace=True)
+    assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
+    assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
+    assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
+    s.close()
