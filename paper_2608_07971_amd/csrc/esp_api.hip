@@ -443,7 +443,7 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
             }
         } else {
             base.lam_out = prices;
-            base.skip_mask = kFlagError | kFlagStopped | kFlagFrozen;
+            base.skip_mask = kFlagError | kFlagStopped | kFlagFrozen | kFlagAborted;
         }
         if (resident) base.sweep_alt = 0;      // a wavefront keeps the same tiles
     };

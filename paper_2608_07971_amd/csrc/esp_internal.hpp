@@ -52,6 +52,7 @@ constexpr size_t resident_lds_limit(int R, int lpj) {
 constexpr int kFlagStopped = 1;                     // converged under tol: skip further updates
 constexpr int kFlagError = 2;                       // invalid prices: skip everything
 constexpr int kFlagFrozen = 8;                      // outer rounds: the cluster's schedule is final
+constexpr int kFlagAborted = 16;                    // an exchange of the solve timed out: no further iterations
 
 // Device status codes (mirror esp_status values).
 constexpr int kStatusNonfinite = 3;

@@ -390,9 +390,11 @@ __device__ __forceinline__ ResidentCtx resident_ctx(const KArgs &a, int cl, int 
 }
 
 // The exchange of iteration m: this lane's word `v` (lanes below xch.words)
-// becomes the cluster's total.  Returns false when another workgroup has
-// recorded an error, or after about 2 s.
-__device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &xch, int m, int lane, uint64_t &v) {
+// becomes the cluster's total.  Returns false after about 2 s, or when another
+// workgroup of the cluster has given up (kFlagAborted, cleared by the solve's
+// prologue).  Nothing else ends a wait: the status word is shared by all clusters
+// and may still hold an error of another cluster or of an earlier call.
+__device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &xch, int cl, int m, int lane, uint64_t &v) {
     constexpr uint64_t kOne = 1ull << kCountShift, kLow = kOne - 1;
     const int par = m & 1;
     const uint64_t tag = static_cast<uint64_t>(m % 255 + 1) << kCountShift;
@@ -423,9 +425,13 @@ __device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &x
             v = x & kLow;
             return true;
         }
-        if ((tries & 63) == 0 && (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                                  __builtin_amdgcn_s_memrealtime() - t0 > 200000000ull)) {
-            if (lane == 0) atomicCAS(a.status, 0, kStatusTimeout);
+        if ((tries & 63) == 0 &&
+            ((__hip_atomic_load(&a.flags[cl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFlagAborted) != 0 ||
+             __builtin_amdgcn_s_memrealtime() - t0 > 200000000ull)) {
+            if (lane == 0) {
+                atomicOr(&a.flags[cl], kFlagAborted);
+                atomicCAS(a.status, 0, kStatusTimeout);
+            }
             return false;
         }
     }
@@ -476,7 +482,7 @@ __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl
             uint64_t v = fx_words(tot, ctx.shift);
             if constexpr (!std::is_floating_point_v<A>) if (xch.words > R)
                 v = static_cast<uint64_t>(static_cast<u128>(tot) >> (kLimbBits * (lane < xch.words ? lane / R : 0))) & kLimbMask;
-            go = exchange_total(a, xch, a.iter_no + it, lane, v);
+            go = exchange_total(a, xch, cl, a.iter_no + it, lane, v);
             if constexpr (std::is_floating_point_v<A>) {
                 tot = fx_to_double(v, ctx.shift);
             } else if (xch.words == R) {

@@ -4,6 +4,8 @@ with several workgroups per cluster their exact sums travel as tagged
 48-bit limbs.  Every iterate against the free-running oracle (bitwise), over
 one and many workgroups, dense and CSR tables, one to three limbs, several
 clusters, penalties, staggered stops, and solves longer than one launch."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -333,4 +335,60 @@ def test_explicit_resident_grids_beyond_the_device(clusters, tiles, r, blocks):
     assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
     assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
     assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
+    s.close()
+
+
+def _one_packing_per_unit():
+    """A solver of 250 equal clusters and a model whose packing takes a compute
+    unit each for some hundred microseconds."""
+    one = workloads.make("small", n_jobs=1000)
+    rep = {k: np.repeat(getattr(one, k), 250, axis=0) for k in ("utility", "demand", "capacity", "eta0", "lam0")}
+    many = workloads.with_penalties(dataclasses.replace(one, **rep), 3)
+    model = workloads.iac_model(many, gpus=[2048] * 250)
+    for k in ("sensitivity", "pressure", "tau_base"):
+        setattr(model, k, torch.as_tensor(getattr(model, k), device="cuda"))
+    return esp.Solver(many), model
+
+
+@pytest.mark.parametrize("case", ["resident", "on_chip", "csr", "persistent", "persistent_csr"])
+@pytest.mark.parametrize("error", ["bad_price", "earlier_call"])
+def test_waits_outlast_errors_of_others(case, error):
+    """A bad price in another cluster, or an error of an earlier call that nobody
+    has read, does not end the solve of a healthy cluster, however long its
+    workgroups wait for each other: here for the last of them to get a compute
+    unit, which first-fit packings on another stream hold."""
+    if case.endswith("csr"):
+        inst = workloads.random_small(50, 3000, 40, 4, n_clusters=3, iters=30)
+    else:
+        inst = _dense(51, 2500 if case == "on_chip" else 600, 32, 4, n_clusters=3)
+    T = 30
+    mode = esp.ESP_MODE_AUTO if case == "on_chip" else esp.ESP_MODE_PERSISTENT if case.startswith("p") else esp.ESP_MODE_RESIDENT
+    _say(f"waits outlast errors: {case} {error}")
+    s = esp.Solver(inst, mode=mode)
+    lam0 = np.array(inst.lam0, dtype=np.float64).reshape(3, 4).copy()
+    if error == "bad_price":
+        lam0[1, 2] = np.nan
+    else:
+        s.reduce_demand(torch.full((3, inst.N), 1000, dtype=torch.int32, device="cuda"))
+    healthy = [0, 2] if error == "bad_price" else [0, 1, 2]
+    ref = oracle.Oracle(inst).solve(iters=T)
+    busy, model = _one_packing_per_unit()
+    side = torch.cuda.Stream()
+    lam = s.prices(lam0)
+    blam = busy.prices(np.zeros((busy.B, busy.R)))
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(4):
+        # (one round without iterations: returns while the packing runs)
+        busy.schedule(model, blam, 1, 0, stream=side)
+        lam.copy_(torch.as_tensor(lam0))
+        got.append({k: v.clone() for k, v in s.solve(lam, T).items()})
+        torch.cuda.synchronize()
+    busy.close()
+    assert s.device_status() == (esp.ESP_ERR_NONFINITE if error == "bad_price" else esp.ESP_ERR_INVALID_ARG)
+    for g in got:
+        for b in healthy:
+            assert g["iters_done"].cpu().numpy()[b] == T, b
+            assert np.array_equal(g["lam"].cpu().numpy()[b], ref["lam"][b]), b
+            assert np.array_equal(g["choice"].cpu().numpy()[b], ref["choice"][b]), b
     s.close()
