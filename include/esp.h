@@ -64,11 +64,9 @@ enum { ESP_STEP_CONST = 0, ESP_STEP_INV_SQRT = 1 };
 
 /* Loop drivers of esp_solve (results are identical in every mode). */
 enum {
-    ESP_MODE_AUTO = 0,        /* resident (below) when the table fits; else persistent for
+    ESP_MODE_AUTO = 0,        /* resident (below) when the table fits on chip; else persistent for
                                  short passes (packed table of at most
-                                 ESP_AUTO_PERSISTENT_BYTES), where launch latency would dominate
-                                 (a dense table that fits the registers and LDS of the device
-                                 stays there for the launch),
+                                 ESP_AUTO_PERSISTENT_BYTES), where launch latency would dominate,
                                  and for solves with tol > 0 (the loop ends on the device once
                                  every cluster has converged); one launch per iteration
                                  otherwise, where the two drivers run within 3%; falls
@@ -79,14 +77,21 @@ enum {
                                  from memory every iteration; the workgroups of a cluster
                                  exchange their exact sums through counted words after each
                                  iteration (ESP_ERR_DEVICE when the grid cannot be co-resident) */
-    ESP_MODE_RESIDENT = 3     /* one launch runs all iterations over tiles held in registers
-                                 (every wavefront of the grid holds at most two 256-entry tiles:
-                                 tables of up to about 2,000 tiles per cluster); each iteration
-                                 is completed inside the launch, the workgroups of a cluster
-                                 exchanging their exact sums through counted words (cooperative
-                                 launch; ESP_ERR_DEVICE when the grid cannot be co-resident).
-                                 esp_create returns ESP_ERR_SHAPE when the table does not fit.
-                                 ESP_MODE_AUTO takes this driver whenever the table fits. */
+    ESP_MODE_RESIDENT = 3     /* one launch runs all iterations over tiles kept on chip for the
+                                 launch; each iteration is completed inside the launch, the
+                                 workgroups of a cluster exchanging their exact sums through
+                                 counted words (cooperative launch with several workgroups per
+                                 cluster).  Asked for explicitly: tables of at most 8 tiles of 256
+                                 entries per planned workgroup (by default up to about 1,500 dense
+                                 and 4,000 ragged tiles in all; fewer ragged ones with many
+                                 resources or wide sums), held in registers;
+                                 esp_create returns ESP_ERR_SHAPE for others.  The few accepted
+                                 tables that the device's registers do not hold (clusters that do
+                                 not divide the compute units, a caller's blocks_per_cluster
+                                 beyond one workgroup per unit) are streamed as by
+                                 ESP_MODE_PERSISTENT.  ESP_MODE_AUTO takes this driver for the
+                                 same tables, and for dense tables that fit the registers and
+                                 the LDS together (up to 8,192 tiles at R = 8). */
 };
 
 #define ESP_AUTO_PERSISTENT_BYTES (256u << 20)   /* what the memory-side cache holds */
@@ -415,10 +420,11 @@ esp_status esp_nearest_profile(esp_ctx *store, int32_t num_queries, const int32_
                                int32_t *nearest, float *estimate, void *stream);
 
 /*
- * esp_loop_driver: the loop driver esp_solve uses for this context's solves
- * with tol = 0, ESP_MODE_STREAM, ESP_MODE_PERSISTENT or ESP_MODE_RESIDENT
- * (ESP_MODE_AUTO resolved against the table size, and against the device
- * once a solve has run).  Host-only.
+ * esp_loop_driver: the loop driver esp_solve launches for this context's
+ * solves with tol = 0 outside graph capture, ESP_MODE_STREAM,
+ * ESP_MODE_PERSISTENT or ESP_MODE_RESIDENT (ESP_MODE_AUTO resolved against the
+ * table size, and against the device once a solve has run; PERSISTENT for an
+ * ESP_MODE_RESIDENT context whose table is streamed).  Host-only.
  * Errors: ESP_ERR_STATE (NULL context), ESP_ERR_INVALID_ARG (mode NULL).
  */
 esp_status esp_loop_driver(const esp_ctx *ctx, int32_t *mode);

@@ -303,7 +303,6 @@ struct esp_ctx {
     int mode = ESP_MODE_AUTO;
     bool auto_mode = false;            // the caller asked for ESP_MODE_AUTO
     bool fell_back = false;            // AUTO: the device refused a co-resident grid
-    bool resident_ok = false;          // the table fits ESP_MODE_RESIDENT
     bool on_chip = false;              // resident launches: the tiles stay on chip
     std::vector<int64_t> off;          // family offsets (host copy)
     std::vector<int64_t> slot_of;      // first table slot of each family
@@ -901,7 +900,6 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     k.limbs = limbs;
     k.xch_clear = 0;
     k.lds_tiles = on_chip ? lds_tiles : 0;
-    c->resident_ok = resident_ok;
     c->on_chip = on_chip;
     *out = c;
     return ESP_OK;
@@ -1190,7 +1188,7 @@ esp_status esp_loop_driver(const esp_ctx *c, int32_t *mode) {
     if (st != ESP_OK) return st;
     if (mode == nullptr) return ESP_ERR_INVALID_ARG;
     if (c->mode == ESP_MODE_STREAM || c->fell_back) *mode = ESP_MODE_STREAM;
-    else if (c->mode == ESP_MODE_RESIDENT || (c->auto_mode && c->resident_ok)) *mode = ESP_MODE_RESIDENT;
+    else if (c->on_chip && (c->mode == ESP_MODE_RESIDENT || c->auto_mode)) *mode = ESP_MODE_RESIDENT;
     else *mode = ESP_MODE_PERSISTENT;
     return ESP_OK;
 }

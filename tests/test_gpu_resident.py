@@ -77,9 +77,12 @@ def test_auto_takes_the_resident_driver_for_small_tables():
         s = esp.Solver(inst)
         assert s.loop_driver() == esp.ESP_MODE_RESIDENT, name
         s.close()
-    s = esp.Solver(workloads.make("large", n_jobs=20000))          # 46 MB, 5,000 tiles
-    assert s.loop_driver() == esp.ESP_MODE_PERSISTENT
-    s.close()
+    # 256 workgroups of 32 tiles at R = 8: 8,192 tiles of 4 jobs
+    for n_jobs, want in ((20000, esp.ESP_MODE_RESIDENT), (32768, esp.ESP_MODE_RESIDENT),
+                         (32769, esp.ESP_MODE_PERSISTENT)):
+        s = esp.Solver(workloads.make("large", n_jobs=n_jobs))
+        assert s.loop_driver() == want, n_jobs
+        s.close()
 
 
 def _staggered():
@@ -167,7 +170,7 @@ def _dense(seed, n_jobs, k, r, **kw):
 # AUTO keeps dense tables beyond two tiles per wavefront on chip (8 wavefronts
 # per workgroup: 16 tiles in registers, the rest in LDS): tables around those
 # sizes and around the LDS limit (at R = 8: 32 tiles per workgroup, 33 are
-# streamed), last tiles partial, one to three limbs, 1 to 17 workgroups (the
+# streamed; with a penalty column 24 and 25), last tiles partial, one to three limbs, 1 to 17 workgroups (the
 # exchange's 16 copies) and the whole device.
 ON_CHIP = {
     # name: (instance, blocks_per_cluster (0 = library default), T)
@@ -184,7 +187,8 @@ ON_CHIP = {
     "k32_r6_17wg": (lambda: _dense(11, 2611, 32, 6), 17, 40),
     "k32_r3_3clusters": (lambda: _dense(12, 900, 32, 3, n_clusters=3), 4, 40),
     "k8_r2_penalties": (lambda: workloads.with_penalties(_dense(13, 1500, 8, 2), 9), 2, 40),
-    "k64_r8_penalties_1wg": (lambda: workloads.with_penalties(_dense(14, 100, 64, 8), 9), 1, 40),
+    "k64_r8_penalties_24tiles_1wg": (lambda: workloads.with_penalties(_dense(14, 95, 64, 8), 9), 1, 40),
+    "k64_r8_penalties_25tiles_1wg": (lambda: workloads.with_penalties(_dense(14, 100, 64, 8), 9), 1, 40),
     "k64_r8_9000jobs": (lambda: workloads.make("large", n_jobs=9000), 0, 12),
     "300clusters": (lambda: _dense(15, 65, 64, 4, n_clusters=300), 0, 8),
 }
@@ -207,6 +211,8 @@ def test_auto_keeps_tables_on_chip(name):
         assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
         assert np.array_equal(g["U"].cpu().numpy(), ref["U"])
         assert (g["iters_done"].cpu().numpy() == T).all()
+    streamed = name in ("k64_r8_33tiles_1wg", "k64_r8_penalties_25tiles_1wg")
+    assert s.loop_driver() == (esp.ESP_MODE_PERSISTENT if streamed else esp.ESP_MODE_RESIDENT)
     s.close()
 
 
@@ -287,7 +293,8 @@ def test_ragged_resident_shapes(clusters, n_jobs):
     inst = workloads.random_small(5, n_jobs, 7, 2, dense=True, n_clusters=clusters, iters=4)
     print(f"[gpu-case] ragged resident B={clusters} N={n_jobs}", flush=True)
     s = esp.Solver(inst, mode=esp.ESP_MODE_RESIDENT)
-    assert s.loop_driver() == esp.ESP_MODE_RESIDENT
+    streamed = clusters == 3 and n_jobs > 48960
+    assert s.loop_driver() == (esp.ESP_MODE_PERSISTENT if streamed else esp.ESP_MODE_RESIDENT)
     g = s.solve(s.prices(inst.lam0), 4, trace=True, trace_choice=True)
     torch.cuda.synchronize()
     ref = oracle.Oracle(inst).solve(iters=4, trace=True, trace_choice=True)
@@ -311,7 +318,10 @@ def test_dense_batches_keep_their_driver(clusters, tiles, r):
         g = s.solve(s.prices(inst.lam0), 5, tol=tol, trace=True)
         torch.cuda.synchronize()
         assert s.device_status() == 0
-        assert s.loop_driver() != esp.ESP_MODE_STREAM              # no grid was refused
+        # no grid was refused: 256 / clusters workgroups of 8 wavefronts hold the table (two tiles of a
+        # wavefront in registers, and in LDS 160 KB / 8 / (R + 1) KB = 6, 3 or 2), or it is streamed
+        fits = -(-tiles // (8 * (256 // clusters))) - 2 <= {2: 6, 4: 3, 6: 2}[r]
+        assert s.loop_driver() == (esp.ESP_MODE_RESIDENT if fits else esp.ESP_MODE_PERSISTENT)
         ref = oracle.Oracle(inst).solve(iters=5, tol=tol)
         assert np.array_equal(g["iters_done"].cpu().numpy(), ref["iters_done"])
         assert np.array_equal(g["lam"].cpu().numpy(), ref["lam"])
@@ -331,6 +341,7 @@ def test_explicit_resident_grids_beyond_the_device(clusters, tiles, r, blocks):
     g = s.solve(s.prices(inst.lam0), 4, trace=True)
     torch.cuda.synchronize()
     assert s.device_status() == 0
+    assert s.loop_driver() == (esp.ESP_MODE_PERSISTENT if clusters == 130 else esp.ESP_MODE_RESIDENT)
     ref = oracle.Oracle(inst).solve(iters=4, trace=True)
     assert np.array_equal(g["tr_lam"].cpu().numpy(), ref["tr_lam"])
     assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
