@@ -69,7 +69,10 @@ enum {
                                  ESP_AUTO_PERSISTENT_BYTES), where launch latency would dominate,
                                  and for solves with tol > 0 (the loop ends on the device once
                                  every cluster has converged); one launch per iteration
-                                 otherwise, where the two drivers run within 3%; falls
+                                 otherwise, where the two drivers run within 3%, and for solves
+                                 with tol = 0 of few iterations on tables above 64 MiB (fewer
+                                 than 5 on chip, 9 of a streamed ragged table, 16 of a dense
+                                 one), which a cooperative launch would make longer; falls
                                  back to one launch per iteration when the device cannot hold
                                  the grid co-resident */
     ESP_MODE_STREAM = 1,      /* one fused launch per iteration */
@@ -421,7 +424,7 @@ esp_status esp_nearest_profile(esp_ctx *store, int32_t num_queries, const int32_
 
 /*
  * esp_loop_driver: the loop driver esp_solve launches for this context's
- * solves with tol = 0 outside graph capture, ESP_MODE_STREAM,
+ * solves with tol = 0 outside graph capture and of 16 or more iterations, ESP_MODE_STREAM,
  * ESP_MODE_PERSISTENT or ESP_MODE_RESIDENT (ESP_MODE_AUTO resolved against the
  * table size, and against the device once a solve has run; PERSISTENT for an
  * ESP_MODE_RESIDENT context whose table is streamed).  Host-only.

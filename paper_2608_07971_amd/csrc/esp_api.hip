@@ -304,6 +304,7 @@ struct esp_ctx {
     bool auto_mode = false;            // the caller asked for ESP_MODE_AUTO
     bool fell_back = false;            // AUTO: the device refused a co-resident grid
     bool on_chip = false;              // resident launches: the tiles stay on chip
+    int32_t min_persistent = 0;        // AUTO, tol = 0: shorter solves run one launch per iteration
     std::vector<int64_t> off;          // family offsets (host copy)
     std::vector<int64_t> slot_of;      // first table slot of each family
     KArgs base{};
@@ -407,6 +408,7 @@ esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *pri
     // each launch then completes all of its iterations itself.
     bool persistent =
         !capturing && !c->fell_back && (c->mode != ESP_MODE_STREAM || (c->auto_mode && tol > 0.0));
+    if (c->auto_mode && !(tol > 0.0) && iters < c->min_persistent) persistent = false;
     bool resident = persistent && c->on_chip && (c->mode == ESP_MODE_RESIDENT || c->auto_mode);
     const int nblk_res = c->pl.nblk_res;
     {
@@ -668,6 +670,17 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     if (c->mode == ESP_MODE_AUTO &&
         static_cast<size_t>(B) * pl.columns() * pl.col_len * sizeof(float) > ESP_AUTO_PERSISTENT_BYTES)
         c->mode = ESP_MODE_STREAM;
+    // A cooperative launch costs about 25 us that an ordinary one does not, and
+    // saves 2.5 to 6 us an iteration against one launch each: short solves of
+    // larger tables are slower in it.  Measured, us, one launch each -> cooperative:
+    // streamed dense tables (40,000 x 64 x 8, 92 MB) T = 1 47 -> 72, 8 177 -> 187,
+    // 16 326 -> 322, (100,000, 230 MB) 8 354 -> 370, 16 666 -> 662; on chip
+    // (30,000 x 64 x 8) T = 3 70 -> 79, 5 99 -> 91; ragged (262,144 x 6, 92 MB)
+    // T = 1 52 -> 75, 4 112 -> 126, 8 192 -> 196, 12 272 -> 263.  Tables up to 64 MiB
+    // take the one launch in any case.
+    const int wgs = on_chip ? pl.nblk_res : pl.nblk;
+    if (wgs > 1 && static_cast<size_t>(B) * pl.columns() * pl.col_len * sizeof(float) > (64u << 20))
+        c->min_persistent = on_chip ? 5 : pl.csr ? 9 : 16;
     auto fail = [&](esp_status e) {
         if (c->h_stage) (void)hipHostFree(c->h_stage);
         if (c->stage_ev) (void)hipEventDestroy(c->stage_ev);

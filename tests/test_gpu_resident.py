@@ -403,3 +403,36 @@ def test_waits_outlast_errors_of_others(case, error):
             assert np.array_equal(g["lam"].cpu().numpy()[b], ref["lam"][b]), b
             assert np.array_equal(g["choice"].cpu().numpy()[b], ref["choice"][b]), b
     s.close()
+
+
+@pytest.mark.parametrize("n_jobs,k,r,shortest", [(40000, 64, 8, 16), (30000, 64, 8, 5), (220000, 12, 8, 9)])
+def test_short_solves_of_large_tables_take_no_cooperative_launch(n_jobs, k, r, shortest):
+    """Above 64 MiB a one-iteration solve of AUTO takes about as long as with one
+    launch per iteration (a cooperative launch makes it 1.3 to 1.6 times as
+    long), and both sides of the shortest cooperative solve match it bit for bit."""
+    inst = _dense(n_jobs, n_jobs, k, r)
+    assert 4 * inst.utility.size * (r + 1) > 64 << 20
+    auto, stream = esp.Solver(inst), esp.Solver(inst, mode=esp.ESP_MODE_STREAM)
+    for T in (1, shortest - 1, shortest):
+        _say(f"short solves N={n_jobs} K={k} R={r} T={T}")
+        a = auto.solve(auto.prices(inst.lam0), T, trace=True)
+        b = stream.solve(stream.prices(inst.lam0), T, trace=True)
+        torch.cuda.synchronize()
+        for key in ("choice", "U", "lam", "tr_lam", "tr_U", "iters_done"):
+            assert torch.equal(a[key], b[key]), (T, key)
+    lam = auto.prices(inst.lam0)
+    us = {id(auto): [], id(stream): []}
+    for i in range(31):
+        for s in (auto, stream):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(10):
+                s.solve(lam, 1)
+            e1.record()
+            torch.cuda.synchronize()
+            us[id(s)].append(e0.elapsed_time(e1) * 100.0)
+    a, b = (sorted(us[id(s)])[15] for s in (auto, stream))
+    print(f"[gpu-case] us a solve of one iteration: AUTO {a:.1f}, one launch each {b:.1f}", flush=True)
+    assert a < 1.2 * b
+    auto.close()
+    stream.close()
