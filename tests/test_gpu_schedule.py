@@ -139,3 +139,53 @@ def test_fullsize_batched_rounds():
     model = workloads.iac_model(inst)
     _say("schedule full-size batched, M=3, T=20")
     _compare(inst, model, 3, 20, clusters=(0, 1, 131, inst.B - 1))
+
+
+def _jobs_of_several_gpus(n_jobs, lo, hi, seed=1):
+    """Every job's favourite configuration takes lo..hi GPUs, 15 to 45% of the
+    compute and 5 to 30 GB of each."""
+    inst = workloads.make("small", n_jobs=n_jobs)
+    rng = np.random.default_rng(seed)
+    d = inst.demand.copy().reshape(1, n_jobs, -1, inst.R)
+    shape = d.shape[:2] + (1,)
+    g = rng.integers(lo, hi + 1, shape)
+    d[..., 0] = g
+    d[..., 1] = g * rng.uniform(5.0, 30.0, shape)
+    d[..., 2] = g * rng.uniform(0.15, 0.45, shape)
+    inst.demand = d.reshape(inst.demand.shape).astype(np.float32)
+    return inst
+
+
+# Jobs that take several GPUs of a group at once: all and parts of a lane's four
+# GPUs, the last of a group and the first of the next, GPUs that become full.
+@pytest.mark.parametrize("gpus,n_jobs,lo,hi", [(5, 30, 2, 5), (9, 60, 8, 8), (63, 100, 1, 8), (255, 300, 2, 3),
+                                               (259, 400, 7, 8), (600, 900, 1, 8), (2048, 1500, 3, 8)])
+def test_packing_jobs_of_several_gpus(gpus, n_jobs, lo, hi):
+    _say(f"packing jobs of {lo}..{hi} GPUs: {gpus} GPUs, {n_jobs} jobs")
+    inst = _jobs_of_several_gpus(n_jobs, lo, hi, gpus)
+    _compare(inst, workloads.iac_model(inst, gpus=[gpus]), 2, 0)
+
+
+def test_jobs_of_several_gpus_are_placed_at_once():
+    """Placing a job's 8 shares one after another made a round of 300 such jobs
+    4.6 times as long as one of 300 single-share jobs (all at once: 2.8)."""
+    us = []
+    for k in (1, 8):
+        inst = _with_penalty_inputs(_jobs_of_several_gpus(300, k, k))
+        model = workloads.iac_model(inst, gpus=[2048])
+        for f in ("sensitivity", "pressure", "tau_base"):
+            setattr(model, f, torch.as_tensor(getattr(model, f), device="cuda"))
+        s = esp.Solver(inst)
+        lam = s.prices(inst.lam0)
+        t = []
+        for _ in range(21):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            s.schedule(model, lam, 1, 0)
+            e1.record()
+            torch.cuda.synchronize()
+            t.append(e0.elapsed_time(e1) * 1e3)
+        us.append(sorted(t)[10])
+        s.close()
+    _say(f"a round of 300 jobs of 1 and 8 shares: {us[0]:.0f} and {us[1]:.0f} us")
+    assert us[1] < 3.6 * us[0]
