@@ -1448,16 +1448,19 @@ inline hipError_t launch_cooperative(const void *f, unsigned blocks, const KArgs
     return hipLaunchCooperativeKernel(f, dim3(blocks), dim3(threads), args, static_cast<unsigned>(lds), s);
 }
 
-// A multi-iteration launch of kernel f with `lds` bytes of dynamic LDS.  With
-// one workgroup per cluster no workgroup waits for another: an ordinary
-// launch.  Otherwise a cooperative one, so that the workgroups of a cluster
-// are co-resident.
+// A multi-iteration launch of kernel f with `lds` bytes of dynamic LDS, at most
+// lds_max.  With one workgroup per cluster no workgroup waits for another: an
+// ordinary launch.  Otherwise a cooperative one, so that the workgroups of a
+// cluster are co-resident.  The kernel's limit of dynamic LDS belongs to the
+// process: every launch sets the same value, so that another thread's launch of
+// the kernel, with fewer tiles, cannot lower it in between.
 inline hipError_t launch_multi(const void *f, unsigned blocks, const KArgs &a, int words, hipStream_t s,
-                               int threads = kBlockThreads, size_t lds = 0) {
+                               int threads = kBlockThreads, size_t lds = 0, size_t lds_max = 0) {
     // a copy's count field (the registers let no more workgroups be co-resident anyway)
     if (a.nblk > 255 * exchange_copies(words)) return hipErrorCooperativeLaunchTooLarge;
     if (lds > 0) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        const hipError_t e =
+            hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_max));
         if (e != hipSuccess) return e;
     }
     if (a.nblk == 1) {
@@ -1488,7 +1491,8 @@ hipError_t launch_dense_coop_ra(int lpj, const KArgs &a, int B, bool resident, h
         default: return hipErrorInvalidValue;
     }
     const size_t lds = resident ? resident_lds(R + 1 + (a.has_pen ? 1 : 0), a.lds_tiles) : 0;
-    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s, resident ? kResidentThreads : kBlockThreads, lds);
+    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s, resident ? kResidentThreads : kBlockThreads, lds,
+                        resident_lds_limit(R, lpj));
 }
 
 template <int R>

@@ -5,6 +5,7 @@ with several workgroups per cluster their exact sums travel as tagged
 one and many workgroups, dense and CSR tables, one to three limbs, several
 clusters, penalties, staggered stops, and solves longer than one launch."""
 import dataclasses
+import threading
 
 import numpy as np
 import pytest
@@ -436,3 +437,38 @@ def test_short_solves_of_large_tables_take_no_cooperative_launch(n_jobs, k, r, s
     assert a < 1.2 * b
     auto.close()
     stream.close()
+
+
+def test_contexts_of_one_kernel_in_two_threads():
+    """Two threads solve on contexts of the same kernel instance with 1 and 2 LDS
+    tiles a wavefront: neither changes what the other's launches may use."""
+    _say("two threads, 17 and 32 tiles on one workgroup")
+    insts = [_dense(3, 65, 64, 8), _dense(4, 127, 64, 8)]
+    refs = [oracle.Oracle(i).solve(iters=3) for i in insts]
+    solvers = [esp.Solver(i, blocks_per_cluster=1) for i in insts]
+    start, errors = threading.Barrier(2), []
+
+    def work(i):
+        try:
+            s, stream = solvers[i], torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                lam0 = s.prices(insts[i].lam0)
+                start.wait()
+                for _ in range(400):
+                    lam = lam0.clone()
+                    g = s.solve(lam, 3)
+            stream.synchronize()
+            assert s.device_status() == 0 and s.loop_driver() == esp.ESP_MODE_RESIDENT
+            assert np.array_equal(g["lam"].cpu().numpy(), refs[i]["lam"])
+            assert np.array_equal(g["choice"].cpu().numpy(), refs[i]["choice"])
+        except BaseException as e:                   # noqa: BLE001 (reported below)
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not errors, errors
+    for s in solvers:
+        s.close()
