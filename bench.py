@@ -40,7 +40,7 @@ def _parse():
     ap.add_argument("--sweep", type=int, default=0, help="0 = alternate sweep direction, 1 = forward only")
     ap.add_argument("--mode", type=int, default=0,
                     help="loop driver: 0 auto, 1 one launch per iteration, 2 persistent (table streamed every "
-                         "iteration), 3 resident (tiles held in registers)")
+                         "iteration), 3 resident (tiles kept on chip)")
     ap.add_argument("--graph", action="store_true",
                     help="capture one step (price reset + esp_solve, one launch per pass) in a HIP graph and time "
                          "its replays")
@@ -242,7 +242,7 @@ def main() -> int:
                      "kernel": ("k_csr" if csr else "k_dense") + " (fused score/select/demand/update)",
                      "driver": ("graph: replays of a captured step, one launch per pass" if args.graph
                                 else "persistent: one cooperative launch runs the T passes" if persistent
-                                else "resident: one launch runs the T passes over tiles held in registers"
+                                else "resident: one launch runs the T passes over tiles kept on chip"
                                 if resident else "stream: one launch per pass"),
                      "bytes_per_pass": bytes_per_pass, "avg_pass_us": avg_pass_s * 1e6,
                      "passes_per_launch": T if (persistent or resident) else 1},

@@ -216,9 +216,9 @@ esp_status esp_update_prices(esp_ctx *ctx, const double *demand, int32_t t, doub
  * esp_solve: `iters` iterations t = t_start .. t_start+iters-1 of
  * select -> demand -> update, one fused kernel pass per iteration (the passes
  * run as one launch each or inside one persistent launch, see ESP_MODE_*;
- * with several workgroups per cluster the update of iteration t is computed
- * at the start of the next pass, or of a closing launch after the last one),
- * then a re-selection at the final prices (Alg. 1).
+ * with several workgroups per cluster and one launch each, the update of
+ * iteration t is computed at the start of the next launch, or of a closing one
+ * after the last), then a re-selection at the final prices (Alg. 1).
  *   prices      device [B][R], in lambda^{t_start} (finite, >= 0; a -0.0 entry is stored
  *               back as +0.0 before the first iteration, so no price the call
  *               returns is -0.0), out the final prices
@@ -249,7 +249,7 @@ esp_status esp_solve(esp_ctx *ctx, double *prices, int32_t iters, int32_t t_star
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation).  Same arguments, results and errors as esp_solve (bit for bit
  * the same outputs), but the call allocates nothing and its per-solve scratch
- * -- per-workgroup partial sums, arrival tickets, barrier words, the prices of
+ * -- per-workgroup partial sums, arrival tickets, exchange words, the prices of
  * the iteration being completed, the stop iteration and the update counts --
  * lives in one static device array of the library, ESP_NOALLOC_SCRATCH_BYTES
  * on each GPU, held until the process ends, instead of the context's

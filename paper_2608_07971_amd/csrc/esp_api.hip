@@ -378,7 +378,7 @@ hipError_t launch_select(const esp_ctx *c, const KArgs &a, hipStream_t s) {
 namespace {
 
 // The body of esp_solve and esp_solve_noalloc.  `kb` is the context's launch
-// arguments with the per-solve scratch (partial sums, tickets, barrier words,
+// arguments with the per-solve scratch (partial sums, tickets, exchange words,
 // lambda_m, stop iteration) pointing into the context's workspace or into the
 // static scratch array; d_iters (device [B]) counts the updates.
 esp_status solve_with(esp_ctx *c, const KArgs &kb, int32_t *d_iters, double *prices, int32_t iters,

@@ -473,9 +473,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_nearest(KArgs a, NearestArgs 
 // A cluster without violations is frozen: later rounds' kernels skip it.
 //
 // First fit is one serial chain over the jobs, so its latency per job bounds
-// the kernel.  Wavefront 0 does nothing else: it holds every GPU's residuals
-// in registers (lane l, slot i: GPU 64 i + l), so testing a group of 4 slots
-// (256 GPUs) is 8 compares whose results are the wave-wide masks, and a share
+// the kernel.  Wavefront 0 does nothing else: it holds the residuals of one
+// group of 256 GPUs in registers (lane l, slot i: GPU 4 l + i of the group; the
+// other groups lie in LDS and are swapped in when a job needs them), so testing
+// the group is 8 compares whose results are the wave-wide masks, and a share
 // is placed by the lanes that hold its GPUs, with no LDS round trip (the
 // occupants are written to LDS, read only after the packing).  The other
 // wavefronts gather the jobs ahead of it, kPackChunk batches of 64 at a time

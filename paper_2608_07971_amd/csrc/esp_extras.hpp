@@ -53,7 +53,7 @@ static_assert(kMaxFamily <= 256, "family sizes minus one fit a byte");
 // Outer ESP-IAC rounds (Alg. 1): one workgroup per cluster packs the
 // selection onto GPUs (first fit), evaluates co-located pairs and raises the
 // penalties of offending configurations.
-constexpr int kMaxGpus = 2048;                      // GPUs per cluster (residuals in one wavefront's registers)
+constexpr int kMaxGpus = 2048;                      // GPUs per cluster (residuals: 256 of them in one wavefront's registers, the others in LDS)
 constexpr int kMaxPerGpu = 4;                       // jobs sharing one GPU
 constexpr int kMaxShards = 8;                       // GPUs of one job
 

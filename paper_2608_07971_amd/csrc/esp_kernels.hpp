@@ -9,12 +9,13 @@
 //   demand  U_r  = sum_j d_{j,c_j,r}, exact             (Sec. 3.2.3, under Eq. 8)
 //   update  lambda_r <- max(0, lambda_r + eta_t (U_r - C_r))  (Eq. 8)
 //
-// With several workgroups per cluster, a solve iteration ends once every
-// workgroup has published its exact demand sums; every workgroup of the
-// cluster then computes U and the update itself at the start of the next
-// iteration (integer sums: all obtain the same bits), so no workgroup waits
-// for a last one to finish the update.  With one workgroup per cluster the
-// workgroup updates at the end of its own iteration.
+// With several workgroups per cluster, such a launch ends once every workgroup
+// has published its exact demand sums; every workgroup of the cluster then
+// computes U and the update itself at the start of the next launch (integer
+// sums: all obtain the same bits), so no workgroup waits for a last one to
+// finish the update.  With one workgroup per cluster the workgroup updates at
+// the end of its own iteration.  Launches of several iterations exchange the
+// sums among the workgroups at the end of each (resident_complete).
 //
 // Table layout (built by the packer): per cluster, one fp32 column for the
 // utility and one per resource, each a sequence of 256-entry tiles.  A
@@ -268,7 +269,7 @@ __device__ __forceinline__ void publish_iteration(const KArgs &a, int cl, int bl
 // alternate too; the tag tells m from m - 2.  The solve's prologue clears the
 // words.
 constexpr uint64_t kLimbMask = (1ull << kLimbBits) - 1;
-constexpr int kSlotWords = kSyncStride / 2;    // 64-bit words of a 256-byte slot of the barrier words
+constexpr int kSlotWords = kSyncStride / 2;    // 64-bit words of a 256-byte slot of the exchange words
 constexpr int kReplicas = 4;
 
 // Where this lane's word (lane = limb * R + resource) is added and released;
@@ -969,7 +970,6 @@ __device__ __forceinline__ uint64_t lanes_before(uint64_t m, uint64_t next) {
 // 100 ragged jobs x 8 3.3 -> 2.1 us, 60,000 x 4 4.1 -> 3.9, 200,000 x 5 x 3 4.6 -> 4.2).
 constexpr int csr_waves(int mode) { return mode == kResident ? kResidentWaves : kBlockWaves; }
 
-//
 // The scoring is 76 of a tile's VALU instructions (R = 6); who wins is worked
 // out on lane masks in scalar registers, which leaves about 190 of the 351 that
 // per-lane flags, indices and staged winners took.  A pass over a small table

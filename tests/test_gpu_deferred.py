@@ -1,9 +1,10 @@
-"""GPU parity of the deferred completion of price iterations (several
-workgroups per cluster): every workgroup completes iteration t (U^t and the
-Eq. 8 update) at the start of iteration t + 1, or in the closing launch after
-the last one.  Covers clusters that meet the stop tolerance at different
+"""GPU parity of the completion of price iterations with several workgroups
+per cluster: with one launch per iteration every workgroup completes iteration t
+(U^t and the Eq. 8 update) at the start of launch t + 1, or in the closing launch
+after the last one; in persistent launches at the end of the iteration, through
+counted words.  Covers clusters that meet the stop tolerance at different
 iterations (including the first), the closing launch with and without the
-final re-selection, group sizes of the persistent barrier, and persistent
+final re-selection, workgroups around the exchange's 16 copies, and persistent
 solves longer than one cooperative launch."""
 import numpy as np
 import pytest
@@ -80,8 +81,8 @@ def test_closing_launch_without_reselection(mode):
 
 def test_persistent_solve_longer_than_one_launch():
     """1,100 iterations on Small (128 workgroups): two cooperative launches
-    (1,024 + 76 iterations); the second starts by completing the first's
-    last iteration.  Bitwise equal to one launch per iteration and to the
+    (1,024 + 76 iterations); the second starts from the prices the first
+    wrote.  Bitwise equal to one launch per iteration and to the
     oracle."""
     inst = workloads.make("small")
     T = 1100

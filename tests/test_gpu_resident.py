@@ -1,7 +1,8 @@
-"""GPU parity of the resident driver (ESP_MODE_RESIDENT): tiles held in
-registers for the whole launch, every iteration completed inside the launch;
-with several workgroups per cluster their exact sums travel as tagged
-48-bit limbs.  Every iterate against the free-running oracle (bitwise), over
+"""GPU parity of the resident driver (ESP_MODE_RESIDENT, and ESP_MODE_AUTO where
+the table fits): tiles kept on chip for the whole launch, every iteration
+completed inside the launch; with several workgroups per cluster their exact
+sums meet in counted words, as 45-bit limbs when one word does not hold them.
+Every iterate against the free-running oracle (bitwise), over
 one and many workgroups, dense and CSR tables, one to three limbs, several
 clusters, penalties, staggered stops, and solves longer than one launch."""
 import dataclasses

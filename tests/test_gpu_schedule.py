@@ -74,8 +74,8 @@ def test_schedule_matches_oracle(name):
         _compare(inst, model, M, T)
 
 
-# GPUs around the 64-GPU slots, the 256-GPU groups and the register instances
-# (256, 512, 1024, 2048 GPUs) of the packing kernel; jobs around its batches of
+# GPUs around the 4 slots of a lane and the 256-GPU groups of the packing
+# kernel (one group in registers, up to 8 in all); jobs around its batches of
 # 64 and chunks of 14 batches; T = 0 takes every job's favourite configuration
 # (8 whole GPUs, shares split over groups, many failures), T = 3 small shares.
 @pytest.mark.parametrize("gpus,n_jobs", [(1, 1), (3, 63), (64, 65), (65, 128), (255, 300), (256, 895), (257, 896),
@@ -91,7 +91,7 @@ def test_packing_edges(gpus, n_jobs):
 
 
 def test_packing_mixed_cluster_sizes():
-    """One launch over clusters far below and at the instance's size."""
+    """One launch over clusters of one to all eight groups."""
     inst = workloads.make("batched", n_jobs=500, n_clusters=4)
     _say("packing of clusters with 1, 64, 700 and 2048 GPUs")
     _compare(inst, workloads.iac_model(inst, gpus=[1, 64, 700, 2048]), 2, 2)

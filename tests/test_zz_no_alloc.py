@@ -77,7 +77,7 @@ def test_noalloc_solve_matches_solve_on_calls_in_a_row():
 
 
 def test_noalloc_refuses_problems_beyond_its_scratch():
-    """512 clusters need more than ESP_NOALLOC_SCRATCH_BYTES (barrier words
+    """512 clusters need more than ESP_NOALLOC_SCRATCH_BYTES (exchange words
     alone take 4352 bytes per cluster): refused on the host, nothing runs."""
     inst = workloads.random_small(44, 64, 8, 4, dense=True, n_clusters=512, iters=5)
     _say("noalloc: 512 clusters, beyond the static scratch")
