@@ -391,11 +391,11 @@ __device__ __forceinline__ ResidentCtx resident_ctx(const KArgs &a, int cl, int 
 }
 
 // The exchange of iteration m: this lane's word `v` (lanes below xch.words)
-// becomes the cluster's total.  Returns false after about 2 s, or when another
-// workgroup of the cluster has given up (kFlagAborted, cleared by the solve's
-// prologue).  Nothing else ends a wait: the status word is shared by all clusters
-// and may still hold an error of another cluster or of an earlier call.
-__device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &xch, int cl, int m, int lane, uint64_t &v) {
+// becomes the cluster's total.  Returns false after about 2 s (resident_outputs
+// records it).  Nothing else ends a wait: the status word is shared by all
+// clusters and may hold an error of another cluster or of an earlier call.  A
+// workgroup gives up once, so the others of its cluster do after at most 2 s more.
+__device__ __forceinline__ bool exchange_total(const Exchange &xch, int m, int lane, uint64_t &v) {
     constexpr uint64_t kOne = 1ull << kCountShift, kLow = kOne - 1;
     const int par = m & 1;
     const uint64_t tag = static_cast<uint64_t>(m % 255 + 1) << kCountShift;
@@ -420,21 +420,12 @@ __device__ __forceinline__ bool exchange_total(const KArgs &a, const Exchange &x
     }
     const uint64_t *const from = release + xch.first_replica * xch.replica_words;
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    // (conditions of the whole wavefront only: a branch per lane in here lengthens every poll)
     for (int tries = 1;; ++tries) {
         const uint64_t x = __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__ballot((x & ~kLow) != tag) == 0) {           // (lanes without a word read word 0)
-            v = x & kLow;
-            return true;
-        }
-        if ((tries & 63) == 0 &&
-            ((__hip_atomic_load(&a.flags[cl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFlagAborted) != 0 ||
-             __builtin_amdgcn_s_memrealtime() - t0 > 200000000ull)) {
-            if (lane == 0) {
-                atomicOr(&a.flags[cl], kFlagAborted);
-                atomicCAS(a.status, 0, kStatusTimeout);
-            }
-            return false;
-        }
+        v = x & kLow;
+        if (__ballot((x & ~kLow) != tag) == 0) return true;   // (lanes without a word read word 0)
+        if ((tries & 63) == 0 && __builtin_amdgcn_s_memrealtime() - t0 > 200000000ull) return false;
     }
 }
 
@@ -483,7 +474,7 @@ __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl
             uint64_t v = fx_words(tot, ctx.shift);
             if constexpr (!std::is_floating_point_v<A>) if (xch.words > R)
                 v = static_cast<uint64_t>(static_cast<u128>(tot) >> (kLimbBits * (lane < xch.words ? lane / R : 0))) & kLimbMask;
-            go = exchange_total(a, xch, cl, a.iter_no + it, lane, v);
+            go = exchange_total(xch, a.iter_no + it, lane, v);
             if constexpr (std::is_floating_point_v<A>) {
                 tot = fx_to_double(v, ctx.shift);
             } else if (xch.words == R) {
@@ -526,11 +517,19 @@ __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl
 }
 
 // End of a resident launch: the prices, the update count and the stop flag of
-// its last completed iteration.
+// its last completed iteration; and a wait that ran out of time, in the status
+// and in the cluster's flags, so that later launches of the solve skip its
+// iterations (here and not where it is found: its constants would take
+// registers of the whole loop).
 template <int R>
 __device__ __forceinline__ void resident_outputs(const KArgs &a, int cl, int blk, int wave, int lane,
                                                  const ResidentCtx &ctx) {
-    if ((blk != 0) | (wave != 0) | (ctx.done == 0)) return;
+    if (wave != 0) return;
+    if ((lane == 0) & !ctx.stop & (ctx.done < a.n_iters)) {
+        atomicOr(&a.flags[cl], kFlagAborted);
+        atomicCAS(a.status, 0, kStatusTimeout);
+    }
+    if ((blk != 0) | (ctx.done == 0)) return;
     if (lane < R) a.lam_out[static_cast<size_t>(cl) * R + lane] = ctx.lo;
     if (lane == 0) {
         if (a.iters_done) a.iters_done[cl] = a.iter_no + ctx.done - 1;
