@@ -392,11 +392,13 @@ def test_waits_outlast_errors_of_others(case, error):
     torch.cuda.synchronize()
     got = []
     for _ in range(4):
-        # (one round without iterations: returns while the packing runs)
-        busy.schedule(model, blam, 1, 0, stream=side)
+        # (one round without iterations: returns while the packing runs, whose outputs
+        # must then not be freed for this stream's tensors)
+        packed = busy.schedule(model, blam, 1, 0, stream=side)
         lam.copy_(torch.as_tensor(lam0))
         got.append({k: v.clone() for k, v in s.solve(lam, T).items()})
         torch.cuda.synchronize()
+        del packed
     busy.close()
     assert s.device_status() == (esp.ESP_ERR_NONFINITE if error == "bad_price" else esp.ESP_ERR_INVALID_ARG)
     for g in got:
