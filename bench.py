@@ -239,7 +239,7 @@ def main() -> int:
         "pct_hbm_peak": 100.0 * achieved / HBM_PEAK_GBS,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": ("k_csr" if csr else "k_dense") + " (fused score/select/demand/update)",
+                     "kernel": ("k_csr" if csr else "k_resident" if resident else "k_dense") + " (fused score/select/demand/update)",
                      "driver": ("graph: replays of a captured step, one launch per pass" if args.graph
                                 else "persistent: one cooperative launch runs the T passes" if persistent
                                 else "resident: one launch runs the T passes over tiles kept on chip"
