@@ -1240,20 +1240,25 @@ __global__ __launch_bounds__(csr_waves(Mode) * kWaveSize, 2) void k_csr(KArgs a)
 
 // Each job's R demands lie in R columns at an arbitrary slot: a chain of two
 // (CSR: three) dependent loads per job, bound by their latency, so the kernel
-// keeps many in flight: 16 wavefronts per workgroup (the partial sums allow
-// the plan's number of workgroups only) and kGatherJobs jobs per thread at
-// once.  Totals over a wavefront's lanes stay in registers.  Measured on 16
-// clusters of 8,192 jobs x 32 x 6 against 4 wavefronts taking one job at a
-// time with an LDS tree per resource: 25.3 -> 21.4 us a call, near the 100 MB of
-// lines that it touches (64 clusters of 2,000 24.5 -> 21.4, 262,144 jobs x 16 x 8
-// 32.1 -> 27.2).
-constexpr int kGatherThreads = 1024;
-constexpr int kGatherWaves = kGatherThreads / kWaveSize;
+// keeps up to kGatherJobs jobs per thread in flight.  Totals over a wavefront's
+// lanes stay in registers.  Workgroups are small (4 wavefronts), so that many
+// clusters' workgroups, or a plan's 512, are on the device at once; 16
+// wavefronts pay only where a workgroup of the plan has thousands of jobs with
+// few loads each (gather_wide).  us a call, one job at a time in 4 wavefronts ->
+// 16 wavefronts -> 4: 16 clusters of 8,192 jobs x 32 x 6 24.9 -> 21.3 -> 20.2 (near the
+// 100 MB of lines that it touches), 262,144 x 16 x 8 31.4 -> 26.5 -> 24.9, 64 of 2,000 x
+// 12 x 6 15.6 -> 28.5 -> 10.8, 600 of 200 x 12 x 8 18.5 -> 30.2 -> 13.7; 1,000,000 x 4 x 3
+// 24.6 -> 16.8 -> 19.2.
 constexpr int kGatherJobs = 4;
+// 16 wavefronts -> 4, jobs per workgroup, us: 3 resources 2,083 11.3 -> 10.4, 3,125 12.3 -> 12.5,
+// 10,400 24.0 -> 31.2; 4 resources 2,500 10.3 -> 10.7, 8,000 23.6 -> 25.6; 6 resources 5,208 24.0 ->
+// 23.2; 8 resources 3,906 26.8 -> 27.0.
+inline bool gather_wide(int R, int N, int nblk) { return R <= 4 && N / nblk >= 2500; }
 
-template <int R, typename A>
-__global__ __launch_bounds__(kGatherThreads) void k_gather(KArgs a) {
-    __shared__ A s_wave[kGatherWaves][R];
+template <int R, typename A, int Threads>
+__global__ __launch_bounds__(Threads) void k_gather(KArgs a) {
+    constexpr int Waves = Threads / kWaveSize;
+    __shared__ A s_wave[Waves][R];
     __shared__ u128 s_bsum[R];
     __shared__ int s_bad;
     const int cl = blockIdx.x / a.nblk;
@@ -1271,8 +1276,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(KArgs a) {
     if (threadIdx.x == 0) s_bad = 0;
     __syncthreads();
     bool bad = false;
-    const int64_t step = static_cast<int64_t>(a.nblk) * kGatherThreads;
-    const int64_t first = static_cast<int64_t>(blk) * kGatherThreads;      // the workgroup's first job of a step
+    const int64_t step = static_cast<int64_t>(a.nblk) * Threads;
+    const int64_t first = static_cast<int64_t>(blk) * Threads;      // the workgroup's first job of a step
     for (int64_t w0 = first; w0 < a.N; w0 += kGatherJobs * step) {
         // The loads of up to kGatherJobs steps in flight together; a step past the end is
         // skipped by the whole workgroup, jobs past the end in the last step are clamped
@@ -1326,7 +1331,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(KArgs a) {
     if (threadIdx.x < R) {
         u128 v = 0;
 #pragma unroll
-        for (int w = 0; w < kGatherWaves; ++w) v += static_cast<u128>(s_wave[w][threadIdx.x]);
+        for (int w = 0; w < Waves; ++w) v += static_cast<u128>(s_wave[w][threadIdx.x]);
         s_bsum[threadIdx.x] = v;
     }
     __syncthreads();
@@ -1502,14 +1507,21 @@ hipError_t launch_dense_coop_r(int lpj, const KArgs &a, int B, bool resident, hi
                     : launch_dense_coop_ra<R, uint64_t>(lpj, a, B, resident, s);
 }
 
+template <int R, int Threads>
+hipError_t launch_gather_rt(const KArgs &a, int B, hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>(B) * a.nblk), block(Threads);
+    if (a.acc128)
+        hipLaunchKernelGGL((k_gather<R, u128, Threads>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((k_gather<R, uint64_t, Threads>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
 template <int R>
 hipError_t launch_gather_r(const KArgs &a, int B, hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>(B) * a.nblk), block(kGatherThreads);
-    if (a.acc128)
-        hipLaunchKernelGGL((k_gather<R, u128>), grid, block, 0, s, a);
-    else
-        hipLaunchKernelGGL((k_gather<R, uint64_t>), grid, block, 0, s, a);
-    return hipGetLastError();
+    if constexpr (R <= 4)
+        if (gather_wide(R, a.N, a.nblk)) return launch_gather_rt<R, 1024>(a, B, s);
+    return launch_gather_rt<R, kBlockThreads>(a, B, s);
 }
 
 template <int R>

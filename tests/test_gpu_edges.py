@@ -106,11 +106,14 @@ def test_csr_scan_edges(sizes, bits):
         _parity(inst, 25, mode)
 
 
-# Around the gather kernel's 1,024 threads, 4 jobs per thread and the plan's
-# workgroups, dense and CSR, 64- and 128-bit sums, several clusters.
+# Around the gather kernel's 256 threads (1,024 from 2,500 jobs per workgroup at up
+# to 4 resources), 4 jobs per thread and the plan's workgroups, dense and CSR, 64- and
+# 128-bit sums, several clusters.
 @pytest.mark.parametrize("n_jobs,k,r,clusters,blocks", [
     (1, 4, 1, 1, 0), (63, 8, 3, 1, 1), (1023, 16, 8, 1, 1), (1024, 16, 5, 1, 1), (1025, 5, 7, 1, 1),
-    (4095, 4, 2, 1, 1), (4097, 12, 6, 1, 1), (5000, 32, 4, 3, 2), (9001, 7, 8, 2, 3), (3000, 64, 8, 1, 0)])
+    (4095, 4, 2, 1, 1), (4097, 12, 6, 1, 1), (5000, 32, 4, 3, 2), (9001, 7, 8, 2, 3), (3000, 64, 8, 1, 0),
+    (255, 4, 2, 1, 1), (257, 12, 6, 1, 1), (2499, 4, 4, 1, 1), (2500, 12, 3, 1, 1), (4999, 8, 1, 2, 2),
+    (5000, 4, 4, 2, 2), (8193, 16, 3, 1, 2), (40, 8, 6, 300, 0)])
 @pytest.mark.parametrize("wide", [False, True])
 def test_reduce_demand_edges(n_jobs, k, r, clusters, blocks, wide):
     inst = workloads.random_small(n_jobs + k, n_jobs, k, r, dense=k != 12, n_clusters=clusters)
@@ -168,3 +171,28 @@ def test_default_stream_is_the_callers():
     with torch.cuda.stream(side):
         assert esp._stream(None) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
     assert esp._stream(side) == side.cuda_stream
+
+
+def test_demand_of_many_clusters_takes_no_longer_than_of_one():
+    """128,000 ragged jobs as 64 clusters or as one: the same loads.  512 workgroups
+    are on the device at once when they have 4 wavefronts (0.8 times as long);
+    with 16 they took 1.6 times as long."""
+    us = []
+    for clusters in (64, 1):
+        inst = workloads.random_small(3, 128000 // clusters, 12, 6, dense=True, n_clusters=clusters)
+        s = esp.Solver(inst)
+        choice = torch.randint(0, 12, (clusters, inst.N), dtype=torch.int32, device="cuda")
+        U = s.reduce_demand(choice)
+        t = []
+        for _ in range(31):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(50):
+                esp.esp_reduce_demand(s.ctx, choice, U)
+            e1.record()
+            torch.cuda.synchronize()
+            t.append(e0.elapsed_time(e1) * 20.0)
+        us.append(sorted(t)[15])
+        s.close()
+    _say(f"demand of 128,000 jobs: {us[0]:.1f} us as 64 clusters, {us[1]:.1f} as one")
+    assert us[0] < 1.2 * us[1]
