@@ -40,6 +40,7 @@ struct Plan {
     size_t col_len = 0; // floats per column
     int nblk = 0;       // workgroups per cluster
     int nblk_res = 0;   // the same in resident launches
+    int res_waves = kResidentWaves;   // wavefronts of their workgroups
     bool res_lds = false;   // resident launches may keep tiles in LDS
     int aos_stride = 0; // floats per entry of the entry-major copy, 0 when there is none
     int64_t aos_lines = 0;  // kStoreLine-byte lines of one cluster's entry-major copy
@@ -175,6 +176,10 @@ esp_status make_plan(const esp_problem *p, const esp_options *opt, Plan *pl) {
     else if (callers) pl->nblk_res = std::min(pl->nblk, per_unit);
     else pl->nblk_res = pl->tiles <= 2 * kResidentWaves ? 1 : std::min(per_unit, max_useful);
     pl->res_lds = !pl->csr && !(callers && pl->nblk > per_unit);
+    // More clusters than compute units, in one workgroup each: with four
+    // wavefronts two of them share a unit, where two tiles per wavefront hold the
+    // table (200 iterations of 512 clusters x 4 tiles x 4 resources 401 -> 244 us).
+    if (pl->nblk_res == 1 && pl->B > cus && pl->tiles <= 2 * kBlockWaves) pl->res_waves = kBlockWaves;
     if (static_cast<int64_t>(pl->nblk) * pl->B > INT32_MAX) return ESP_ERR_SHAPE;
 
     const size_t B = pl->B, R = pl->R;
@@ -634,7 +639,7 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     const bool resident_ok = static_cast<int64_t>(pl.tiles) <= 2ll * pl.nblk * kBlockWaves &&
                              (pl.nblk == 1 || (groups >= 1 && pl.nblk <= 32 * groups && pl.nblk <= 4 * 255));
     limbs = need_bits <= kCountShift ? 1 : (need_bits + kLimbBits - 1) / kLimbBits;   // as exchanged
-    const int64_t res_waves = static_cast<int64_t>(pl.nblk_res) * kResidentWaves;
+    const int64_t res_waves = static_cast<int64_t>(pl.nblk_res) * pl.res_waves;
     int lds_tiles = 0;
     bool on_chip = pl.tiles <= 2 * res_waves && (resident_ok || !pl.csr);
     if (!on_chip && pl.res_lds) {
@@ -913,6 +918,7 @@ esp_status esp_create(const esp_problem *p, const esp_step_rule *step, const esp
     k.limbs = limbs;
     k.xch_clear = 0;
     k.lds_tiles = on_chip ? lds_tiles : 0;
+    k.res_waves = pl.res_waves;
     c->on_chip = on_chip;
     *out = c;
     return ESP_OK;

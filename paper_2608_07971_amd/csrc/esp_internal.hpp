@@ -34,12 +34,12 @@ constexpr int kCountShift = 56;
 constexpr int kLimbBits = 45;                       // the limbs of 2,048 workgroups add up to kCountShift bits
 // Copies that share the first adds of `words` words (a slot line of 8, 16 or 24).
 __host__ __device__ constexpr int exchange_copies(int words) { return words <= 8 ? 16 : words <= 16 ? 8 : 4; }
-// Dense resident workgroups: 8 wavefronts, two per SIMD (a lone wavefront
+// Resident workgroups: 8 wavefronts (4 for many small clusters), two per SIMD (a lone wavefront
 // issues an instruction every 7 cycles or so while it scores), one workgroup
 // per CU.  Tiles beyond two per wavefront lie in LDS: the CU's 160 KB less
 // what the kernel itself uses (step sizes, staged demands, sums).
 constexpr int kResidentWaves = 8;
-constexpr int kResidentThreads = kResidentWaves * kWaveSize;
+constexpr int kResidentThreads = kResidentWaves * kWaveSize;   // (at most: see KArgs::res_waves)
 constexpr size_t resident_lds(int columns, int tiles_per_wave) {
     return static_cast<size_t>(kResidentWaves) * tiles_per_wave * columns * kTileEntries * sizeof(float);
 }
@@ -144,6 +144,7 @@ struct KArgs {
     // Multi-iteration launches (every iteration completed in the launch).
     int32_t limbs;                 // limbs per workgroup sum
     int32_t lds_tiles;             // tiles per wavefront kept in LDS (dense resident launches)
+    int32_t res_waves;             // wavefronts per workgroup of resident launches, kResidentWaves or kBlockWaves
     size_t xch_clear;              // words of `sync` k_prepare sets to 0 before a solve of such launches (0: none)
 };
 

@@ -449,11 +449,18 @@ __device__ __forceinline__ bool exchange_total(const Exchange &xch, int m, int l
 struct Nothing {
     __device__ __forceinline__ void operator()() const {}
 };
+// The wavefronts' sums of an iteration (LDS).  A launch of fewer than Waves
+// wavefronts sets them to 0 first: those of the missing ones stay so.
+template <int R, int Waves, typename A>
+__device__ __forceinline__ A (&wave_sums())[Waves][R] {
+    __shared__ A s_wave[Waves][R];
+    return s_wave;
+}
 template <int R, int Waves, int Group, typename A, typename Between = Nothing>
 __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl, int blk, int wave, int lane, A acc,
                                                   double eta, double (&lam)[R], ResidentCtx &ctx, const Exchange &xch,
                                                   Between &&between = {}) {
-    __shared__ A s_wave[Waves][R];
+    A(&s_wave)[Waves][R] = wave_sums<R, Waves, A>();
     __shared__ double s_price[R];
     __shared__ int s_go;
     if constexpr (Group > 0) {
@@ -467,8 +474,23 @@ __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl
         // (every partial sum fits the accumulator type A: the packer sized A for
         // the whole column's total)
         A tot = 0;
+        if constexpr (std::is_floating_point_v<A> || Waves <= kBlockWaves) {
 #pragma unroll
-        for (int w = 0; w < Waves; ++w) tot += s_wave[w][lane % R];
+            for (int w = 0; w < Waves; ++w) tot += s_wave[w][lane % R];
+        } else {
+            // (integer sums: with the upper wavefronts' behind a branch, 3,000 jobs x 16 x 5 of 54-bit
+            // sums 3.61 -> 3.50 us an iteration, 9,000 x 64 x 8 of 96-bit ones 5.26 -> 5.13; binary64 ones
+            // lose as much by it)
+            A x[Waves];
+#pragma unroll
+            for (int w = 0; w < Waves; ++w) x[w] = s_wave[w][lane % R];
+#pragma unroll
+            for (int w = 0; w < kBlockWaves; ++w) tot += x[w];
+            if (a.res_waves > kBlockWaves) {
+#pragma unroll
+                for (int w = kBlockWaves; w < Waves; ++w) tot += x[w];
+            }
+        }
         bool go = true;
         if (a.nblk > 1) {
             // lane l R + r exchanges limb l of resource r
@@ -492,8 +514,8 @@ __device__ __forceinline__ bool resident_complete(const KArgs &a, int it, int cl
         const double lo = ctx.lo;
         const double U = fx_to_double(tot, ctx.shift);
         const double gd = U - ctx.cap;
-        const double x = lo + eta * gd;
-        const double ln = (x > 0.0) ? x : 0.0;
+        const double next = lo + eta * gd;
+        const double ln = (next > 0.0) ? next : 0.0;
         const double scale = lo > 1.0 ? lo : 1.0;
         const bool ok = (lane >= R) | (fabs(ln - lo) <= a.tol * scale);
         const bool stop = (a.tol > 0.0) & (__ballot(!ok) == 0);
@@ -812,7 +834,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(KArgs a) {
     const int jt = lane / LPJ;                 // job within the tile
     // tile s of wavefront w: every workgroup's wavefront w before any's w + 1, so that the wavefronts
     // that share a SIMD (w and w + 4) both have tiles only when there are more than 4 per workgroup
-    const int stride = a.nblk * kResidentWaves;
+    const int stride = a.nblk * a.res_waves;
     const int tile0 = wave * a.nblk + blk;
     const int last = a.tiles - 1;
     const double sw = a.has_pen ? a.switch_cost[cl] : 0.0;
@@ -898,6 +920,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(KArgs a) {
         if (a.has_pen) p[(R + 1) * kWaveSize] = pp;
     }
     wave_sync();
+    if (threadIdx.x < kResidentWaves * R) wave_sums<R, kResidentWaves, A>()[threadIdx.x / R][threadIdx.x % R] = 0;
     const double *etas = resident_etas(a, cl);
 #pragma unroll
     for (int r = 0; r < R; ++r) lam[r] = a.lam_in[cl * R + r];
@@ -1028,7 +1051,7 @@ __global__ __launch_bounds__(csr_waves(Mode) * kWaveSize, 2) void k_csr(KArgs a)
         return wave_totals<R>(x);
     };
     const double sw = a.has_pen ? a.switch_cost[cl] : 0.0;
-    const int stride = a.nblk * Waves;
+    const int stride = a.nblk * (Mode == kResident ? a.res_waves : Waves);
     const int last = a.tiles - 1;
     auto load_tile = [&](int t, int rev, f4 &u, f4 (&d)[R], f4 &pn, Heads &h) {
         const int tl = rev ? last - t : t;
@@ -1168,6 +1191,7 @@ __global__ __launch_bounds__(csr_waves(Mode) * kWaveSize, 2) void k_csr(KArgs a)
 #pragma unroll
         for (int r = 0; r < R; ++r) lam[r] = s_lam[r];
     } else {
+        if (Mode == kResident && threadIdx.x < Waves * R) wave_sums<R, Waves, A>()[threadIdx.x / R][threadIdx.x % R] = 0;
         etas = resident_etas(a, cl);
 #pragma unroll
         for (int r = 0; r < R; ++r) lam[r] = a.lam_in[cl * R + r];
@@ -1496,7 +1520,8 @@ hipError_t launch_dense_coop_ra(int lpj, const KArgs &a, int B, bool resident, h
         default: return hipErrorInvalidValue;
     }
     const size_t lds = resident ? resident_lds(R + 1 + (a.has_pen ? 1 : 0), a.lds_tiles) : 0;
-    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s, resident ? kResidentThreads : kBlockThreads, lds,
+    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s,
+                        resident ? a.res_waves * kWaveSize : kBlockThreads, lds,
                         resident_lds_limit(R, lpj));
 }
 
@@ -1568,7 +1593,8 @@ hipError_t launch_csr_coop_r(const KArgs &a, int B, bool resident, hipStream_t s
     const void *f = a.acc128 ? csr_multi_kernel<R, u128, false>(resident)
                     : a.lane_f64 ? csr_multi_kernel<R, uint64_t, true>(resident)
                                  : csr_multi_kernel<R, uint64_t, false>(resident);
-    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s, resident ? kResidentThreads : kBlockThreads);
+    return launch_multi(f, static_cast<unsigned>(B) * a.nblk, a, R * a.limbs, s,
+                        resident ? a.res_waves * kWaveSize : kBlockThreads);
 }
 
 

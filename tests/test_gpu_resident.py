@@ -475,3 +475,55 @@ def test_contexts_of_one_kernel_in_two_threads():
     assert not errors, errors
     for s in solvers:
         s.close()
+
+
+# More clusters than compute units, one workgroup each: of four wavefronts with up
+# to 8 tiles (two per wavefront), of eight above; both sides of 256 clusters and of 8
+# tiles; binary64, 64- and 128-bit sums; ragged tiles; penalties; a tolerance.
+@pytest.mark.parametrize("clusters,tiles,r,k,span", [
+    (256, 8, 4, 32, 0), (257, 8, 4, 32, 0), (257, 9, 4, 32, 0), (600, 1, 8, 64, 0), (300, 5, 1, 4, 0), (300, 7, 6, 16, 12),
+    (300, 3, 5, 8, 36), (260, 8, 8, 12, 0), (260, 9, 3, 12, 0), (520, 2, 7, 40, 0), (300, 6, 8, 12, 12), (300, 4, 4, 7, 36)])
+def test_more_clusters_than_compute_units(clusters, tiles, r, k, span):
+    inst = _dense(clusters + tiles, max(1, tiles * (256 // k) - 1), k, r, n_clusters=clusters)
+    if span:
+        inst = _wide(inst, 3, span)
+    if tiles == 7:
+        inst = workloads.with_penalties(inst, 5)
+    _say(f"many clusters B={clusters} tiles={tiles} R={r} K={k} span={span}")
+    s = esp.Solver(inst)
+    assert s.loop_driver() == esp.ESP_MODE_RESIDENT
+    o = oracle.Oracle(inst)
+    for tol in (0.0, 1e-3):
+        ref = o.solve(iters=12, tol=tol, trace=True)
+        g = s.solve(s.prices(inst.lam0), 12, tol=tol, trace=True)
+        torch.cuda.synchronize()
+        assert s.device_status() == 0
+        assert np.array_equal(g["iters_done"].cpu().numpy(), ref["iters_done"])
+        assert np.array_equal(g["lam"].cpu().numpy(), ref["lam"])
+        assert np.array_equal(g["choice"].cpu().numpy(), ref["choice"])
+        if tol == 0.0:
+            assert np.array_equal(g["tr_U"].cpu().numpy(), ref["tr_U"])
+    s.close()
+
+
+def test_small_clusters_share_a_compute_unit():
+    """512 clusters of 4 tiles take hardly longer than 256 (in workgroups that fill
+    a compute unit 1.8 times as long)."""
+    us = []
+    for clusters in (512, 256):
+        inst = _dense(1, 32, 32, 4, n_clusters=clusters)
+        s = esp.Solver(inst)
+        lam = s.prices(inst.lam0)
+        t = []
+        for _ in range(21):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(5):
+                s.solve(lam, 200)
+            e1.record()
+            torch.cuda.synchronize()
+            t.append(e0.elapsed_time(e1) * 200.0)
+        us.append(sorted(t)[10])
+        s.close()
+    _say(f"200 iterations: {us[0]:.0f} us of 512 clusters, {us[1]:.0f} of 256")
+    assert us[0] < 1.4 * us[1]
