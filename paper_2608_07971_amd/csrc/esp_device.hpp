@@ -186,14 +186,20 @@ __device__ __forceinline__ A fx_of(float v, int sh) {
         // v * 2^-sh is a whole number below 2^63 in binary64: exact at each step
         return static_cast<A>(ldexp(static_cast<double>(v), -sh));
     } else {
-        constexpr int kMax = static_cast<int>(sizeof(A)) * 8 - 1;
+        // Shifts of 32-bit words only: a 64-bit shift whose amount lies in the last
+        // register allocated to the wavefront has read a wrong amount here (one instance
+        // of the demand kernel, with two workgroups on a compute unit).
         const uint32_t bits = __float_as_uint(v);
         const uint32_t e = bits >> 23;
         const uint32_t m = (bits & 0x7fffffu) | (e ? 0x800000u : 0u);
-        int s = (e ? static_cast<int>(e) : 1) - 150 - sh;
-        s = s > kMax ? kMax : (s < -kMax ? -kMax : s);       // (zero: m = 0 shifts to 0 either way)
-        const A mm = m;
-        return s >= 0 ? (mm << s) : (mm >> (-s));
+        const int s = (e ? static_cast<int>(e) : 1) - 150 - sh;      // (zero: m = 0, whatever s is)
+        const uint32_t x = m >> (s < 0 ? (s > -31 ? -s : 31) : 0);   // the bits shifted out are 0
+        const uint32_t up = s > 0 ? static_cast<uint32_t>(s) : 0u;
+        const uint32_t q = up >> 5, n = up & 31u;
+        const uint32_t lo = x << n, hi = (x >> 1) >> (31u - n);      // of the words q and q + 1
+        const uint32_t w0 = q == 0 ? lo : 0u, w1 = q == 1 ? lo : q == 0 ? hi : 0u;
+        const uint32_t w2 = q == 2 ? lo : q == 1 ? hi : 0u, w3 = q == 3 ? lo : q == 2 ? hi : 0u;
+        return (static_cast<A>((static_cast<uint64_t>(w3) << 32) | w2) << 64) | ((static_cast<uint64_t>(w1) << 32) | w0);
     }
 }
 

@@ -113,7 +113,8 @@ def test_csr_scan_edges(sizes, bits):
     (1, 4, 1, 1, 0), (63, 8, 3, 1, 1), (1023, 16, 8, 1, 1), (1024, 16, 5, 1, 1), (1025, 5, 7, 1, 1),
     (4095, 4, 2, 1, 1), (4097, 12, 6, 1, 1), (5000, 32, 4, 3, 2), (9001, 7, 8, 2, 3), (3000, 64, 8, 1, 0),
     (255, 4, 2, 1, 1), (257, 12, 6, 1, 1), (2499, 4, 4, 1, 1), (2500, 12, 3, 1, 1), (4999, 8, 1, 2, 2),
-    (5000, 4, 4, 2, 2), (8193, 16, 3, 1, 2), (40, 8, 6, 300, 0)])
+    (5000, 4, 4, 2, 2), (8193, 16, 3, 1, 2), (40, 8, 6, 300, 0), (56, 16, 5, 300, 0),
+    (100, 12, 8, 600, 0), (33, 5, 7, 600, 0), (70, 8, 4, 520, 0), (64, 4, 3, 520, 0), (90, 16, 2, 520, 0)])
 @pytest.mark.parametrize("wide", [False, True])
 def test_reduce_demand_edges(n_jobs, k, r, clusters, blocks, wide):
     inst = workloads.random_small(n_jobs + k, n_jobs, k, r, dense=k != 12, n_clusters=clusters)
