@@ -189,3 +189,38 @@ def test_jobs_of_several_gpus_are_placed_at_once():
         s.close()
     _say(f"a round of 300 jobs of 1 and 8 shares: {us[0]:.0f} and {us[1]:.0f} us")
     assert us[1] < 3.6 * us[0]
+
+
+# More clusters than compute units, two workgroups of the packing on one: clusters of
+# one and several groups of GPUs, next to each other in LDS.
+@pytest.mark.parametrize("clusters,n_jobs,gpus", [(300, 40, 700), (300, 90, 256), (300, 25, 1100)])
+def test_packing_more_clusters_than_compute_units(clusters, n_jobs, gpus):
+    _say(f"packing {clusters} clusters of {n_jobs} jobs on up to {gpus} GPUs")
+    inst = workloads.make("batched", n_jobs=n_jobs, n_clusters=clusters)
+    sizes = [gpus - (7 * b) % gpus for b in range(clusters)]
+    _compare(inst, workloads.iac_model(inst, gpus=sizes), 2, 1, clusters=[0, 1, 37, 255, 256, 257, 298, 299])
+
+
+def test_packing_of_clusters_sharing_a_compute_unit():
+    """A round of 300 clusters on 512 GPUs each takes hardly longer than one of 256
+    (with one workgroup on a compute unit 1.6 times as long)."""
+    us = []
+    for clusters in (300, 256):
+        inst = _with_penalty_inputs(workloads.make("batched", n_jobs=400, n_clusters=clusters))
+        model = workloads.iac_model(inst, gpus=[512] * clusters)
+        for f in ("sensitivity", "pressure", "tau_base"):
+            setattr(model, f, torch.as_tensor(getattr(model, f), device="cuda"))
+        s = esp.Solver(inst)
+        lam = s.prices(inst.lam0)
+        t = []
+        for _ in range(15):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            s.schedule(model, lam, 1, 0)
+            e1.record()
+            torch.cuda.synchronize()
+            t.append(e0.elapsed_time(e1) * 1e3)
+        us.append(sorted(t)[7])
+        s.close()
+    _say(f"a round of 300 and of 256 clusters: {us[0]:.0f} and {us[1]:.0f} us")
+    assert us[0] < 1.4 * us[1]
