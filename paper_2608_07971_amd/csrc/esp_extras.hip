@@ -486,8 +486,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_nearest(KArgs a, NearestArgs 
 // several takes its GPUs of a group at once: 300 jobs of 8 GPUs each on 2,048,
 // one round without iterations 508 -> 284 us against share after share).  Measured per
 // round against one wavefront that gathered and placed with the residuals in
-// LDS: 4,096 jobs on 512 GPUs (1,035 jobs tried) 870 -> 254 us, 32 clusters of
-// 4,096 jobs on 576..768 GPUs 1,256 -> 378 us.
+// LDS: 4,096 jobs on 512 GPUs (1,035 jobs tried) 870 -> 257 us, 32 clusters of
+// 4,096 jobs on 576..768 GPUs 1,256 -> 383 us.
 //
 // Shortcuts, all exact because residuals only shrink while jobs are placed:
 //  - a job that needs at least as much (GPU count, memory and compute per
